@@ -373,9 +373,8 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
     if (e != hipSuccess) return e; \
   } while (0)
 #define TIMED(kind, call) TRY(timed(kind, s, [&]() { return (call); }))
-  // (the sweep planner marks the large problems of a sweep's first pass itself)
-  if ((c.pass2 || !c.tebd) && c.chol && tebd_size_class(0, std::max(c.mmax, c.nmax), c.lmax) >= 2)
-    TIMED(PK_SCHEDULE, launch_chol_mark(probs, c, s));
+  // (the sweep planner marks the problems of a sweep's first pass itself)
+  if (c.chol && (c.pass2 || !c.tebd)) TIMED(PK_SCHEDULE, launch_chol_mark(probs, c, s));
   TIMED(PK_SCHEDULE, launch_schedule(probs, c, s));
   if (c.bounds_dev) TRY(bounds_ready(s));
   if (c.tebd) {
@@ -406,20 +405,29 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   TIMED(PK_SKETCH_AOM, sketch(SK_Y_FROM_OMEGA));
   // the first QR reveals the sketch's rank (column pivoting); the power
   // iterations keep that rank and orthonormalise without pivoting
-  // The large problems may take the Gram-based QR first (when their sketch
-  // is well conditioned every column is kept, as the pivoted QR would);
-  // the Householder kernels then take every problem it did not finish.
-  auto qr_step = [&](int which, int pivot) -> hipError_t {
-    // no problem of the batch can reach the Gram path's size classes: skip it
-    const int rows_max = which ? c.nmax : c.mmax;
-    if (c.chol && tebd_size_class(0, rows_max, c.lmax) >= 2) {
-      hipError_t er = timed(PK_QR, s, [&]() { return launch_chol_qr(probs, c, which, s); });
-      if (er != hipSuccess) return er;
+  // Every QR after the first is Gram-based: its columns are graded like the
+  // singular values, and scaled to unit length they are well conditioned.
+  // The first one's are not; in the standalone call and the FP32-product
+  // sweeps it tries the Gram (which then keeps every column, as the pivoted
+  // QR would), and the pivoted Householder kernels take what that refuses.
+  // The last QR of the range finder has to be orthonormal to rounding, and so
+  // has the basis that the Accuracy Check projects on.
+  // (FP32 products keep to their own Gram-based QR, and to the Householder
+  // kernels for what that does not take.)
+  auto qr_step = [&](int which, bool first, bool last) -> hipError_t {
+    const int mode = (last ? QRM_STRICT : 0) | (first ? QRM_FIRST : 0);
+    const bool gram = c.mixed ? gram_f32_any(c, which) : !first || c.chol;
+    if (gram) {
+      const hipError_t er = timed(PK_QR, s, [&]() {
+        return c.mixed ? launch_gram_f32(probs, c, which, s) : launch_gram_qr(probs, c, which, mode, s);
+      });
+      if (er != hipSuccess || (!first && !c.mixed && !gram_on_queue(c, which))) return er;
     }
-    const int gate = c.chol && tebd_size_class(0, rows_max, c.lmax) >= 2 ? 2 : 0;
-    return timed(PK_QR, s, [&]() { return launch_qr(probs, c, which, 0, pivot, s, gate); });
+    return timed(PK_QR, s, [&]() {
+      return launch_qr(probs, c, which, 0, first, s, gram ? 2 : 0);
+    });
   };
-  TRY(qr_step(0, 1));
+  TRY(qr_step(0, true, c.q == 0 || c.acc_count != nullptr));
   if (c.acc_count) {
     // Accuracy Check rounds: probe, decide, orthonormalise the grown bases;
     // the host reads how many problems still probe after each round, and
@@ -450,19 +458,15 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   }
   for (int j = 0; j < c.q; ++j) {
     TIMED(PK_SKETCH_AHQ, sketch(SK_YT_FROM_Y));
-    TRY(qr_step(1, 0));
+    TRY(qr_step(1, false, false));
     TIMED(PK_SKETCH_AQT, sketch(SK_Y_FROM_YT));
-    TRY(qr_step(0, 0));
+    TRY(qr_step(0, false, j + 1 == c.q));
   }
   TIMED(PK_SKETCH_AHQ, launch_sketch(probs, c, SK_YT_FROM_Y, s));  // B^H = A^H Q
   // B^H = Q_B R_B in column order: the one-sided Jacobi on R_B^H that follows
   // converges in as many sweeps as after a pivoted QR, and the QR is cheaper.
-  // The large problems try the Gram-based QR first (R_B = R_2 R_1).
-  {
-    const bool gram_r = c.chol && tebd_size_class(0, c.nmax, c.lmax) >= 2;
-    if (gram_r) TIMED(PK_QR_R, launch_chol_qr(probs, c, 1, s, 1));
-    TIMED(PK_QR_R, launch_qr(probs, c, 1, 1, 0, s, gram_r ? 2 : 0));
-  }
+  TIMED(PK_QR_R, launch_gram_qr(probs, c, 1, QRM_STRICT | QRM_WANT_R, s));
+  if (gram_on_queue(c, 1)) TIMED(PK_QR_R, launch_qr(probs, c, 1, 1, 0, s, 2));
   {
     // the small SVD works on the revealed rank, anywhere in [1, l1]; each
     // launch ends with the truncation of its problems
@@ -532,9 +536,9 @@ tebd_status enqueue_sweep(const tebd_mps* mps, const tebd_z* gates, int64_t gate
   // thread, with a quarter of headroom: any grid covers every tile (the
   // launches are persistent), so the estimate only affects speed.
   static thread_local int32_t last_tiles[2][TK_COUNT] = {
-      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1},
-      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1}};
-  static_assert(TK_COUNT == 16, "one -1 per tile kind above");
+      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1},
+      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1}};
+  static_assert(TK_COUNT == 18, "one -1 per tile kind above");
   if (c.adaptive == 3) {
     c.acc_count = c.retry_count + kAccCountSlot;
     c.acc_lcap = int32_t(pl.lcap);

@@ -335,61 +335,6 @@ hipError_t launch_sketch_f32(Prob* probs, const Common& c, int which, hipStream_
   return hipGetLastError();
 }
 
-// --------------------------------------------------------------------------
-// Gram-based QR (CholeskyQR2) of the large problems, the tile-queue parts:
-// G = Y^H Y into C (l x l), and Q = Y R^-1 into Qc with R^-1 (upper
-// triangular, from k_chol) in J.  WHICH selects the m x l sketch Y (bit 1 of
-// P.chol) or the n x l sketch Yt (bit 2); in the second pass only the
-// problems whose first pass succeeded take part.
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_gram(Prob* probs, const int32_t* offs, int nprob, int tebd,
-                                              int pass) {
-  __shared__ zt smem[CfgSk::lds_elems];
-  for_each_tile<TK_GRAM>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
-    if (!(P.chol & (WHICH ? 2 : 1)) || (pass && !P.chol_ok)) return;
-    const int rows = WHICH ? P.n : P.m;
-    const zt* Yc = WHICH ? P.Yt : P.Y;
-    LdAdjColA la{Yc, rows};
-    LdColB lb{Yc, rows};
-    StCol st{P.C, P.l};
-    zgemm_tile<CfgSk>(M, N, rows, m0, n0, la, lb, st, smem);
-  });
-}
-
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_qapply(Prob* probs, const int32_t* offs, int nprob,
-                                                int tebd) {
-  __shared__ zt smem[CfgSk::lds_elems];
-  for_each_tile<WHICH ? TK_QAPN : TK_QAPM>(probs, offs, nprob, tebd,
-                                           [&](Prob& P, int M, int N, int m0, int n0, int) {
-    if (!P.chol_ok) return;
-    const int rows = WHICH ? P.n : P.m;
-    LdColA la{WHICH ? P.Yt : P.Y, rows};
-    LdColB lb{P.J, P.l};
-    StCol st{P.Qc, rows};
-    zgemm_tile<CfgSk>(M, N, P.l, m0, n0, la, lb, st, smem);
-  });
-}
-
-hipError_t launch_gram(Prob* probs, const Common& c, int which, int pass, hipStream_t s) {
-  const dim3 g(grid_for(c, TK_GRAM));
-  if (which)
-    TEBD_LAUNCH("k_gram<1>", k_gram<1>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, pass);
-  else
-    TEBD_LAUNCH("k_gram<0>", k_gram<0>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, pass);
-  return hipGetLastError();
-}
-
-hipError_t launch_qapply(Prob* probs, const Common& c, int which, hipStream_t s) {
-  if (which)
-    TEBD_LAUNCH("k_qapply<1>", k_qapply<1>, dim3(grid_for(c, TK_QAPN)), dim3(256), 0, s, probs,
-                c.offs, c.nprob, c.tebd);
-  else
-    TEBD_LAUNCH("k_qapply<0>", k_qapply<0>, dim3(grid_for(c, TK_QAPM)), dim3(256), 0, s, probs,
-                c.offs, c.nprob, c.tebd);
-  return hipGetLastError();
-}
-
 // The FP64 sketch products on 64 x 64 output tiles (fewer operand reloads
 // for large problems; chosen per launch by the autotune cache).
 template <int WHICH, class Cfg, int KM, int KN>

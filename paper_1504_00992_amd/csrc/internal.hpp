@@ -42,9 +42,9 @@ struct Prob {
   // probe column of the Gaussian stream, capacity of the basis, and 1 while
   // the basis grew this round (its QR runs)
   int32_t ac_r, ac_col, ac_cap, ac_grow;
-  // Gram-based QR (CholeskyQR2) of the large problems: eligible in this
-  // pipeline, and 1 while the current QR's Gram passes have succeeded
-  int32_t chol, chol_ok;
+  // Gram-based QR: kGram* bits (where its steps run), 1 while the current QR
+  // needs no Householder kernel, and 1 when its second pass is wanted
+  int32_t chol, chol_ok, chol_again;
   // Gate groups (TEBD): consecutive problems of one bond that share its gate
   // form one product G [Theta_1 | Theta_2 | ...] over all their columns.
   // gtot: the group's columns (every member), gn: members (the first member
@@ -68,7 +68,7 @@ struct Prob {
   zt* X;         // l x l column-major: left vectors of the small SVD, sorted
   zt* W;         // l x l column-major: right rotation, sorted
   zt* qru;       // 2 max(m, n): reflectors of the global-memory QR beyond its LDS rows
-  zt* Qc;        // max(m, n) x l column-major: Q of the Gram-based QR (then swapped with Y or Yt)
+  zt* Qc;        // max(m, n) x l elements: partial Gram matrices of the tile-queue QR (or null)
   double* sig;   // l: singular values sorted descending
   int32_t* piv;  // l: column order of the QR of B^H (B^H P = Q_B R_B; P = I unless pivoted)
   double* part;  // npart Frobenius partial sums
@@ -101,7 +101,7 @@ struct Prob {
   int32_t tape_ldu, tape_ldvh;
 };
 
-constexpr int TK_COUNT_MAX = 16;  // tile kinds of the forward pipeline (enum below)
+constexpr int TK_COUNT_MAX = 18;  // tile kinds of the forward pipeline (enum below)
 
 // Parameters of a launch sequence that are common to all problems.
 struct Common {
@@ -124,8 +124,8 @@ struct Common {
   int32_t* retry_count;  // device: problems whose first stage was rejected (adaptive rank)
   int32_t* bounds_dev = nullptr;  // host-mapped pinned memory: k_schedule writes {min, max}
                                   // of m, n, l1 there, then the tile total of every kind
-  int32_t ktiles[TK_COUNT_MAX] = {-1, -1, -1, -1, -1, -1, -1, -1,
-                                  -1, -1, -1, -1, -1, -1, -1, -1};  // host copy of the totals (-1: unknown)
+  int32_t ktiles[TK_COUNT_MAX] = {-1, -1, -1, -1, -1, -1, -1, -1, -1,
+                                  -1, -1, -1, -1, -1, -1, -1, -1, -1};  // host copy of the totals (-1: unknown)
   int32_t* offs;     // device: per tile kind, exclusive prefix sums of tile counts [nprob + 1]
   int32_t grid;      // workgroups of the persistent contraction launches (multiple of 8)
   // TEBD sweeps: the capacity sizes (d_max chi_cap rows, the fixed-rank sketch
@@ -139,7 +139,7 @@ struct Common {
   int32_t acc_lcap = 0;          // Accuracy Check: largest basis width (QR classes)
   int32_t acc_r = 0;             // Accuracy Check: probe width
   int32_t retry_read = 0;        // enqueue the host read of *retry_count after the truncation
-  int32_t chol = 0;              // 1: Gram-based QR (CholeskyQR2) for the large problems
+  int32_t chol = 0;              // 1: the first QR tries the Gram, the large sketches use the tile queue
 };
 
 // Kernel-level event timing for tebd_profile_enable / tebd_profile_read:
@@ -187,12 +187,14 @@ enum {
   TK_ACB = 8,    // Accuracy Check: m x r probe products A Omega_r
   TK_SKM_W = 9,  // TK_SKM on 64 x 64 tiles (the wide sketch variant)
   TK_SKN_W = 10, // TK_SKN on 64 x 64 tiles
-  TK_GRAM = 11,  // Gram-based QR: l x l Gram matrices Y^H Y
-  TK_QAPM = 12,  // Gram-based QR: m x l products Y R^-1
-  TK_QAPN = 13,  // Gram-based QR: n x l products Yt R^-1
+  TK_GRAM = 11,  // Gram-based QR: partial l x l Gram matrices Y^H Y over chunks of rows
+  TK_QAPM = 12,  // Gram-based QR: m x l products Y R^-1, by strips of rows
+  TK_QAPN = 13,  // Gram-based QR: n x l products Yt R^-1, by strips of rows
   TK_SKM_S = 14, // TK_SKM on 16 x 16 tiles (the split-depth sketch variant)
   TK_SKN_S = 15, // TK_SKN on 16 x 16 tiles
-  TK_COUNT = 16
+  TK_GQ_L = 16,  // Gram-based QR: one item per problem of a workgroup
+  TK_GQ_S = 17,  // Gram-based QR: one item per problem of a wavefront
+  TK_COUNT = 18
 };
 
 static_assert(TK_COUNT == TK_COUNT_MAX, "Common::ktiles holds one total per kind");
@@ -244,6 +246,48 @@ inline int32_t grid_for(const Common& c, int kind, int kind2 = -1) {
 }
 
 
+// Gram-based QR: where the steps of a problem run.
+enum {
+  kGramTileM = 1,  // the m x l sketch on the tile queue
+  kGramTileN = 2,  // the n x l sketch on the tile queue
+  kGramFirst = 4,  // the first QR tries the Gram before the pivoted Householder QR
+  kGramF32M = 8,   // FP32 products: the m x l sketch takes launch_gram_f32
+  kGramF32N = 16   // FP32 products: the n x l sketch takes launch_gram_f32
+};
+// rows l^2 beyond which a sketch's Gram-based QR is spread over the chip
+// (three or four launches) instead of run by one workgroup (one launch).
+// Measured, the six QRs of a truncation, one workgroup / tile queue: 256 x 30
+// (230400) 217 / 250 us, 512 x 20 (204800) 310 / 240, 256 x 40 (409600)
+// 348 / 306, 512 x 58 915 / 417, 2048 x 20 958 / 327.
+constexpr int64_t kGramQueueWork = 200000;
+// The padded 16 x 16 blocks of the factor need four l x l buffers (k_chol),
+// which hold one block from l = 8 on.
+constexpr int64_t kGramQueueMinL = 8;
+__host__ __device__ inline bool gram_queue_size(int64_t rows, int64_t l) {
+  return l >= kGramQueueMinL && rows * l * l > kGramQueueWork;
+}
+// The fewest rows of such a sketch of l columns.
+inline int gram_queue_rows(int l) {
+  return l >= kGramQueueMinL ? int(kGramQueueWork / (int64_t(l) * l)) + 1 : INT32_MAX;
+}
+// Problems whose Gram-based QRs one wavefront does (both sketches).
+constexpr int kGqSmallRows = 64;
+__host__ __device__ inline bool gram_small(int m, int n, int l) {
+  return l <= 16 && m <= kGqSmallRows && n <= kGqSmallRows;
+}
+// Row chunks of a Gram matrix on the tile queue: the l x l output alone has
+// too few tiles to fill the chip.  Their partial sums live in Qc (at most
+// max(m, n) / l of them fit) or, without it, one chunk goes straight to C.
+constexpr int kGramTile = 32, kGramMaxChunks = 8;
+__host__ __device__ inline int gram_blocks(int l) { return (l + kGramTile - 1) / kGramTile; }
+__host__ __device__ inline int gram_chunks(int rows, int l, bool room) {
+  if (!room) return 1;
+  const int by_room = rows / l, by_rows = rows / 128;
+  int n = by_room < by_rows ? by_room : by_rows;
+  n = n < kGramMaxChunks ? n : kGramMaxChunks;
+  return n < 1 ? 1 : n;
+}
+
 // Launchers (defined in the .hip files).  All enqueue on `s` and return the
 // first HIP error met, or hipSuccess.
 hipError_t launch_plan_sweep(Prob* probs, const Common& c, const tebd_mps& mps, const zt* gates,
@@ -270,13 +314,24 @@ hipError_t launch_sketch_f32(Prob* probs, const Common& c, int which, hipStream_
 // gate 2: only the problems the Gram-based QR did not finish.
 hipError_t launch_qr(Prob* probs, const Common& c, int which, int want_r, int pivot, hipStream_t s,
                      int gate = 0);
-// Gram-based QR (CholeskyQR2) of the large problems of a QR step (which: 0
-// the m x l sketch Y, 1 the n x l sketch Yt), before launch_qr(..., gate 2).
-// want_r: also R (into Rb, column order) for the QR of B^H.
-hipError_t launch_chol_qr(Prob* probs, const Common& c, int which, hipStream_t s, int want_r = 0);
+// Gram-based QR of a QR step (which: 0 the m x l sketch Y, 1 the n x l sketch
+// Yt) of every problem, by one workgroup each or, for the large sketches
+// (gram_bits), on the tile queue.  mode: QRM_* bits.  Problems it leaves to
+// the Householder kernels (launch_qr with gate 2) have chol_ok = 0.
+enum {
+  QRM_FIRST = 1,   // the QR of Y0 = A Omega: the Householder kernels reveal the rank of what it refuses
+  QRM_STRICT = 2,  // the columns must be orthonormal to rounding (a second pass where one is not enough)
+  QRM_WANT_R = 4   // also R (into Rb, column order)
+};
+hipError_t launch_gram_qr(Prob* probs, const Common& c, int which, int mode, hipStream_t s);
+// Whether any problem of the batch may take the tile queue for this sketch.
+bool gram_on_queue(const Common& c, int which);
+// The range finder's QRs of the FP32-product path, QR classes 2 and 3 (the
+// others, and what it refuses, stay with launch_qr, gate 2 here too), and
+// whether any problem of the batch is in those classes.
+hipError_t launch_gram_f32(Prob* probs, const Common& c, int which, hipStream_t s);
+bool gram_f32_any(const Common& c, int which);
 hipError_t launch_chol_mark(Prob* probs, const Common& c, hipStream_t s);
-hipError_t launch_gram(Prob* probs, const Common& c, int which, int pass, hipStream_t s);
-hipError_t launch_qapply(Prob* probs, const Common& c, int which, hipStream_t s);
 // Accuracy Check round: B = A Omega_r into the columns after the basis, then
 // the probe residual, the decision and the growth of the basis.
 hipError_t launch_acc_probe(Prob* probs, const Common& c, hipStream_t s);
@@ -302,7 +357,6 @@ __host__ __device__ inline size_t slab_bytes(int64_t m, int64_t n, int64_t l, in
   size_t b = 0;
   const size_t z = sizeof(zt);
   if (tebd) b += align256(m * n * z);  // A (a TEBD sweep keeps Theta in a region of its own)
-  // with the Gram-based QR, Y, Yt and Qc trade places: each holds max(m, n) rows
   const int64_t rows_y = (!tebd || mixed) && n > m ? n : m;
   const int64_t rows_yt = (!tebd || mixed) && m > n ? m : n;
   b += align256(n * l * z);          // Omega
@@ -310,7 +364,7 @@ __host__ __device__ inline size_t slab_bytes(int64_t m, int64_t n, int64_t l, in
   b += align256(rows_yt * l * z);    // Yt
   b += 5 * align256(l * l * z);      // Rb, C, J, X, W
   b += align256(2 * (m > n ? m : n) * z);  // reflector staging of the global-memory QR
-  if (!tebd || mixed) b += align256((m > n ? m : n) * l * z);  // Qc of the Gram-based QR
+  if (!tebd || mixed) b += align256((m > n ? m : n) * l * z);  // partial Gram matrices
   b += align256(l * sizeof(double)); // sig
   b += align256(l * sizeof(int32_t));  // piv
   b += align256(npart * sizeof(double));

@@ -32,14 +32,18 @@ __device__ __forceinline__ int updated_bond_extent(const Prob& P) {
   return e < P.chi_cap ? e : P.chi_cap;
 }
 
+// Whether the Gram of a problem's sketches may be split into row chunks.
+__device__ __forceinline__ bool gram_room(const Prob& P) {
+  return P.Qc && !(P.chol & (kGramF32M | kGramF32N));
+}
+
 // Output shape of each contraction kind for problem P (0 x 0 when skipped).
 template <>
 struct TileKinds<Prob> {
   static constexpr int count = TK_COUNT;
   static constexpr bool small_tiles(int kind) {
     return kind == TK_SKM || kind == TK_SKN || kind == TK_FORMU || kind == TK_FORMV ||
-           kind == TK_THETA || kind == TK_ACB || kind == TK_GRAM || kind == TK_QAPM ||
-           kind == TK_QAPN;
+           kind == TK_THETA || kind == TK_ACB || kind == TK_GRAM;
   }
   static constexpr int tile_m(int kind) {
     return kind == TK_GATE                      ? kGateTileM
@@ -114,19 +118,37 @@ struct TileKinds<Prob> {
           N = P.ac_r;
         }
         break;
-      case TK_GRAM:
-        if (P.chol) M = N = P.l;
+      case TK_GRAM:  // the chunks of either sketch side by side (FP32 products: one chunk)
+        if (P.chol & (kGramF32M | kGramF32N)) {
+          M = N = P.l;
+        } else if (const int by = P.chol & 3) {
+          M = P.l;
+          const int rows = by == 1 ? P.m : by == 2 ? P.n : P.m > P.n ? P.m : P.n;
+          N = gram_chunks(rows, P.l1, gram_room(P)) * gram_blocks(P.l) * kGramTile;
+        }
         break;
-      case TK_QAPM:
-        if (P.chol & 1) {
+      case TK_GQ_L:  // classes by the width the pass started with: it shrinks as QRs run
+        M = N = gram_small(P.m, P.n, P.l1) ? 0 : 1;
+        break;
+      case TK_GQ_S:
+        M = N = gram_small(P.m, P.n, P.l1) ? 1 : 0;
+        break;
+      case TK_QAPM:  // strips of 64 rows; FP32 products: a 64 x 64 tile here is a 32 x 32 one
+        if (P.chol & kGramF32M) {
+          M = 2 * P.m;
+          N = 2 * P.l;
+        } else if (P.chol & kGramTileM) {
           M = P.m;
-          N = P.l;
+          N = 1;
         }
         break;
       case TK_QAPN:
-        if (P.chol & 2) {
+        if (P.chol & kGramF32N) {
+          M = 2 * P.n;
+          N = 2 * P.l;
+        } else if (P.chol & kGramTileN) {
           M = P.n;
-          N = P.l;
+          N = 1;
         }
         break;
       default:

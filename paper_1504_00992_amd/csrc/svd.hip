@@ -1,0 +1,646 @@
+// Small SVD of the projected matrix by one-sided Jacobi, and the truncation
+// rule with lambda renormalisation (one workgroup per problem).
+//
+// Paper: Tamascelli, Rosenbach, Plenio, arXiv:1504.00992.  The SVD of B = Q^H A
+// of Sec. IV step ii (computed as B^H = Q_B R_B, then a one-sided Jacobi SVD of
+// R_B^H, which keeps small singular values to high relative accuracy), and the
+// discarded weight of Sec. II.C, Eq. (defdiscweigt), evaluated with the
+// Frobenius identity of Sec. IV.
+#include <cfloat>
+#include <type_traits>
+
+#include "householder.hpp"
+#include "kinds.hpp"
+#include "sidestreams.hpp"
+
+namespace tebd {
+
+// Column kernels over the strided rows r0, r0 + G, ... < rows, four rows per
+// iteration with independent partial sums, so that the LDS loads of four
+// rows are in flight together instead of one load latency per row.
+__device__ __forceinline__ zt col_dot(const zt* u, const zt* y, int r0, int rows, int G) {
+  double a0 = 0.0, b0 = 0.0, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0, a3 = 0.0, b3 = 0.0;
+  int r = r0;
+  for (; r + 3 * G < rows; r += 4 * G) {
+    const zt u0 = u[r], u1 = u[r + G], u2 = u[r + 2 * G], u3 = u[r + 3 * G];
+    const zt y0 = y[r], y1 = y[r + G], y2 = y[r + 2 * G], y3 = y[r + 3 * G];
+    zdot_acc(u0, y0, a0, b0);
+    zdot_acc(u1, y1, a1, b1);
+    zdot_acc(u2, y2, a2, b2);
+    zdot_acc(u3, y3, a3, b3);
+  }
+  for (; r < rows; r += G) zdot_acc(u[r], y[r], a0, b0);
+  return make_double2((a0 + a1) + (a2 + a3), (b0 + b1) + (b2 + b3));
+}
+
+__device__ __forceinline__ double col_norm2(const zt* y, int r0, int rows, int G) {
+  double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0;
+  int r = r0;
+  for (; r + 3 * G < rows; r += 4 * G) {
+    n0 += zabs2(y[r]);
+    n1 += zabs2(y[r + G]);
+    n2 += zabs2(y[r + 2 * G]);
+    n3 += zabs2(y[r + 3 * G]);
+  }
+  for (; r < rows; r += G) n0 += zabs2(y[r]);
+  return (n0 + n1) + (n2 + n3);
+}
+
+// --------------------------------------------------------------------------
+// Small SVD of B (l x n) from B^H = Q_B R_B: one-sided Jacobi on C = R_B^H
+// (l x l).  Column pairs are rotated in the round-robin order of the circle
+// method, l/2 disjoint pairs per round, one pair per wavefront at a time.
+// A pair (p, q) with Gram entries a = |c_p|^2, b = |c_q|^2, g = c_p^H c_q is
+// rotated when |g| > tol sqrt(a b):  phi = arg g, zeta = (b - a) / (2|g|),
+// t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), cs = 1/sqrt(1+t^2), sn = t cs,
+//   c_p <- cs c_p - sn e^{-i phi} c_q,  c_q <- sn c_p + cs e^{-i phi} c_q,
+// which zeroes the (p, q) Gram entry.  The same rotation accumulates into J.
+// At convergence C J = X Sigma with orthogonal columns, so
+// B = X Sigma (Q_B J)^H: left vectors X (normalised columns), values Sigma,
+// right vectors Q_B J (formed later).  Outputs are sorted descending.
+// C and J live in LDS when 2 l^2 fits, else in global memory; a pair's
+// columns are held in registers (l <= 64 * REGS) for the whole rotation.
+
+// Rotation of a column pair with Gram entries a = |c_p|^2, b = |c_q|^2 and
+// g = c_p^H c_q (given as gr + i gi): false when |g| <= tol sqrt(a b).
+// Otherwise zeta = (b - a) / (2|g|), t = sign(zeta) / (|zeta| + sqrt(1 +
+// zeta^2)), cs = 1 / sqrt(1 + t^2), sn = t cs, em = e^{-i arg g}, and
+// ag = |g| (the carried norms move by t |g|).  Reciprocal square roots keep
+// the chain of dependent operations short.
+__device__ __forceinline__ bool jacobi_rotation(double gr, double gi, double a, double b,
+                                                double tol, double& ag, double& t, double& cs,
+                                                double& sn, zt& em) {
+  const double g2 = gr * gr + gi * gi;
+  if (!(g2 > tol * tol * (a * b)) || g2 == 0.0) return false;
+  const double ig = rsqrt(g2);  // 1 / |g|
+  ag = g2 * ig;
+  const double zeta = 0.5 * (b - a) * ig;
+  t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
+  cs = rsqrt(1.0 + t * t);
+  sn = t * cs;
+  em = make_double2(gr * ig, -gi * ig);
+  return true;
+}
+
+// Round-robin (circle method) pairing of lp players: position 0 stays, the
+// others rotate by one place per round.  pos < lp and round < lp - 1, so
+// one conditional subtraction reduces modulo lp - 1 (no integer division).
+__device__ __forceinline__ int circle_player(int pos, int round, int lp) {
+  if (pos == 0) return 0;
+  const int x = pos - 1 + round;
+  return 1 + (x >= lp - 1 ? x - (lp - 1) : x);
+}
+
+
+// Column norms are recomputed exactly at the start of every sweep and then
+// carried through the rotations analytically (a' = a - t|g|, b' = b + t|g|),
+// so each pair needs a single complex reduction, g = c_p^H c_q.
+// A sweep whose rotations all turned by less than about 1e-7 rad (|g|^2 <=
+// kSmallTurn a b) leaves the columns so close to orthogonal that the next
+// sweep would likely rotate nothing; instead of running that sweep,
+// pairs_below_tol tests every pair of the current C at once.
+constexpr double kSmallTurn = 1e-14;
+
+// True when no pair of columns of C (column c at C + c S) would be rotated:
+// every |c_p^H c_q| <= tol |c_p| |c_q| with nrm[c] = |c_c|^2 recomputed and
+// visible to the workgroup (the test of jacobi_rotation).  The verdict of a
+// sweep that rotates nothing, from l (l - 1) / 2 independent dot products
+// instead of l - 1 dependent rounds.  Whole workgroup (one barrier).
+template <int NT>
+__device__ __forceinline__ bool pairs_below_tol(const zt* C, int S, int l, double tol,
+                                                const double* nrm) {
+  // thread t: columns {2a, 2a + 1} x {2b, 2b + 1}, a <= b, four dot products
+  // per pass over the rows (a missing last column repeats the one before)
+  const int nh = (l + 1) / 2;
+  int bad = 0;
+  for (int t = threadIdx.x; t < nh * nh; t += NT) {
+    const int a = t / nh, b = t - a * nh;
+    if (a > b) continue;
+    const int p0 = 2 * a, q0 = 2 * b;
+    const int p1 = p0 + 1 < l ? p0 + 1 : p0, q1 = q0 + 1 < l ? q0 + 1 : q0;
+    const zt* x0 = C + size_t(p0) * S;
+    const zt* x1 = C + size_t(p1) * S;
+    const zt* y0 = C + size_t(q0) * S;
+    const zt* y1 = C + size_t(q1) * S;
+    double g[4][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+    for (int r = 0; r < l; ++r) {
+      const zt u0 = x0[r], u1 = x1[r], v0 = y0[r], v1 = y1[r];
+      zdot_acc(u0, v0, g[0][0], g[0][1]);
+      zdot_acc(u0, v1, g[1][0], g[1][1]);
+      zdot_acc(u1, v0, g[2][0], g[2][1]);
+      zdot_acc(u1, v1, g[3][0], g[3][1]);
+    }
+    const int ps[4] = {p0, p0, p1, p1}, qs[4] = {q0, q1, q0, q1};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double g2 = g[i][0] * g[i][0] + g[i][1] * g[i][1];
+      if (ps[i] < qs[i] && g2 > tol * tol * (nrm[ps[i]] * nrm[qs[i]]) && g2 != 0.0) bad = 1;
+    }
+  }
+  return __syncthreads_or(bad) == 0;
+}
+
+// One pair per wavefront at a time; ALL_PAIRS: after a sweep of small turns,
+// pairs_below_tol may end the iteration without the sweep that rotates
+// nothing.
+template <int NT, int REGS, bool ALL_PAIRS>
+__device__ __forceinline__ void jacobi_core(zt* C, zt* J, int l, int& converged_out,
+                                            int* rotated, int* large, double* nrm) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lp = l + (l & 1);
+  const double tol = DBL_EPSILON * sqrt(double(l));
+  constexpr int kMaxSweeps = 40;
+  bool converged = (l == 1);
+  for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
+    for (int c = wave; c < l; c += NW) {
+      double s = 0.0;
+#pragma unroll
+      for (int i = 0; i < REGS; ++i) {
+        const int r = lane + 64 * i;
+        if (r < l) s += zabs2(C[size_t(c) * l + r]);
+      }
+      s = wave_sum(s);
+      if (lane == 0) nrm[c] = s;
+    }
+    if (tid == 0) {
+      *rotated = 0;
+      *large = 0;
+    }
+    __syncthreads();
+    for (int round = 0; round < lp - 1; ++round) {
+      for (int pr = wave; pr < lp / 2; pr += NW) {
+        const int a = circle_player(pr, round, lp), b = circle_player(lp - 1 - pr, round, lp);
+        const int p = a < b ? a : b, q = a < b ? b : a;
+        if (q >= l) continue;
+        zt* cp = C + size_t(p) * l;
+        zt* cq = C + size_t(q) * l;
+        zt xp[REGS], xq[REGS];
+        double gr = 0.0, gi = 0.0;
+#pragma unroll
+        for (int i = 0; i < REGS; ++i) {
+          const int r = lane + 64 * i;
+          xp[i] = r < l ? cp[r] : make_double2(0.0, 0.0);
+          xq[i] = r < l ? cq[r] : make_double2(0.0, 0.0);
+          const zt t = zcmul(xp[i], xq[i]);
+          gr += t.x;
+          gi += t.y;
+        }
+        gr = wave_sum(gr);
+        gi = wave_sum(gi);
+        const double app = nrm[p], aqq = nrm[q];
+        double ag, t, cs, sn;
+        zt em;  // e^{-i phi}
+        if (!jacobi_rotation(gr, gi, app, aqq, tol, ag, t, cs, sn, em)) continue;
+#pragma unroll
+        for (int i = 0; i < REGS; ++i) {
+          const int r = lane + 64 * i;
+          if (r < l) {
+            const zt x = xp[i], y = zmul(em, xq[i]);
+            cp[r] = zrot_lo(x, y, cs, sn);
+            cq[r] = zrot_hi(x, y, cs, sn);
+          }
+        }
+        zt* jp = J + size_t(p) * l;
+        zt* jq = J + size_t(q) * l;
+#pragma unroll
+        for (int i = 0; i < REGS; ++i) {
+          const int r = lane + 64 * i;
+          if (r < l) {
+            const zt x = jp[r], y = zmul(em, jq[r]);
+            jp[r] = zrot_lo(x, y, cs, sn);
+            jq[r] = zrot_hi(x, y, cs, sn);
+          }
+        }
+        if (lane == 0) {
+          nrm[p] = fmax(app - t * ag, 0.0);
+          nrm[q] = aqq + t * ag;
+          *rotated = 1;
+          if (ag * ag > kSmallTurn * (app * aqq)) *large = 1;
+        }
+      }
+      __syncthreads();
+    }
+    converged = (*rotated == 0);
+    const bool turned_far = (*large != 0);
+    __syncthreads();
+    if (ALL_PAIRS && !converged && !turned_far) {
+      for (int c = wave; c < l; c += NW) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < REGS; ++i) {
+          const int r = lane + 64 * i;
+          if (r < l) s += zabs2(C[size_t(c) * l + r]);
+        }
+        s = wave_sum(s);
+        if (lane == 0) nrm[c] = s;
+      }
+      __syncthreads();
+      converged = pairs_below_tol<NT>(C, l, l, tol, nrm);
+    }
+  }
+  converged_out = converged ? 1 : 0;
+}
+
+// Column norms, descending order, and the sorted outputs X, W, sig.
+template <int NT>
+__device__ __forceinline__ void jacobi_finish(Prob& P, const zt* C, const zt* J, int l,
+                                              double* sig_s, int* perm_s) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int c = wave; c < l; c += NW) {
+    double s = 0.0;
+    for (int r = lane; r < l; r += 64) s += zabs2(C[size_t(c) * l + r]);
+    s = wave_sum(s);
+    if (lane == 0) sig_s[c] = sqrt(s);
+  }
+  __syncthreads();
+  for (int j = tid; j < l; j += NT) {
+    const double sj = sig_s[j];
+    int rank = 0;
+    for (int i = 0; i < l; ++i) {
+      const double si = sig_s[i];
+      rank += (si > sj) || (si == sj && i < j);
+    }
+    perm_s[rank] = j;
+  }
+  __syncthreads();
+  for (int e = tid; e < l * l; e += NT) {
+    const int c = e / l, r = e - c * l;
+    const int src = perm_s[c];
+    const double sv = sig_s[src];
+    const zt x = C[size_t(src) * l + r];
+    P.X[e] = sv > 0.0 ? zscale(x, 1.0 / sv) : make_double2(0.0, 0.0);
+    P.W[e] = J[size_t(src) * l + r];
+  }
+  for (int c = tid; c < l; c += NT) P.sig[c] = sig_s[perm_s[c]];
+}
+
+// --------------------------------------------------------------------------
+// Truncation: chi' = min(chi_max, smallest c with w(c) <= eps), where
+// w(c) = (||A||_F^2 - sum_{j<=c} s_j^2) / ||A||_F^2; eps <= 0 keeps
+// min(chi_max, l).  TEBD: lambda' = s / ||s_{1..chi'}|| and chi' are written
+// into the MPS.  Run by the whole workgroup of the problem's small SVD after
+// it (sorted(c): the c-th largest singular value, from LDS); the scans run
+// on thread 0 so the summation order is fixed.  The global reads (partial
+// sums, outer lambdas) are spread over the workgroup first: one thread
+// reading them one after another waited for each.
+constexpr int kTailChunk = 64;
+
+template <int NT, class Sorted>
+__device__ __forceinline__ void truncate_tail(Prob& P, int l, double eps, int tebd,
+                                              int32_t* retry_count, Sorted sorted, double* scan) {
+  __shared__ int chi_s, first_s;
+  __shared__ double norm_s, frob_s;
+  __shared__ double part_s[kTailChunk];
+  const int tid = threadIdx.x;
+  // ||A||_F^2 from the partial sums, the gate product's (TEBD) or k_frob's:
+  // loaded kTailChunk at a time, added by thread 0 in index order
+  const int npart =
+      tebd ? gate_partials(P.dl * P.dr, P.gcol0, P.chi_l * P.chi_r) : kFrobSlices;
+  __syncthreads();  // the singular values are in place
+  // one round of global reads: the first chunk of partial sums, and whether
+  // an outer lambda is at or below the floor (its inverse was taken as 0)
+  if (tid < kTailChunk && tid < npart) part_s[tid] = P.part[tid];
+  bool floor_hit = false;
+  if (tebd) {
+    if (P.lam_l)
+      for (int a = tid; a < P.chi_l; a += NT) floor_hit |= !(P.lam_l[a] > P.lambda_floor);
+    if (P.lam_r)
+      for (int b = tid; b < P.chi_r; b += NT) floor_hit |= !(P.lam_r[b] > P.lambda_floor);
+  }
+  floor_hit = __syncthreads_or(floor_hit) != 0;
+  double frob2 = 0.0;
+  for (int i0 = 0; i0 < npart; i0 += kTailChunk) {
+    if (i0 > 0) {
+      __syncthreads();  // the previous chunk is summed
+      if (tid < kTailChunk && i0 + tid < npart) part_s[tid] = P.part[i0 + tid];
+      __syncthreads();
+    }
+    if (tid == 0) {
+      const int n = npart - i0 < kTailChunk ? npart - i0 : kTailChunk;
+      for (int i = 0; i < n; ++i) frob2 += part_s[i];
+    }
+  }
+  // kept(c) = s_1^2 + ... + s_c^2 in index order (thread 0, into scan[c - 1]);
+  // then every c at once: w(c) = (||A||_F^2 - kept(c)) / ||A||_F^2, and chi'
+  // the smallest c <= cap with w(c) <= eps.  The same operations as one
+  // thread scanning c = 1, 2, ..., without its chain of divisions.
+  // A first stage that may still be retried only accepts a rank <= k1.
+  const bool can_retry = P.l2 > P.l1;
+  int cap = P.kcap < l ? P.kcap : l;
+  if (can_retry && P.k1 < cap) cap = P.k1;
+  if (tid == 0) {
+    double kept = 0.0;
+    for (int c = 0; c < l; ++c) {
+      const double sv = sorted(c);
+      kept += sv * sv;
+      scan[c] = kept;
+    }
+    frob_s = frob2;
+    first_s = INT32_MAX;
+  }
+  __syncthreads();
+  const double fr = frob_s;
+  int first = INT32_MAX;
+  bool nonfinite = false;
+  for (int c = tid + 1; c <= l; c += NT) {
+    nonfinite |= !isfinite(sorted(c - 1));
+    const double wc = fr > 0.0 ? (fr - scan[c - 1]) / fr : 0.0;
+    if (eps > 0.0 && c <= cap && wc <= eps && c < first) first = c;
+  }
+  if (first != INT32_MAX) atomicMin(&first_s, first);
+  nonfinite = __syncthreads_or(nonfinite) != 0;
+  if (tid == 0) {
+    int flags = P.flags;
+    P.frob2 = frob2;
+    const bool found = first_s != INT32_MAX;
+    const int chi = found ? first_s : cap;
+    // the discarded weight at chi' (or at cap when no c qualifies)
+    double w = fr > 0.0 ? (fr - scan[chi - 1]) / fr : 0.0;
+    const double nk = scan[chi - 1];  // the kept squares summed up to chi'
+    const bool finite = isfinite(frob2) && !nonfinite;
+    int out = chi;
+    if (can_retry && !(eps > 0.0 && found)) {
+      // stage 1 rejected: leave every output untouched, run stage 2
+      P.retry = 1;
+      if (retry_count) atomicAdd(retry_count, 1);
+      out = -1;
+    }
+    if (eps > 0.0 && !found) flags |= TEBD_DEV_CHI_BOUND;
+    if (!finite) flags |= TEBD_DEV_NONFINITE;
+    if (w < 0.0) w = 0.0;
+    if (floor_hit) flags |= TEBD_DEV_LAMBDA_FLOOR;
+    if (out >= 0) {
+      P.chi_new = chi;
+      P.flags = flags;
+      *P.disc = w;
+      *P.status = flags;
+      if (P.chi_out) *P.chi_out = chi;
+    }
+    chi_s = out;
+    norm_s = sqrt(nk);
+  }
+  __syncthreads();
+  const int chi = chi_s;
+  if (chi < 0) return;
+  if (tebd) {
+    const double inv = norm_s > 0.0 ? 1.0 / norm_s : 0.0;
+    for (int j = threadIdx.x; j < P.chi_cap; j += NT) P.lam_mid[j] = j < chi ? sorted(j) * inv : 0.0;
+    if (threadIdx.x == 0) *P.chi_slot = chi;
+  } else {
+    for (int j = threadIdx.x; j < P.kcap; j += NT) P.S[j] = j < chi ? sorted(j) : 0.0;
+  }
+}
+
+// Size classes of the small SVD, by l: 0 (l <= 32, 256 threads) and 1
+// (l <= 64, 512 threads) rotate every pair of a round at once (k_svd_pairs);
+// 2 (C and J in LDS) and 3 (global memory) rotate one pair per wavefront at
+// a time (jacobi_core).
+__host__ __device__ __forceinline__ int svd_class(int l) {
+  if (l <= 32) return 0;
+  if (l <= 64) return 1;
+  if (2 * l * l <= kLdsElems) return 2;
+  return 3;
+}
+
+// C and J in LDS with an odd column stride, and all l/2 pairs of a round
+// rotated at once: G = NT / (l/2 rounded up to a power of two) lanes per
+// pair, at most 16 (DPP sums only; for these two classes always 16).  Lane h
+// of a pair loads every G-th row of both columns of C and J into
+// registers, sums its part of g = c_p^H c_q, the group sum
+// combines them, and the same lanes rotate the rows they hold and store
+// them; one barrier per round.  Same rotation, tolerance, carried norms and
+// sweep limit as jacobi_core.
+constexpr int kPairGroupMax = 16;
+
+
+template <int NT, int CLS>
+__global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int tebd,
+                                                  int32_t* retry_count) {
+  extern __shared__ zt lds[];  // C, then J: l columns of stride l | 1 each
+  __shared__ double nrm[64];
+  __shared__ double sig_s[64];
+  __shared__ double srt_s[64];  // singular values in descending order
+  __shared__ int perm_s[64];
+  Prob& P = probs[blockIdx.x];
+  const int l = P.l;
+  if (l == 0 || svd_class(l) != CLS) return;
+  const int S = l | 1;
+  zt* Cs = lds;
+  zt* Js = lds + l * S;
+  const int tid = threadIdx.x;
+  const zt zero = make_double2(0.0, 0.0);  // value, never addressed
+  for (int e = tid; e < l * l; e += NT) {
+    const int c = e / l, r = e - c * l;
+    Cs[c * S + r] = zconj(P.Rb[size_t(r) * l + c]);
+    Js[c * S + r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+  }
+  const int lp = l + (l & 1);
+  // lanes per pair: l/2 <= NT / 16 pairs in these classes, so 16 each
+  constexpr int G = kPairGroupMax;
+  static_assert(NT / (CLS == 0 ? 16 : 32) >= kPairGroupMax, "pairs of a round fit at 16 lanes");
+  const int k = tid / G, h = tid - k * G;
+  int lc2 = 1;
+  while (lc2 < l) lc2 <<= 1;
+  const int GN = NT / lc2 < kPairGroupMax ? NT / lc2 : kPairGroupMax;  // lanes per column
+  const int cn = tid / GN, hn = tid - cn * GN;
+  const double tol = DBL_EPSILON * sqrt(double(l));
+  constexpr int kMaxSweeps = 40;
+  bool converged = (l == 1);
+  __syncthreads();
+  for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
+    double s = 0.0;
+    if (cn < l) s = col_norm2(Cs + cn * S, hn, l, GN);
+    s = group_sum(s, GN);
+    if (cn < l && hn == 0) nrm[cn] = s;
+    __syncthreads();
+    int any = 0, large = 0;
+    for (int round = 0; round < lp - 1; ++round) {
+      int p = 0, q = 0;
+      bool act = k < lp / 2;
+      if (act) {
+        const int a = circle_player(k, round, lp), b = circle_player(lp - 1 - k, round, lp);
+        p = a < b ? a : b;
+        q = a < b ? b : a;
+        act = q < l;
+      }
+      // rows h, h + G, ... < l: G = 16 here (l/2 <= NT / 16), so at most
+      // 32 / 16 or 64 / 16 of them
+      constexpr int RPR = (CLS == 0 ? 32 : 64) / kPairGroupMax;
+      zt x[RPR], y[RPR], xj[RPR], yj[RPR];
+      zt* cp = Cs + p * S;
+      zt* cq = Cs + q * S;
+      zt* jp = Js + p * S;
+      zt* jq = Js + q * S;
+      double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+      for (int i = 0; i < RPR; ++i) {
+        const int r = h + G * i;
+        const bool in = act && r < l;
+        x[i] = zload_if(in, cp + r);
+        y[i] = zload_if(in, cq + r);
+        xj[i] = zload_if(in, jp + r);
+        yj[i] = zload_if(in, jq + r);
+        zdot_acc(x[i], y[i], g0, g1);
+      }
+      const double gr = group_sum(g0, G), gi = group_sum(g1, G);
+      if (act) {
+        const double app = nrm[p], aqq = nrm[q];
+        double ag, t, cs, sn;
+        zt em;  // e^{-i phi}
+        if (jacobi_rotation(gr, gi, app, aqq, tol, ag, t, cs, sn, em)) {
+#pragma unroll
+          for (int i = 0; i < RPR; ++i) {
+            const int r = h + G * i;
+            if (r < l) {
+              const zt ey = zmul(em, y[i]), eyj = zmul(em, yj[i]);
+              cp[r] = zrot_lo(x[i], ey, cs, sn);
+              cq[r] = zrot_hi(x[i], ey, cs, sn);
+              jp[r] = zrot_lo(xj[i], eyj, cs, sn);
+              jq[r] = zrot_hi(xj[i], eyj, cs, sn);
+            }
+          }
+          if (h == 0) {
+            nrm[p] = fmax(app - t * ag, 0.0);
+            nrm[q] = aqq + t * ag;
+          }
+          any = 1;
+          if (ag * ag > kSmallTurn * (app * aqq)) large = 1;
+        }
+      }
+      __syncthreads();
+    }
+    const bool rotated = __syncthreads_or(any) != 0;
+    const bool turned_far = __syncthreads_or(large) != 0;
+    converged = !rotated;
+    if (rotated && !turned_far) {
+      double s2 = 0.0;
+      if (cn < l) s2 = col_norm2(Cs + cn * S, hn, l, GN);
+      s2 = group_sum(s2, GN);
+      if (cn < l && hn == 0) nrm[cn] = s2;
+      __syncthreads();
+      converged = pairs_below_tol<NT>(Cs, S, l, tol, nrm);
+    }
+  }
+  if (!converged && tid == 0) P.flags |= TEBD_DEV_JACOBI_NOCONV;
+  // singular values, descending order, sorted outputs
+  {
+    double s = 0.0;
+    if (cn < l) s = col_norm2(Cs + cn * S, hn, l, GN);
+    s = group_sum(s, GN);
+    if (cn < l && hn == 0) sig_s[cn] = sqrt(s);
+  }
+  __syncthreads();
+  if (tid < l) {
+    const double sj = sig_s[tid];
+    int rank = 0;
+    for (int i = 0; i < l; ++i) {
+      const double si = sig_s[i];
+      rank += (si > sj) || (si == sj && i < tid);
+    }
+    perm_s[rank] = tid;
+  }
+  __syncthreads();
+  for (int e = tid; e < l * l; e += NT) {
+    const int c = e / l, r = e - c * l;
+    const int src = perm_s[c];
+    const double sv = sig_s[src];
+    const zt x = Cs[src * S + r];
+    P.X[e] = sv > 0.0 ? zscale(x, 1.0 / sv) : zero;
+    P.W[e] = Js[src * S + r];
+  }
+  if (tid < l) {
+    const double v = sig_s[perm_s[tid]];
+    srt_s[tid] = v;
+    P.sig[tid] = v;
+  }
+  truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return srt_s[c]; }, nrm);
+}
+
+// Classes 2 and 3: one pair per wavefront at a time (jacobi_core), C and J
+// in LDS (LDS_CJ) or in the problem's global scratch.
+template <int NT, int REGS, bool LDS_CJ>
+__global__ __launch_bounds__(NT) void k_small_svd(Prob* probs, double eps, int tebd,
+                                                  int32_t* retry_count) {
+  extern __shared__ zt lds[];
+  __shared__ double sig_s[kMaxL];
+  __shared__ int perm_s[kMaxL];
+  __shared__ int rotated, large_turn;
+  __shared__ double nrm[kMaxL];
+  Prob& P = probs[blockIdx.x];
+  const int l = P.l;
+  if (l == 0 || svd_class(l) != (LDS_CJ ? 2 : 3)) return;
+  zt* C = LDS_CJ ? lds : P.C;
+  zt* J = LDS_CJ ? lds + l * l : P.J;
+  for (int e = threadIdx.x; e < l * l; e += NT) {
+    const int c = e / l, r = e - c * l;
+    C[e] = zconj(P.Rb[size_t(r) * l + c]);
+    J[e] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+  }
+  __syncthreads();
+  int converged;
+  // the all-pairs test only where C is in LDS (from global memory it costs
+  // about the sweep it would save)
+  jacobi_core<NT, REGS, LDS_CJ>(C, J, l, converged, &rotated, &large_turn, nrm);
+  if (!converged && threadIdx.x == 0) P.flags |= TEBD_DEV_JACOBI_NOCONV;
+  jacobi_finish<NT>(P, C, J, l, sig_s, perm_s);
+  truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return sig_s[perm_s[c]]; }, nrm);
+}
+
+hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
+  static const hipError_t attr = []() {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_small_svd<1024, 2, true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       int(size_t(kLdsElems) * sizeof(zt)));
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_svd_pairs<512, 1>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                               int(2 * 64 * 65 * sizeof(zt)));
+  }();
+  if (attr != hipSuccess) return attr;
+  typedef void (*Launch)(hipStream_t, Prob*, int, double, int, int32_t*);
+  struct Item {
+    Launch fn;
+    Prob* probs;
+    int nprob;
+    double eps;
+    int tebd;
+    int32_t* retry;
+    void operator()(hipStream_t t) const { fn(t, probs, nprob, eps, tebd, retry); }
+  };
+  const Launch fns[4] = {
+      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
+        TEBD_LAUNCH("k_svd_pairs<256, 0>", (k_svd_pairs<256, 0>), dim3(np), dim3(256),
+                    2 * 32 * 33 * sizeof(zt), t, p, e, tb, rc);
+      },
+      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
+        TEBD_LAUNCH("k_svd_pairs<512, 1>", (k_svd_pairs<512, 1>), dim3(np), dim3(512),
+                    2 * 64 * 65 * sizeof(zt), t, p, e, tb, rc);
+      },
+      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
+        TEBD_LAUNCH("k_small_svd<1024, 2, true>", (k_small_svd<1024, 2, true>), dim3(np), dim3(1024),
+                    size_t(kLdsElems) * sizeof(zt), t, p, e, tb, rc);
+      },
+      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
+        TEBD_LAUNCH("k_small_svd<1024, 4, false>", (k_small_svd<1024, 4, false>), dim3(np), dim3(1024), 0,
+                    t, p, e, tb, rc);
+      }};
+  // the problem's l here is the rank the range finder revealed
+  const int lo = svd_class(c.lmin < 1 ? 1 : c.lmin), hi = svd_class(c.lmax);
+  Item items[4];
+  int n = 0;
+  int32_t* retry = c.pass2 ? nullptr : c.retry_count;
+  for (int k = lo; k <= hi; ++k) items[n++] = {fns[k], probs, c.nprob, c.eps, c.tebd, retry};
+  return fork_join(s, items, n, c);
+}
+
+}  // namespace tebd
+
+extern "C" int32_t tebd_size_class(int32_t factorization, int32_t rows, int32_t l) {
+  using namespace tebd;
+  if (l < 1 || l > kMaxL) return -1;
+  if (factorization == 0) return rows < 1 || rows > kMaxRows ? -1 : qr_class(rows, l);
+  if (factorization == 1) return svd_class(l);
+  return -1;
+}

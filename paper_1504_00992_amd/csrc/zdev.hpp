@@ -45,6 +45,19 @@ __device__ __forceinline__ zt zload_if(bool c, const zt* p) {
   return v;
 }
 
+// 1 / sqrt(d) and 1 / d for a normal positive d: the hardware estimate (about
+// 23 bits) and one third-order correction, shorter chains than the library's.
+__device__ __forceinline__ double rsqrt_pos(double d) {
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-d * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+__device__ __forceinline__ double rcp_pos(double d) {
+  const double y = __builtin_amdgcn_rcp(d);
+  const double e = fma(-d, y, 1.0);
+  return fma(y, fma(e, e, e), y);
+}
+
 // Wavefront sum of a double, result in every lane.  DPP moves on the two
 // 32-bit halves: quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror and
 // row_mirror give every lane its 16-lane row sum; row_bcast15 into rows 1, 3
@@ -119,6 +132,13 @@ __device__ __forceinline__ int32_t wave_scan_i32(int32_t v, int32_t identity, Op
   v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x142, 0xa, 0xf, false));
   v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x143, 0xc, 0xf, false));
   return v;
+}
+
+// Index of the wavefront in its workgroup, as a scalar: the compiler cannot
+// see that threadIdx.x / 64 is uniform, and treats branches, loop counters
+// and lane indices formed from it as divergent.
+__device__ __forceinline__ int wave_id() {
+  return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
 }
 
 // Uniform read of lane `src` (src uniform across the wavefront).

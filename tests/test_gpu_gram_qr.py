@@ -1,0 +1,70 @@
+"""Gram-based QR at the edges of its size classes, against the oracle.
+
+Truncated SVDs and bond updates whose sketches sit at the edges of the 16 x 16
+tiles (l = 15, 16, 17, ...), of the wavefront's problems (l <= 16, 64 rows), of
+the LDS the factor takes (l = 80) and of the tile queue (rows l^2 = 200000,
+l = 8).  Tolerances: those of the parity tests of the truncation and of the
+bond update (singular values and reconstructions 1e-10 s_1, orthonormality
+1e-12, chi' and status exact).  They leave room for this QR: one Cholesky pass
+whose scaled pivots stay above 1/4 is orthonormal to about
+4 u sqrt(rows) l <= 2e-13 here (u = 1.1e-16, random-walk sums), and a second
+pass follows where they do not.
+"""
+import numpy as np
+import pytest
+
+import test_gpu_rrsvd as rr
+import test_gpu_tebd as tb
+import workloads as wl
+from paper_1504_00992_amd import _lib
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,chi_max,p", [
+    (64, 64, 1, 1), (17, 16, 5, 10), (64, 63, 6, 10), (65, 64, 6, 10), (64, 64, 7, 10),
+    (300, 40, 22, 10), (129, 128, 23, 10), (200, 190, 38, 10), (83, 80, 39, 10),
+    (84, 80, 39, 10), (75, 75, 63, 10), (76, 90, 64, 10), (3125, 30, 6, 2), (3126, 30, 6, 2), (8192, 24, 5, 2),
+    (90, 300, 71, 10), (300, 257, 100, 10), (300, 280, 246, 10)])
+def test_truncation_at_the_edges(m, n, chi_max, p):
+    gen = wl.rng(m * 1000 + n + chi_max)
+    s = np.exp(-np.arange(min(m, n)) / (chi_max / 6.0))
+    a = wl.known_spectrum(m, n, s, gen)
+    U, S, VH, chi, w, st = rr._gpu([a], chi_max, p, 2, 1e-10)
+    # a graded first sketch may be refused by the Gram (only the report of that differs)
+    rr._compare([a], (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, p, 2, 1e-10)
+
+
+@pytest.mark.parametrize("q", [0, 1])
+def test_flat_spectrum_and_a_mixed_batch(q):
+    # well conditioned first sketches (kept whole by the Gram), sizes of every
+    # route in one batch, with and without power iterations
+    gen = wl.rng(77 + q)
+    mats = [wl.known_spectrum(m, n, np.linspace(1, 0.5, min(m, n)), gen)
+            for m, n in [(40, 30), (64, 64), (65, 17), (150, 140), (700, 90), (20, 3)]]
+    mats.append(np.zeros((50, 40), dtype=np.complex128))
+    rr._compare(mats, rr._gpu(mats, 30, 10, q, 1e-10), 30, 10, q, 1e-10)
+
+
+@pytest.mark.parametrize("dims,chis,bond,chi_max,p", [
+    ([2, 2, 2, 2], [1, 32, 40, 32, 1], 1, 6, 10),      # 64 rows, l = 16
+    ([2, 2, 2, 2], [1, 33, 40, 32, 1], 1, 6, 10),      # 66 rows on one side
+    ([2, 2, 2, 2], [1, 70, 80, 70, 1], 1, 70, 10),     # l = 80: the factor in LDS
+    ([2, 2, 2, 2], [1, 70, 80, 75, 1], 1, 71, 10),     # l = 81: in global memory
+    ([2, 2, 2, 2], [1, 100, 90, 100, 1], 1, 100, 10),  # l = 110
+])
+def test_bond_updates_at_the_edges(dims, chis, bond, chi_max, p):
+    tb.test_bond_update_matches_oracle(dims, chis, bond, chi_max, p)
+
+
+@pytest.mark.parametrize("n,chi_max", [(192, 50), (207, 34), (300, 50), (300, 2), (60, 4)])
+def test_refused_sketches_reach_the_householder_class_of_their_size(n, chi_max):
+    # a zero matrix: every Gram is refused.  Sizes on the tile queue in QR
+    # classes 1, 2 and 3, and below it; beside them a matrix that is kept.
+    gen = wl.rng(n)
+    mats = [np.zeros((n, n), dtype=np.complex128),
+            wl.known_spectrum(n, n, np.exp(-np.arange(n) / (chi_max / 6.0)), gen)]
+    U, S, VH, chi, w, st = rr._gpu(mats, chi_max, 10, 2, 1e-10)
+    large = _lib.tebd_size_class(0, n, chi_max + 10) >= 2
+    assert bool(st[0] & _lib.DEV_QR_FALLBACK) == large
+    rr._compare(mats, (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, 10, 2, 1e-10)
