@@ -819,7 +819,8 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Prob* probs, int pass, in
   }
   if (tid == 0) {
     P.chol_ok = 1;
-    P.chol_again = pass == 0 && (mode & QRM_STRICT) && (flags & 2);
+    // (the second pass leaves it set: Q takes its factor too)
+    if (pass == 0) P.chol_again = (mode & QRM_STRICT) && (flags & 2);
   }
 }
 

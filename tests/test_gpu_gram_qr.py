@@ -35,6 +35,17 @@ def test_truncation_at_the_edges(m, n, chi_max, p):
     rr._compare([a], (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, p, 2, 1e-10)
 
 
+@pytest.mark.parametrize("m,n,chi_max", [(60, 50, 40), (70, 68, 60), (75, 68, 60), (400, 300, 70)])
+@pytest.mark.parametrize("decay", [0.1, 0.2, 0.25])
+def test_second_pass_of_an_ill_conditioned_sketch(m, n, chi_max, decay):
+    # no power iteration: the QR of A Omega (kappa 1e3 to 1e8) decides the span,
+    # and one Cholesky pass of it is not orthonormal to rounding
+    gen = wl.rng(m + int(100 * decay))
+    a = wl.known_spectrum(m, n, np.exp(-decay * np.arange(min(m, n))), gen)
+    U, S, VH, chi, w, st = rr._gpu([a], chi_max, 3, 0, 0.0)
+    rr._compare([a], (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, 3, 0, 0.0)
+
+
 @pytest.mark.parametrize("q", [0, 1])
 def test_flat_spectrum_and_a_mixed_batch(q):
     # well conditioned first sketches (kept whole by the Gram), sizes of every
