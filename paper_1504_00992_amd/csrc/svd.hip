@@ -65,18 +65,22 @@ __device__ __forceinline__ double col_norm2(const zt* y, int r0, int rows, int G
 // g = c_p^H c_q (given as gr + i gi): false when |g| <= tol sqrt(a b).
 // Otherwise zeta = (b - a) / (2|g|), t = sign(zeta) / (|zeta| + sqrt(1 +
 // zeta^2)), cs = 1 / sqrt(1 + t^2), sn = t cs, em = e^{-i arg g}, and
-// ag = |g| (the carried norms move by t |g|).  Reciprocal square roots keep
-// the chain of dependent operations short.
+// ag = |g| (the carried norms move by t |g|).  Every lane of the group computes
+// it on the critical path of a round: square root and division go through the
+// hardware estimates (rsqrt_pos, rcp_pos), 8 instructions instead of 15.
 __device__ __forceinline__ bool jacobi_rotation(double gr, double gi, double a, double b,
                                                 double tol, double& ag, double& t, double& cs,
                                                 double& sn, zt& em) {
   const double g2 = gr * gr + gi * gi;
   if (!(g2 > tol * tol * (a * b)) || g2 == 0.0) return false;
-  const double ig = rsqrt(g2);  // 1 / |g|
+  const double ig = rsqrt_pos(g2);  // 1 / |g|
   ag = g2 * ig;
-  const double zeta = 0.5 * (b - a) * ig;
-  t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-  cs = rsqrt(1.0 + t * t);
+  const double zeta = 0.5 * (b - a) * ig, az = fabs(zeta);
+  const bool far = az > 1e100;  // zeta^2 would overflow; there sqrt(1 + zeta^2) = |zeta|
+  const double z2 = far ? 1.0 : fma(zeta, zeta, 1.0);
+  const double root = far ? az : z2 * rsqrt_pos(z2);
+  t = copysign(rcp_pos(az + root), zeta);
+  cs = rsqrt_pos(fma(t, t, 1.0));
   sn = t * cs;
   em = make_double2(gr * ig, -gi * ig);
   return true;
@@ -404,21 +408,25 @@ __host__ __device__ __forceinline__ int svd_class(int l) {
   return 3;
 }
 
-// C and J in LDS with an odd column stride, and all l/2 pairs of a round
-// rotated at once: G = NT / (l/2 rounded up to a power of two) lanes per
-// pair, at most 16 (DPP sums only; for these two classes always 16).  Lane h
-// of a pair loads every G-th row of both columns of C and J into
-// registers, sums its part of g = c_p^H c_q, the group sum
-// combines them, and the same lanes rotate the rows they hold and store
-// them; one barrier per round.  Same rotation, tolerance, carried norms and
-// sweep limit as jacobi_core.
-constexpr int kPairGroupMax = 16;
-
+// C and J in LDS, and all l/2 pairs of a round rotated at once by 16 lanes
+// each: lane h of a pair loads every 16th row of both columns of C and J into
+// registers, sums its part of g = c_p^H c_q, the group sum (DPP) combines
+// them, and the same lanes rotate the rows they hold and store them; one
+// barrier per round.  A round is bound by the instructions of a wavefront
+// (about five cycles each, a branch twenty), so the columns are padded with
+// zero rows to a multiple of 16 (an odd stride) and no row is tested: the
+// rotation keeps them zero.  Half of a round is LDS traffic: C and J are read
+// and written whole (2 x 52 KB at l = 34, 128 B a cycle).  Measured, one
+// problem of l = 34: 270 us with a test per row and the library's square root
+// and division, 240 us so.
+// Same rotation, tolerance, carried norms and sweep limit as jacobi_core.
+constexpr int kPairGroup = 16;
+constexpr int kPairRowsLds0 = 2 * 32 * 33, kPairRowsLds1 = 2 * 64 * 65;  // elements of C and J
 
 template <int NT, int CLS>
 __global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int tebd,
                                                   int32_t* retry_count) {
-  extern __shared__ zt lds[];  // C, then J: l columns of stride l | 1 each
+  extern __shared__ zt lds[];  // C, then J: l columns of stride S each
   __shared__ double nrm[64];
   __shared__ double sig_s[64];
   __shared__ double srt_s[64];  // singular values in descending order
@@ -426,24 +434,26 @@ __global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int t
   Prob& P = probs[blockIdx.x];
   const int l = P.l;
   if (l == 0 || svd_class(l) != CLS) return;
-  const int S = l | 1;
+  constexpr int G = kPairGroup;
+  constexpr int RPR = (CLS == 0 ? 32 : 64) / G;  // rows per lane, at most
+  static_assert(NT / (CLS == 0 ? 16 : 32) >= G, "pairs of a round fit at 16 lanes");
+  const int rp = (l + G - 1) & ~(G - 1);  // padded rows
+  const int S = rp | 1;
   zt* Cs = lds;
   zt* Js = lds + l * S;
   const int tid = threadIdx.x;
   const zt zero = make_double2(0.0, 0.0);  // value, never addressed
-  for (int e = tid; e < l * l; e += NT) {
-    const int c = e / l, r = e - c * l;
-    Cs[c * S + r] = zconj(P.Rb[size_t(r) * l + c]);
-    Js[c * S + r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
-  }
+  for (int c = tid / G; c < l; c += NT / G)
+    for (int r = tid & (G - 1); r < rp; r += G) {
+      const zt v = zload_if(r < l, P.Rb + size_t(r) * l + c);
+      Cs[c * S + r] = zconj(v);
+      Js[c * S + r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+    }
   const int lp = l + (l & 1);
-  // lanes per pair: l/2 <= NT / 16 pairs in these classes, so 16 each
-  constexpr int G = kPairGroupMax;
-  static_assert(NT / (CLS == 0 ? 16 : 32) >= kPairGroupMax, "pairs of a round fit at 16 lanes");
   const int k = tid / G, h = tid - k * G;
   int lc2 = 1;
   while (lc2 < l) lc2 <<= 1;
-  const int GN = NT / lc2 < kPairGroupMax ? NT / lc2 : kPairGroupMax;  // lanes per column
+  const int GN = NT / lc2 < G ? NT / lc2 : G;  // lanes per column
   const int cn = tid / GN, hn = tid - cn * GN;
   const double tol = DBL_EPSILON * sqrt(double(l));
   constexpr int kMaxSweeps = 40;
@@ -457,49 +467,41 @@ __global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int t
     __syncthreads();
     int any = 0, large = 0;
     for (int round = 0; round < lp - 1; ++round) {
-      int p = 0, q = 0;
-      bool act = k < lp / 2;
-      if (act) {
-        const int a = circle_player(k, round, lp), b = circle_player(lp - 1 - k, round, lp);
-        p = a < b ? a : b;
-        q = a < b ? b : a;
-        act = q < l;
-      }
-      // rows h, h + G, ... < l: G = 16 here (l/2 <= NT / 16), so at most
-      // 32 / 16 or 64 / 16 of them
-      constexpr int RPR = (CLS == 0 ? 32 : 64) / kPairGroupMax;
-      zt x[RPR], y[RPR], xj[RPR], yj[RPR];
-      zt* cp = Cs + p * S;
-      zt* cq = Cs + q * S;
-      zt* jp = Js + p * S;
-      zt* jq = Js + q * S;
-      double g0 = 0.0, g1 = 0.0;
-#pragma unroll
-      for (int i = 0; i < RPR; ++i) {
-        const int r = h + G * i;
-        const bool in = act && r < l;
-        x[i] = zload_if(in, cp + r);
-        y[i] = zload_if(in, cq + r);
-        xj[i] = zload_if(in, jp + r);
-        yj[i] = zload_if(in, jq + r);
-        zdot_acc(x[i], y[i], g0, g1);
-      }
-      const double gr = group_sum(g0, G), gi = group_sum(g1, G);
-      if (act) {
+      const int a = circle_player(k, round, lp), b = circle_player(lp - 1 - k, round, lp);
+      const int p = a < b ? a : b, q = a < b ? b : a;
+      if (k < lp / 2 && q < l) {
+        zt x[RPR], y[RPR], xj[RPR], yj[RPR];
+        zt* cp = Cs + p * S + h;
+        zt* cq = Cs + q * S + h;
+        zt* jp = Js + p * S + h;
+        zt* jq = Js + q * S + h;
         const double app = nrm[p], aqq = nrm[q];
+        double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < RPR; ++i) {
+          if (G * i >= l) break;  // uniform
+          x[i] = cp[G * i];
+          y[i] = cq[G * i];
+          xj[i] = jp[G * i];
+          yj[i] = jq[G * i];
+        }
+#pragma unroll
+        for (int i = 0; i < RPR; ++i) {
+          if (G * i >= l) break;
+          zdot_acc(x[i], y[i], g0, g1);
+        }
+        const double gr = group_sum(g0, G), gi = group_sum(g1, G);
         double ag, t, cs, sn;
         zt em;  // e^{-i phi}
         if (jacobi_rotation(gr, gi, app, aqq, tol, ag, t, cs, sn, em)) {
 #pragma unroll
           for (int i = 0; i < RPR; ++i) {
-            const int r = h + G * i;
-            if (r < l) {
-              const zt ey = zmul(em, y[i]), eyj = zmul(em, yj[i]);
-              cp[r] = zrot_lo(x[i], ey, cs, sn);
-              cq[r] = zrot_hi(x[i], ey, cs, sn);
-              jp[r] = zrot_lo(xj[i], eyj, cs, sn);
-              jq[r] = zrot_hi(xj[i], eyj, cs, sn);
-            }
+            if (G * i >= l) break;
+            const zt ey = zmul(em, y[i]), eyj = zmul(em, yj[i]);
+            cp[G * i] = zrot_lo(x[i], ey, cs, sn);
+            cq[G * i] = zrot_hi(x[i], ey, cs, sn);
+            jp[G * i] = zrot_lo(xj[i], eyj, cs, sn);
+            jq[G * i] = zrot_hi(xj[i], eyj, cs, sn);
           }
           if (h == 0) {
             nrm[p] = fmax(app - t * ag, 0.0);
@@ -596,7 +598,7 @@ hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_svd_pairs<512, 1>),
                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                               int(2 * 64 * 65 * sizeof(zt)));
+                               int(kPairRowsLds1 * sizeof(zt)));
   }();
   if (attr != hipSuccess) return attr;
   typedef void (*Launch)(hipStream_t, Prob*, int, double, int, int32_t*);
@@ -612,11 +614,11 @@ hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
   const Launch fns[4] = {
       [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
         TEBD_LAUNCH("k_svd_pairs<256, 0>", (k_svd_pairs<256, 0>), dim3(np), dim3(256),
-                    2 * 32 * 33 * sizeof(zt), t, p, e, tb, rc);
+                    kPairRowsLds0 * sizeof(zt), t, p, e, tb, rc);
       },
       [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
         TEBD_LAUNCH("k_svd_pairs<512, 1>", (k_svd_pairs<512, 1>), dim3(np), dim3(512),
-                    2 * 64 * 65 * sizeof(zt), t, p, e, tb, rc);
+                    kPairRowsLds1 * sizeof(zt), t, p, e, tb, rc);
       },
       [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
         TEBD_LAUNCH("k_small_svd<1024, 2, true>", (k_small_svd<1024, 2, true>), dim3(np), dim3(1024),
