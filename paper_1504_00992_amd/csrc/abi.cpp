@@ -472,6 +472,17 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
     // launch ends with the truncation of its problems
     Common cs = c;
     cs.lmin = 1;
+    if (wide_svd(cs)) {
+      const int32_t* found = nullptr;
+      TIMED(PK_SMALL_SVD, launch_wide_list(probs, cs, &found, s));
+      cs.wide_n = cs.nprob;
+      cs.wide_l = cs.lmax;
+      if (cs.tebd) {
+        int32_t v = 0;
+        TRY(read_counter(found, &v, s));
+        wide_found(cs, v);
+      }
+    }
     TIMED(PK_SMALL_SVD, launch_small_svd(probs, cs, s));
   }
   // the host's read of the rejected first stages lands while U and V^H form

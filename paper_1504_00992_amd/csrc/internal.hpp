@@ -45,6 +45,7 @@ struct Prob {
   // Gram-based QR: kGram* bits (where its steps run), 1 while the current QR
   // needs no Householder kernel, and 1 when its second pass is wanted
   int32_t chol, chol_ok, chol_again;
+  int32_t jac;                       // wide small SVD: JacBits of its sweeps
   // Gate groups (TEBD): consecutive problems of one bond that share its gate
   // form one product G [Theta_1 | Theta_2 | ...] over all their columns.
   // gtot: the group's columns (every member), gn: members (the first member
@@ -139,6 +140,9 @@ struct Common {
   int32_t acc_lcap = 0;          // Accuracy Check: largest basis width (QR classes)
   int32_t acc_r = 0;             // Accuracy Check: probe width
   int32_t retry_read = 0;        // enqueue the host read of *retry_count after the truncation
+  // the small SVD of classes 2 and 3: problems for many workgroups and their
+  // largest l (-1: a workgroup each)
+  int32_t wide_n = -1, wide_l = 0;
   int32_t chol = 0;              // 1: the first QR tries the Gram, the large sketches use the tile queue
 };
 
@@ -338,6 +342,12 @@ hipError_t launch_acc_probe(Prob* probs, const Common& c, hipStream_t s);
 hipError_t launch_acc_resid(Prob* probs, const Common& c, int round, hipStream_t s);
 // Small SVD of every problem, then its truncation (chi', lambda', w, status).
 hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s);
+// Whether the batch may take the many-workgroup small SVD; the list of the
+// problems that do (*found: device address of their number and largest l,
+// which wide_found unpacks into c).
+bool wide_svd(const Common& c);
+hipError_t launch_wide_list(Prob* probs, const Common& c, const int32_t** found, hipStream_t s);
+void wide_found(Common& c, int32_t found);
 hipError_t launch_form_uv(Prob* probs, const Common& c, hipStream_t s);
 hipError_t launch_tape(Prob* probs, const Common& c, hipStream_t s);
 

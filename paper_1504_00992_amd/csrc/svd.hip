@@ -7,11 +7,13 @@
 // discarded weight of Sec. II.C, Eq. (defdiscweigt), evaluated with the
 // Frobenius identity of Sec. IV.
 #include <cfloat>
+#include <functional>
 #include <type_traits>
 
 #include "householder.hpp"
 #include "kinds.hpp"
 #include "sidestreams.hpp"
+#include "zgemm.hpp"
 
 namespace tebd {
 
@@ -560,11 +562,305 @@ __global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int t
   truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return srt_s[c]; }, nrm);
 }
 
-// Classes 2 and 3: one pair per wavefront at a time (jacobi_core), C and J
-// in LDS (LDS_CJ) or in the problem's global scratch.
+// --------------------------------------------------------------------------
+// Classes 2 and 3 over many workgroups.  One CU's share of the work is the
+// bound of a single-workgroup iteration (l = 200: 1.4 GFLOP of rotations and
+// 1.3 MB per round through one CU, 34 ms; l = 74: 2.9 ms), so the columns are
+// split into blocks of kJacBlock and a launch rotates, in one workgroup per
+// pair of blocks, every pair of columns across the two; the block pairs
+// follow the circle method, and the first launch of a sweep also rotates
+// the pairs inside the blocks.  A wavefront keeps one column of the first
+// block (its rows of C and J) in registers and meets the second block's
+// columns, in LDS, one after another.  Same rotation, tolerance, carried
+// norms and (kJacSweeps at most, then jacobi_core goes on) order of
+// magnitude of sweeps as one workgroup's circle: 5 to 7.
+// Measured, sum of the launches, one workgroup / these: l = 200, two problems
+// 33.8 / 3.1 ms; l = 74, 20 problems 2.86 / 0.90 ms.  A launch takes 4.5 us with
+// nothing to do, 13 us (l = 74) to 17 us (l = 200) with.
+constexpr int kJacBlock = 8, kJacThreads = 64 * kJacBlock, kJacSweeps = 7, kJacCheckFrom = 2;
+
+// Per sweep s, in Prob::jac: bit s a rotation happened, bit 8 + s one of them
+// by more than a small turn, bit 16 + s the test of all pairs after it failed.
+// A sweep ends the iteration when nothing rotated in it, or only by small
+// turns and every pair passed the test (made from sweep kJacCheckFrom on).
+__device__ __forceinline__ bool jac_done(int bits, int sweep) {
+  const int rot = bits & 0xff;
+  const int more = ((bits >> 8 | bits >> 16) & 0xff) | ((1 << kJacCheckFrom) - 1);
+  return (~(rot & more) & ((1 << sweep) - 1)) != 0;
+}
+static_assert(kJacSweeps <= 8, "bits per sweep in Prob::jac");
+
+// The problems of these classes (indices, in order, then their number in the
+// low 22 bits of list[nprob] and the largest l above), one workgroup.
+__global__ __launch_bounds__(1024) void k_jac_list(Prob* probs, int nprob, int32_t* list) {
+  __shared__ int wsum[16], wmax[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+  int base = 0, lmax = 0;
+  for (int p0 = 0; p0 < nprob; p0 += 1024) {
+    const int p = p0 + tid;
+    const int l = p < nprob ? probs[p].l : 0;
+    const bool in = l > 0 && svd_class(l) >= 2;
+    const unsigned long long m = __ballot(in);
+    if (lane == 0) wsum[wave] = __popcll(m);
+    __syncthreads();
+    int at = base + __popcll(m & ((1ull << lane) - 1));
+    for (int w = 0; w < 16; ++w) {
+      at += w < wave ? wsum[w] : 0;
+      base += wsum[w];
+    }
+    if (in) {
+      list[at] = p;
+      probs[p].jac = 0;
+      lmax = l > lmax ? l : lmax;
+    }
+    __syncthreads();
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    const int o = __shfl_xor(lmax, off, 64);
+    lmax = o > lmax ? o : lmax;
+  }
+  if (lane == 0) wmax[wave] = lmax;
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 16; ++w) lmax = wmax[w] > lmax ? wmax[w] : lmax;
+    list[nprob] = base | lmax << 22;
+  }
+}
+constexpr int kJacCountMask = (1 << 22) - 1;
+
+// One column's rows of C and J: lane h holds rows h + 64 i.
+template <int REGS>
+struct JacColumn {
+  zt c[REGS], j[REGS];
+};
+
+template <int REGS>
+__device__ __forceinline__ double jac_norm2(const JacColumn<REGS>& x) {
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < REGS; ++i) s += zabs2(x.c[i]);
+  return wave_sum(s);
+}
+
+// One wavefront: rotates columns x and y (squared norms na, nb, carried);
+// bit 0 of the result: rotated, bit 1: by more than a small turn.
+template <int REGS>
+__device__ __forceinline__ int jac_rotate(JacColumn<REGS>& x, JacColumn<REGS>& y, double tol,
+                                          double& na, double& nb) {
+  double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+  for (int i = 0; i < REGS; ++i) zdot_acc(x.c[i], y.c[i], g0, g1);
+  g0 = wave_sum(g0);
+  g1 = wave_sum(g1);
+  double ag, t, cs, sn;
+  zt em;
+  if (!jacobi_rotation(g0, g1, na, nb, tol, ag, t, cs, sn, em)) return 0;
+#pragma unroll
+  for (int i = 0; i < REGS; ++i) {
+    const zt u = x.c[i], v = zmul(em, y.c[i]), uj = x.j[i], vj = zmul(em, y.j[i]);
+    x.c[i] = zrot_lo(u, v, cs, sn);
+    y.c[i] = zrot_hi(u, v, cs, sn);
+    x.j[i] = zrot_lo(uj, vj, cs, sn);
+    y.j[i] = zrot_hi(uj, vj, cs, sn);
+  }
+  const int r = ag * ag > kSmallTurn * (na * nb) ? 3 : 1;
+  na = fmax(na - t * ag, 0.0);
+  nb += t * ag;
+  return r;
+}
+
+template <int REGS>
+__global__ __launch_bounds__(kJacThreads) void k_jac_round(Prob* probs, const int32_t* list,
+                                                           int nprob, int pairs, int sweep,
+                                                           int round) {
+  extern __shared__ zt lds[];  // columns of C, then of J, per slot: second block, first block
+  __shared__ double nrm[2 * kJacBlock];
+  __shared__ int changed[kJacBlock];
+  constexpr int S = 64 * REGS;
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int items = (list[nprob] & kJacCountMask) * pairs;
+  auto put = [&](int slot, const JacColumn<REGS>& x) {
+    zt* at = lds + slot * 2 * S + lane;
+#pragma unroll
+    for (int i = 0; i < REGS; ++i) {
+      at[64 * i] = x.c[i];
+      at[S + 64 * i] = x.j[i];
+    }
+  };
+  auto get = [&](int slot, JacColumn<REGS>& x) {
+    const zt* at = lds + slot * 2 * S + lane;
+#pragma unroll
+    for (int i = 0; i < REGS; ++i) {
+      x.c[i] = at[64 * i];
+      x.j[i] = at[S + 64 * i];
+    }
+  };
+  for (int it = blockIdx.x; it < items; it += gridDim.x) {
+    const int i = it / pairs, k = it - i * pairs;
+    Prob& P = probs[list[i]];
+    const int l = P.l, nb = ((l + kJacBlock - 1) / kJacBlock + 1) & ~1;
+    if (k >= nb / 2 || round >= nb - 1 || jac_done(P.jac, sweep)) continue;
+    const int a = circle_player(k, round, nb), b = circle_player(nb - 1 - k, round, nb);
+    // an odd number of blocks: the last player is none (its partner's inner
+    // pairs still rotate)
+    if (round > 0 && (a > b ? a : b) * kJacBlock >= l) continue;
+    const int p = (a < b ? a : b) * kJacBlock + w, q = (a < b ? b : a) * kJacBlock + w;
+    const double tol = DBL_EPSILON * sqrt(double(l));
+    const bool start = sweep == 0 && round == 0;
+    auto load = [&](int col, JacColumn<REGS>& x) {
+      const int cc = col < l ? col : l - 1;
+#pragma unroll
+      for (int u = 0; u < REGS; ++u) {
+        const int r = lane + 64 * u, rc = r < l ? r : l - 1;
+        const bool in = r < l && col < l;
+        const zt v = start ? zconj(P.Rb[size_t(rc) * l + cc]) : P.C[size_t(cc) * l + rc];
+        const zt vj = start ? make_double2(r == col ? 1.0 : 0.0, 0.0) : P.J[size_t(cc) * l + rc];
+        x.c[u] = make_double2(in ? v.x : 0.0, in ? v.y : 0.0);
+        x.j[u] = make_double2(in ? vj.x : 0.0, in ? vj.y : 0.0);
+      }
+    };
+    auto store = [&](int col, const JacColumn<REGS>& x) {
+      if (col >= l) return;
+#pragma unroll
+      for (int u = 0; u < REGS; ++u) {
+        const int r = lane + 64 * u;
+        if (r < l) {
+          P.C[size_t(col) * l + r] = x.c[u];
+          P.J[size_t(col) * l + r] = x.j[u];
+        }
+      }
+    };
+    JacColumn<REGS> x, y;
+    load(p, x);
+    load(q, y);
+    int bits = 0;
+    double na = jac_norm2(x);
+    {
+      const double n = jac_norm2(y);
+      if (lane == 0) {
+        nrm[w] = n;
+        nrm[kJacBlock + w] = na;
+        changed[w] = start;
+      }
+    }
+    put(w, y);
+    bool moved = start;  // the first block's column
+    if (round == 0) {    // the pairs inside either block
+      put(kJacBlock + w, x);
+      for (int r = 0; r < kJacBlock - 1; ++r) {
+        const int h = w & (kJacBlock / 2 - 1), side = w < kJacBlock / 2 ? 0 : kJacBlock;
+        const int s0 = circle_player(h, r, kJacBlock),
+                  s1 = circle_player(kJacBlock - 1 - h, r, kJacBlock);
+        const int lo = side + (s0 < s1 ? s0 : s1), hi = side + (s0 < s1 ? s1 : s0);
+        __syncthreads();
+        get(lo, x);
+        get(hi, y);
+        double nl = nrm[lo], nh = nrm[hi];
+        const int c = jac_rotate(x, y, tol, nl, nh);
+        if (c) {
+          put(lo, x);
+          put(hi, y);
+          if (lane == 0) {
+            nrm[lo] = nl;
+            nrm[hi] = nh;
+          }
+        }
+        bits |= c;
+      }
+      const bool inner = __syncthreads_or(bits) != 0;
+      moved |= inner;
+      if (lane == 0 && inner) changed[w] = 1;
+      get(kJacBlock + w, x);
+      na = nrm[kJacBlock + w];
+    }
+    for (int s = 0; s < kJacBlock; ++s) {
+      const int slot = (w + s) & (kJacBlock - 1);
+      __syncthreads();
+      get(slot, y);
+      double n = nrm[slot];
+      const int c = jac_rotate(x, y, tol, na, n);
+      if (c) {
+        put(slot, y);
+        if (lane == 0) {
+          nrm[slot] = n;
+          changed[slot] = 1;
+        }
+        moved = true;
+      }
+      bits |= c;
+    }
+    if (moved) store(p, x);
+    const int all = (__syncthreads_or(bits & 1) ? 1 : 0) | (__syncthreads_or(bits & 2) ? 1 << 8 : 0);
+    if (changed[w]) {
+      get(w, y);
+      store(q, y);
+    }
+    if (threadIdx.x == 0 && all) atomicOr(&P.jac, all << sweep);
+    __syncthreads();  // nrm, changed and the slots are free
+  }
+}
+
+// The test of all pairs after a sweep of small turns only (jacobi_rotation's,
+// norms recomputed): a wavefront per 16 x 16 tile of the Gram matrix.
+__global__ __launch_bounds__(256) void k_jac_check(Prob* probs, const int32_t* list, int nprob,
+                                                   int blocks, int sweep) {
+  const int lane = threadIdx.x & 63, ti = lane & 15, tk = lane >> 4;
+  const int tiles = blocks * blocks;
+  const int items = (list[nprob] & kJacCountMask) * tiles;
+  for (int it = blockIdx.x * 4 + wave_id(); it < items; it += gridDim.x * 4) {
+    const int i = it / tiles, t = it - i * tiles, bi = t / blocks, bj = t - bi * blocks;
+    Prob& P = probs[list[i]];
+    const int l = P.l, bits = P.jac >> sweep;
+    if (bi > bj || bj * 16 >= l || !(bits & 1) || (bits & (1 << 8)) || jac_done(P.jac, sweep))
+      continue;
+    const int p = bi * 16 + ti, q = bj * 16 + ti;
+    const zt* cp = P.C + size_t(p < l ? p : l - 1) * l;
+    const zt* cq = P.C + size_t(q < l ? q : l - 1) * l;
+    v4d re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+    double np = 0.0, nq = 0.0;
+    for (int k0 = 0; k0 < l; k0 += 16) {
+      zt u[4], v[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = k0 + 4 * s + tk, kc = k < l ? k : l - 1;
+        u[s] = cp[kc];
+        v[s] = cq[kc];
+        if (k >= l) u[s] = v[s] = make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {  // g = conj(u) v
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].x, v[s].x, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].x, v[s].y, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].y, v[s].y, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(-u[s].y, v[s].x, im, 0, 0, 0);
+        np += zabs2(u[s]);
+        nq += zabs2(v[s]);
+      }
+    }
+    np += __shfl_xor(np, 16, 64);
+    np += __shfl_xor(np, 32, 64);
+    nq += __shfl_xor(nq, 16, 64);
+    nq += __shfl_xor(nq, 32, 64);
+    const double tol = DBL_EPSILON * sqrt(double(l));
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {  // entry (tk + 4 r, ti) of the tile
+      const int row = tk + 4 * r;
+      const double nr = __shfl(np, row, 64), g2 = re[r] * re[r] + im[r] * im[r];
+      const bool pair = bi * 16 + row < q && q < l;
+      bad |= pair && g2 > tol * tol * (nr * nq) && g2 != 0.0;
+    }
+    if (__any(bad) && lane == 0) atomicOr(&P.jac, 1 << (16 + sweep));
+  }
+}
+
+// Classes 2 and 3 by one workgroup: one pair per wavefront at a time
+// (jacobi_core), C and J in LDS (LDS_CJ) or in the problem's global scratch.
+// resumed: both classes, after the launches above (the iteration only where
+// they did not finish it).
 template <int NT, int REGS, bool LDS_CJ>
 __global__ __launch_bounds__(NT) void k_small_svd(Prob* probs, double eps, int tebd,
-                                                  int32_t* retry_count) {
+                                                  int32_t* retry_count, int resumed) {
   extern __shared__ zt lds[];
   __shared__ double sig_s[kMaxL];
   __shared__ int perm_s[kMaxL];
@@ -572,68 +868,120 @@ __global__ __launch_bounds__(NT) void k_small_svd(Prob* probs, double eps, int t
   __shared__ double nrm[kMaxL];
   Prob& P = probs[blockIdx.x];
   const int l = P.l;
-  if (l == 0 || svd_class(l) != (LDS_CJ ? 2 : 3)) return;
+  if (l == 0 || (resumed ? svd_class(l) < 2 : svd_class(l) != (LDS_CJ ? 2 : 3))) return;
   zt* C = LDS_CJ ? lds : P.C;
   zt* J = LDS_CJ ? lds + l * l : P.J;
-  for (int e = threadIdx.x; e < l * l; e += NT) {
-    const int c = e / l, r = e - c * l;
-    C[e] = zconj(P.Rb[size_t(r) * l + c]);
-    J[e] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+  int converged = 1;
+  if (!resumed || !jac_done(P.jac, kJacSweeps)) {
+    if (!resumed)
+      for (int e = threadIdx.x; e < l * l; e += NT) {
+        const int c = e / l, r = e - c * l;
+        C[e] = zconj(P.Rb[size_t(r) * l + c]);
+        J[e] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+      }
+    __syncthreads();
+    // the all-pairs test only where C is in LDS (from global memory it costs
+    // about the sweep it would save)
+    jacobi_core<NT, REGS, LDS_CJ>(C, J, l, converged, &rotated, &large_turn, nrm);
   }
-  __syncthreads();
-  int converged;
-  // the all-pairs test only where C is in LDS (from global memory it costs
-  // about the sweep it would save)
-  jacobi_core<NT, REGS, LDS_CJ>(C, J, l, converged, &rotated, &large_turn, nrm);
   if (!converged && threadIdx.x == 0) P.flags |= TEBD_DEV_JACOBI_NOCONV;
   jacobi_finish<NT>(P, C, J, l, sig_s, perm_s);
   truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return sig_s[perm_s[c]]; }, nrm);
 }
 
+// The launches of the wide small SVD (classes 2 and 3) for at most `count`
+// problems of at most lmax columns.
+void launch_jacobi_rounds(Prob* probs, const int32_t* list, int nprob, int count, int lmax,
+                          hipStream_t s) {
+  const int nb = ((lmax + kJacBlock - 1) / kJacBlock + 1) & ~1, pairs = nb / 2;
+  const int blocks = (lmax + 15) / 16;
+  const int64_t items = int64_t(count) * pairs, tiles = int64_t(count) * blocks * blocks;
+  const dim3 g(unsigned(items < 1024 ? items : 1024)), gt(unsigned(tiles < 4096 ? (tiles + 3) / 4 : 1024));
+  const size_t column = lmax <= 128 ? 2 * 128 * sizeof(zt) : 2 * 256 * sizeof(zt);
+  for (int sweep = 0; sweep < kJacSweeps; ++sweep) {
+    for (int r = 0; r < nb - 1; ++r) {
+      const size_t lds = (r == 0 ? 2 : 1) * kJacBlock * column;
+      if (lmax <= 128)
+        TEBD_LAUNCH("k_jac_round<2>", k_jac_round<2>, g, dim3(kJacThreads), lds, s, probs, list, nprob, pairs, sweep, r);
+      else
+        TEBD_LAUNCH("k_jac_round<4>", k_jac_round<4>, g, dim3(kJacThreads), lds, s, probs, list, nprob, pairs, sweep, r);
+    }
+    if (sweep >= kJacCheckFrom)
+      TEBD_LAUNCH("k_jac_check", k_jac_check, gt, dim3(256), 0, s, probs, list, nprob, blocks, sweep);
+  }
+}
+
+// The list lies where the queue of the Theta products was.
+int32_t* jac_list(const Common& c) { return c.offs + size_t(TK_THETA) * (c.nprob + 1); }
+
+// Classes 2 and 3 take launch_jacobi_rounds where the host can know that there
+// are such problems: in a truncation of matrices by the widths it asked for,
+// in a sweep that synchronises with the host by reading what the range finder
+// revealed (15 us, against 0.3 ms of empty launches).  Sweeps that only
+// enqueue know the capacity alone and keep to one launch.
+bool wide_svd(const Common& c) {
+  return svd_class(c.lmax) >= 2 && (!c.tebd || c.adaptive >= 2);
+}
+
+hipError_t launch_wide_list(Prob* probs, const Common& c, const int32_t** found, hipStream_t s) {
+  TEBD_LAUNCH("k_jac_list", k_jac_list, dim3(1), dim3(1024), 0, s, probs, c.nprob, jac_list(c));
+  *found = jac_list(c) + c.nprob;
+  return hipGetLastError();
+}
+
+void wide_found(Common& c, int32_t found) {
+  c.wide_n = found & kJacCountMask;
+  c.wide_l = found >> 22;
+}
+
 hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
   static const hipError_t attr = []() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_small_svd<1024, 2, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       int(size_t(kLdsElems) * sizeof(zt)));
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_svd_pairs<512, 1>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               int(kPairRowsLds1 * sizeof(zt)));
+    const struct {
+      const void* fn;
+      size_t elems;
+    } lds[] = {{reinterpret_cast<const void*>(&k_small_svd<1024, 2, true>), size_t(kLdsElems)},
+               {reinterpret_cast<const void*>(&k_svd_pairs<512, 1>), size_t(kPairRowsLds1)},
+               {reinterpret_cast<const void*>(&k_jac_round<2>), size_t(4 * kJacBlock * 128)},
+               {reinterpret_cast<const void*>(&k_jac_round<4>), size_t(4 * kJacBlock * 256)}};
+    for (const auto& f : lds) {
+      const hipError_t e = hipFuncSetAttribute(f.fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               int(f.elems * sizeof(zt)));
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }();
   if (attr != hipSuccess) return attr;
-  typedef void (*Launch)(hipStream_t, Prob*, int, double, int, int32_t*);
-  struct Item {
-    Launch fn;
-    Prob* probs;
-    int nprob;
-    double eps;
-    int tebd;
-    int32_t* retry;
-    void operator()(hipStream_t t) const { fn(t, probs, nprob, eps, tebd, retry); }
-  };
-  const Launch fns[4] = {
-      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
-        TEBD_LAUNCH("k_svd_pairs<256, 0>", (k_svd_pairs<256, 0>), dim3(np), dim3(256),
-                    kPairRowsLds0 * sizeof(zt), t, p, e, tb, rc);
-      },
-      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
-        TEBD_LAUNCH("k_svd_pairs<512, 1>", (k_svd_pairs<512, 1>), dim3(np), dim3(512),
-                    kPairRowsLds1 * sizeof(zt), t, p, e, tb, rc);
-      },
-      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
-        TEBD_LAUNCH("k_small_svd<1024, 2, true>", (k_small_svd<1024, 2, true>), dim3(np), dim3(1024),
-                    size_t(kLdsElems) * sizeof(zt), t, p, e, tb, rc);
-      },
-      [](hipStream_t t, Prob* p, int np, double e, int tb, int32_t* rc) {
-        TEBD_LAUNCH("k_small_svd<1024, 4, false>", (k_small_svd<1024, 4, false>), dim3(np), dim3(1024), 0,
-                    t, p, e, tb, rc);
-      }};
   // the problem's l here is the rank the range finder revealed
-  const int lo = svd_class(c.lmin < 1 ? 1 : c.lmin), hi = svd_class(c.lmax);
-  Item items[4];
-  int n = 0;
+  const int lo = svd_class(c.lmin < 1 ? 1 : c.lmin);
+  int hi = svd_class(c.lmax);
   int32_t* retry = c.pass2 ? nullptr : c.retry_count;
-  for (int k = lo; k <= hi; ++k) items[n++] = {fns[k], probs, c.nprob, c.eps, c.tebd, retry};
+  const bool wide = c.wide_n > 0;
+  if (c.wide_n == 0 && hi > 1) hi = 1;
+  auto pairs0 = [&](hipStream_t t) {
+    TEBD_LAUNCH("k_svd_pairs<256, 0>", (k_svd_pairs<256, 0>), dim3(c.nprob), dim3(256),
+                kPairRowsLds0 * sizeof(zt), t, probs, c.eps, c.tebd, retry);
+  };
+  auto pairs1 = [&](hipStream_t t) {
+    TEBD_LAUNCH("k_svd_pairs<512, 1>", (k_svd_pairs<512, 1>), dim3(c.nprob), dim3(512),
+                kPairRowsLds1 * sizeof(zt), t, probs, c.eps, c.tebd, retry);
+  };
+  auto small2 = [&](hipStream_t t) {
+    TEBD_LAUNCH("k_small_svd<1024, 2, true>", (k_small_svd<1024, 2, true>), dim3(c.nprob),
+                dim3(1024), size_t(kLdsElems) * sizeof(zt), t, probs, c.eps, c.tebd, retry, 0);
+  };
+  auto small3 = [&](hipStream_t t) {
+    if (wide) launch_jacobi_rounds(probs, jac_list(c), c.nprob, c.wide_n, c.wide_l, t);
+    TEBD_LAUNCH("k_small_svd<1024, 4, false>", (k_small_svd<1024, 4, false>), dim3(c.nprob),
+                dim3(1024), 0, t, probs, c.eps, c.tebd, retry, wide ? 1 : 0);
+  };
+  const std::function<void(hipStream_t)> fns[4] = {pairs0, pairs1, small2, small3};
+  std::function<void(hipStream_t)> items[4];
+  int n = 0;
+  for (int k = lo; k <= hi && k < 2; ++k) items[n++] = fns[k];
+  if (wide)
+    items[n++] = fns[3];
+  else
+    for (int k = lo < 2 ? 2 : lo; k <= hi; ++k) items[n++] = fns[k];
   return fork_join(s, items, n, c);
 }
 

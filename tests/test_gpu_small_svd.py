@@ -28,3 +28,32 @@ def test_widths_of_the_pair_kernels(l, decay):
     U, S, VH, chi, w, st = rr._gpu(mats, l - p, p, 0, 0.0)
     assert not np.any(st & ~_lib.DEV_QR_FALLBACK)
     rr._compare(mats, (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), l - p, p, 0, 0.0)
+
+
+@pytest.mark.parametrize("l", [65, 69, 70, 72, 73, 80, 81, 128, 129, 200, 256])
+@pytest.mark.parametrize("steep", [0.0, 4.0, 24.0])
+def test_widths_of_the_block_rounds(l, steep):
+    # one block of 8 columns more or less, an odd number of blocks, the
+    # register classes (128); beside it a narrower problem of the same batch;
+    # spectra down to e^-24, above the rank tolerance 1e-13 of the first QR
+    decay = steep / l
+    gen = wl.rng(100 * l + int(steep))
+    n = l + 5
+    mats = [wl.known_spectrum(n + 2, n, np.exp(-decay * np.arange(n)) * np.linspace(1, 0.7, n), gen),
+            wl.known_spectrum(72, 90, np.exp(-decay * np.arange(72)) * np.linspace(1, 0.6, 72), gen),
+            wl.known_spectrum(40, 30, np.exp(-decay * np.arange(30)) * np.linspace(1, 0.6, 30), gen)]
+    U, S, VH, chi, w, st = rr._gpu(mats, l - 3, 3, 0, 0.0)
+    assert not np.any(st & ~_lib.DEV_QR_FALLBACK)
+    rr._compare(mats, (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), l - 3, 3, 0, 0.0)
+
+
+def test_a_batch_of_more_pairs_than_workgroups():
+    gen = wl.rng(9)
+    mats = [wl.known_spectrum(90 + i % 5, 85, np.exp(-0.1 * np.arange(85)), gen) for i in range(260)]
+    U, S, VH, chi, w, st = rr._gpu(mats, 70, 10, 0, 0.0)
+    pick = [0, 1, 2, 130, 258, 259]
+    for i in pick:
+        ou, os_, ovh, ochi, ow, ost = rr._oracle(mats[i], i, 70, 10, 0, 0.0)
+        assert np.max(np.abs(S[i][:ochi] - os_)) <= 1e-10 * os_[0]
+        rec = (U[i][:, :ochi] * S[i][None, :ochi]) @ VH[i][:ochi]
+        assert np.max(np.abs(rec - (ou * os_[None, :]) @ ovh)) <= 1e-10 * os_[0]
