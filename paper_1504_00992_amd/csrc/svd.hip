@@ -106,6 +106,7 @@ __device__ __forceinline__ int circle_player(int pos, int round, int lp) {
 // sweep would likely rotate nothing; instead of running that sweep,
 // pairs_below_tol tests every pair of the current C at once.
 constexpr double kSmallTurn = 1e-14;
+constexpr int kMaxSweeps = 40;
 
 // True when no pair of columns of C (column c at C + c S) would be rotated:
 // every |c_p^H c_q| <= tol |c_p| |c_q| with nrm[c] = |c_c|^2 recomputed and
@@ -146,108 +147,6 @@ __device__ __forceinline__ bool pairs_below_tol(const zt* C, int S, int l, doubl
   return __syncthreads_or(bad) == 0;
 }
 
-// One pair per wavefront at a time; ALL_PAIRS: after a sweep of small turns,
-// pairs_below_tol may end the iteration without the sweep that rotates
-// nothing.
-template <int NT, int REGS, bool ALL_PAIRS>
-__device__ __forceinline__ void jacobi_core(zt* C, zt* J, int l, int& converged_out,
-                                            int* rotated, int* large, double* nrm) {
-  constexpr int NW = NT / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lp = l + (l & 1);
-  const double tol = DBL_EPSILON * sqrt(double(l));
-  constexpr int kMaxSweeps = 40;
-  bool converged = (l == 1);
-  for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
-    for (int c = wave; c < l; c += NW) {
-      double s = 0.0;
-#pragma unroll
-      for (int i = 0; i < REGS; ++i) {
-        const int r = lane + 64 * i;
-        if (r < l) s += zabs2(C[size_t(c) * l + r]);
-      }
-      s = wave_sum(s);
-      if (lane == 0) nrm[c] = s;
-    }
-    if (tid == 0) {
-      *rotated = 0;
-      *large = 0;
-    }
-    __syncthreads();
-    for (int round = 0; round < lp - 1; ++round) {
-      for (int pr = wave; pr < lp / 2; pr += NW) {
-        const int a = circle_player(pr, round, lp), b = circle_player(lp - 1 - pr, round, lp);
-        const int p = a < b ? a : b, q = a < b ? b : a;
-        if (q >= l) continue;
-        zt* cp = C + size_t(p) * l;
-        zt* cq = C + size_t(q) * l;
-        zt xp[REGS], xq[REGS];
-        double gr = 0.0, gi = 0.0;
-#pragma unroll
-        for (int i = 0; i < REGS; ++i) {
-          const int r = lane + 64 * i;
-          xp[i] = r < l ? cp[r] : make_double2(0.0, 0.0);
-          xq[i] = r < l ? cq[r] : make_double2(0.0, 0.0);
-          const zt t = zcmul(xp[i], xq[i]);
-          gr += t.x;
-          gi += t.y;
-        }
-        gr = wave_sum(gr);
-        gi = wave_sum(gi);
-        const double app = nrm[p], aqq = nrm[q];
-        double ag, t, cs, sn;
-        zt em;  // e^{-i phi}
-        if (!jacobi_rotation(gr, gi, app, aqq, tol, ag, t, cs, sn, em)) continue;
-#pragma unroll
-        for (int i = 0; i < REGS; ++i) {
-          const int r = lane + 64 * i;
-          if (r < l) {
-            const zt x = xp[i], y = zmul(em, xq[i]);
-            cp[r] = zrot_lo(x, y, cs, sn);
-            cq[r] = zrot_hi(x, y, cs, sn);
-          }
-        }
-        zt* jp = J + size_t(p) * l;
-        zt* jq = J + size_t(q) * l;
-#pragma unroll
-        for (int i = 0; i < REGS; ++i) {
-          const int r = lane + 64 * i;
-          if (r < l) {
-            const zt x = jp[r], y = zmul(em, jq[r]);
-            jp[r] = zrot_lo(x, y, cs, sn);
-            jq[r] = zrot_hi(x, y, cs, sn);
-          }
-        }
-        if (lane == 0) {
-          nrm[p] = fmax(app - t * ag, 0.0);
-          nrm[q] = aqq + t * ag;
-          *rotated = 1;
-          if (ag * ag > kSmallTurn * (app * aqq)) *large = 1;
-        }
-      }
-      __syncthreads();
-    }
-    converged = (*rotated == 0);
-    const bool turned_far = (*large != 0);
-    __syncthreads();
-    if (ALL_PAIRS && !converged && !turned_far) {
-      for (int c = wave; c < l; c += NW) {
-        double s = 0.0;
-#pragma unroll
-        for (int i = 0; i < REGS; ++i) {
-          const int r = lane + 64 * i;
-          if (r < l) s += zabs2(C[size_t(c) * l + r]);
-        }
-        s = wave_sum(s);
-        if (lane == 0) nrm[c] = s;
-      }
-      __syncthreads();
-      converged = pairs_below_tol<NT>(C, l, l, tol, nrm);
-    }
-  }
-  converged_out = converged ? 1 : 0;
-}
-
 // Column norms, descending order, and the sorted outputs X, W, sig.
 template <int NT>
 __device__ __forceinline__ void jacobi_finish(Prob& P, const zt* C, const zt* J, int l,
@@ -271,13 +170,16 @@ __device__ __forceinline__ void jacobi_finish(Prob& P, const zt* C, const zt* J,
     perm_s[rank] = j;
   }
   __syncthreads();
-  for (int e = tid; e < l * l; e += NT) {
-    const int c = e / l, r = e - c * l;
+  for (int c = wave; c < l; c += NW) {
     const int src = perm_s[c];
-    const double sv = sig_s[src];
-    const zt x = C[size_t(src) * l + r];
-    P.X[e] = sv > 0.0 ? zscale(x, 1.0 / sv) : make_double2(0.0, 0.0);
-    P.W[e] = J[size_t(src) * l + r];
+    const double sv = sig_s[src], inv = sv > 0.0 ? 1.0 / sv : 0.0;
+    const zt* cc = C + size_t(src) * l;
+    const zt* jc = J + size_t(src) * l;
+    for (int r = lane; r < l; r += 64) {
+      const zt x = cc[r], w = jc[r];
+      P.X[size_t(c) * l + r] = sv > 0.0 ? zscale(x, inv) : make_double2(0.0, 0.0);
+      P.W[size_t(c) * l + r] = w;
+    }
   }
   for (int c = tid; c < l; c += NT) P.sig[c] = sig_s[perm_s[c]];
 }
@@ -401,8 +303,8 @@ __device__ __forceinline__ void truncate_tail(Prob& P, int l, double eps, int te
 
 // Size classes of the small SVD, by l: 0 (l <= 32, 256 threads) and 1
 // (l <= 64, 512 threads) rotate every pair of a round at once (k_svd_pairs);
-// 2 (C and J in LDS) and 3 (global memory) rotate one pair per wavefront at
-// a time (jacobi_core).
+// 2 and 3 rotate the pairs of two blocks of columns (jac_pair), 2 up to where
+// C and J would fit in LDS.
 __host__ __device__ __forceinline__ int svd_class(int l) {
   if (l <= 32) return 0;
   if (l <= 64) return 1;
@@ -421,7 +323,6 @@ __host__ __device__ __forceinline__ int svd_class(int l) {
 // and written whole (2 x 52 KB at l = 34, 128 B a cycle).  Measured, one
 // problem of l = 34: 270 us with a test per row and the library's square root
 // and division, 240 us so.
-// Same rotation, tolerance, carried norms and sweep limit as jacobi_core.
 constexpr int kPairGroup = 16;
 constexpr int kPairRowsLds0 = 2 * 32 * 33, kPairRowsLds1 = 2 * 64 * 65;  // elements of C and J
 
@@ -458,7 +359,6 @@ __global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int t
   const int GN = NT / lc2 < G ? NT / lc2 : G;  // lanes per column
   const int cn = tid / GN, hn = tid - cn * GN;
   const double tol = DBL_EPSILON * sqrt(double(l));
-  constexpr int kMaxSweeps = 40;
   bool converged = (l == 1);
   __syncthreads();
   for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
@@ -563,30 +463,37 @@ __global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int t
 }
 
 // --------------------------------------------------------------------------
-// Classes 2 and 3 over many workgroups.  One CU's share of the work is the
-// bound of a single-workgroup iteration (l = 200: 1.4 GFLOP of rotations and
-// 1.3 MB per round through one CU, 34 ms; l = 74: 2.9 ms), so the columns are
-// split into blocks of kJacBlock and a launch rotates, in one workgroup per
-// pair of blocks, every pair of columns across the two; the block pairs
-// follow the circle method, and the first launch of a sweep also rotates
-// the pairs inside the blocks.  A wavefront keeps one column of the first
-// block (its rows of C and J) in registers and meets the second block's
-// columns, in LDS, one after another.  Same rotation, tolerance, carried
-// norms and (kJacSweeps at most, then jacobi_core goes on) order of
-// magnitude of sweeps as one workgroup's circle: 5 to 7.
-// Measured, sum of the launches, one workgroup / these: l = 200, two problems
-// 33.8 / 3.1 ms; l = 74, 20 problems 2.86 / 0.90 ms.  A launch takes 4.5 us with
-// nothing to do, 13 us (l = 74) to 17 us (l = 200) with.
+// Classes 2 and 3.  The columns are split into blocks of kJacBlock; a
+// workgroup rotates every pair of columns across two blocks at a time
+// (jac_pair), the block pairs follow the circle method, and the first round
+// of a sweep also rotates the pairs inside the blocks.  A wavefront keeps one
+// column of the first block (its rows of C and J) in registers and meets the
+// second block's columns, in LDS, one after another.  Rotation, tolerance,
+// carried norms (recomputed for every block pair) and sweep limit as in
+// k_svd_pairs; 5 to 7 sweeps.
+//
+// The rounds are launches of a workgroup per block pair (k_jac_round) where the
+// host knows that there are such problems: one CU's arithmetic and memory
+// are the bound of a single workgroup (l = 200: 1.4 GFLOP of rotations).
+// k_small_svd then goes on where kJacSweeps sweeps were not enough; without
+// the launches it runs all of them, the same operations in the same order, so
+// that every rank mode of a sweep gives the same bits.
+// Measured, the whole small SVD of one workgroup that rotated single pairs /
+// these launches: l = 200, two problems 33.8 / 3.1 ms; l = 74, 20 problems
+// 2.86 / 0.90 ms; by one workgroup in blocks, l = 74 2.28 ms.  A launch takes
+// 4.5 us with nothing to do, 13 us (l = 74) to 17 us (l = 200) with.
 constexpr int kJacBlock = 8, kJacThreads = 64 * kJacBlock, kJacSweeps = 7, kJacCheckFrom = 2;
 
-// Per sweep s, in Prob::jac: bit s a rotation happened, bit 8 + s one of them
-// by more than a small turn, bit 16 + s the test of all pairs after it failed.
-// A sweep ends the iteration when nothing rotated in it, or only by small
-// turns and every pair passed the test (made from sweep kJacCheckFrom on).
+// Per launched sweep s, in Prob::jac: bit s a rotation happened, bit 8 + s one
+// of them by more than a small turn, bit 16 + s the test of all pairs after it
+// failed.
+__device__ __forceinline__ bool sweep_ended(bool rotated, bool more, int sweep) {
+  return !rotated || (!more && sweep >= kJacCheckFrom);
+}
 __device__ __forceinline__ bool jac_done(int bits, int sweep) {
-  const int rot = bits & 0xff;
-  const int more = ((bits >> 8 | bits >> 16) & 0xff) | ((1 << kJacCheckFrom) - 1);
-  return (~(rot & more) & ((1 << sweep) - 1)) != 0;
+  for (int s = 0; s < sweep; ++s)
+    if (sweep_ended(bits >> s & 1, (bits >> 8 | bits >> 16) >> s & 1, s)) return true;
+  return false;
 }
 static_assert(kJacSweeps <= 8, "bits per sweep in Prob::jac");
 
@@ -669,16 +576,22 @@ __device__ __forceinline__ int jac_rotate(JacColumn<REGS>& x, JacColumn<REGS>& y
   return r;
 }
 
+// kJacBlock wavefronts (this one is w): blocks a and b of round `round`; start:
+// C and J are still R_B^H and the identity.  Returns bit 0: something rotated,
+// bit 8: by more than a small turn (in any such group of the workgroup: they
+// run in step, each with lds and sh of its own).  lds: columns of C, then of
+// J, per slot: kJacBlock slots of the second block, and in round 0 as many of
+// the first.  Columns beyond l count as zero.
+struct JacShared {
+  double nrm[2 * kJacBlock];
+  int changed[kJacBlock];
+};
+
 template <int REGS>
-__global__ __launch_bounds__(kJacThreads) void k_jac_round(Prob* probs, const int32_t* list,
-                                                           int nprob, int pairs, int sweep,
-                                                           int round) {
-  extern __shared__ zt lds[];  // columns of C, then of J, per slot: second block, first block
-  __shared__ double nrm[2 * kJacBlock];
-  __shared__ int changed[kJacBlock];
+__device__ __forceinline__ int jac_pair(Prob& P, int a, int b, int round, bool start, int w,
+                                        zt* lds, JacShared& sh) {
   constexpr int S = 64 * REGS;
-  const int lane = threadIdx.x & 63, w = wave_id();
-  const int items = (list[nprob] & kJacCountMask) * pairs;
+  const int lane = threadIdx.x & 63, l = P.l;
   auto put = [&](int slot, const JacColumn<REGS>& x) {
     zt* at = lds + slot * 2 * S + lane;
 #pragma unroll
@@ -695,209 +608,238 @@ __global__ __launch_bounds__(kJacThreads) void k_jac_round(Prob* probs, const in
       x.j[i] = at[S + 64 * i];
     }
   };
+  auto load = [&](int col, JacColumn<REGS>& x) {
+    const int cc = col < l ? col : l - 1;
+#pragma unroll
+    for (int u = 0; u < REGS; ++u) {
+      const int r = lane + 64 * u, rc = r < l ? r : l - 1;
+      const bool in = r < l && col < l;
+      const zt v = start ? zconj(P.Rb[size_t(rc) * l + cc]) : P.C[size_t(cc) * l + rc];
+      const zt vj = start ? make_double2(r == col ? 1.0 : 0.0, 0.0) : P.J[size_t(cc) * l + rc];
+      x.c[u] = make_double2(in ? v.x : 0.0, in ? v.y : 0.0);
+      x.j[u] = make_double2(in ? vj.x : 0.0, in ? vj.y : 0.0);
+    }
+  };
+  auto store = [&](int col, const JacColumn<REGS>& x) {
+    if (col >= l) return;
+#pragma unroll
+    for (int u = 0; u < REGS; ++u) {
+      const int r = lane + 64 * u;
+      if (r < l) {
+        P.C[size_t(col) * l + r] = x.c[u];
+        P.J[size_t(col) * l + r] = x.j[u];
+      }
+    }
+  };
+  const int p = (a < b ? a : b) * kJacBlock + w, q = (a < b ? b : a) * kJacBlock + w;
+  const double tol = DBL_EPSILON * sqrt(double(l));
+  JacColumn<REGS> x, y;
+  load(p, x);
+  load(q, y);
+  int bits = 0;
+  double na = jac_norm2(x);
+  {
+    const double n = jac_norm2(y);
+    if (lane == 0) {
+      sh.nrm[w] = n;
+      sh.nrm[kJacBlock + w] = na;
+      sh.changed[w] = start;
+    }
+  }
+  put(w, y);
+  bool moved = start;  // the first block's column
+  if (round == 0) {    // the pairs inside either block
+    put(kJacBlock + w, x);
+    for (int r = 0; r < kJacBlock - 1; ++r) {
+      const int h = w & (kJacBlock / 2 - 1), side = w < kJacBlock / 2 ? 0 : kJacBlock;
+      const int s0 = circle_player(h, r, kJacBlock),
+                s1 = circle_player(kJacBlock - 1 - h, r, kJacBlock);
+      const int lo = side + (s0 < s1 ? s0 : s1), hi = side + (s0 < s1 ? s1 : s0);
+      __syncthreads();
+      get(lo, x);
+      get(hi, y);
+      double nl = sh.nrm[lo], nh = sh.nrm[hi];
+      const int c = jac_rotate(x, y, tol, nl, nh);
+      if (c) {
+        put(lo, x);
+        put(hi, y);
+        if (lane == 0) {
+          sh.nrm[lo] = nl;
+          sh.nrm[hi] = nh;
+        }
+      }
+      bits |= c;
+    }
+    const bool inner = __syncthreads_or(bits) != 0;
+    moved |= inner;
+    if (lane == 0 && inner) sh.changed[w] = 1;
+    get(kJacBlock + w, x);
+    na = sh.nrm[kJacBlock + w];
+  }
+  for (int s = 0; s < kJacBlock; ++s) {
+    const int slot = (w + s) & (kJacBlock - 1);
+    __syncthreads();
+    get(slot, y);
+    double n = sh.nrm[slot];
+    const int c = jac_rotate(x, y, tol, na, n);
+    if (c) {
+      put(slot, y);
+      if (lane == 0) {
+        sh.nrm[slot] = n;
+        sh.changed[slot] = 1;
+      }
+      moved = true;
+    }
+    bits |= c;
+  }
+  if (moved) store(p, x);
+  const int all = (__syncthreads_or(bits & 1) ? 1 : 0) | (__syncthreads_or(bits & 2) ? 1 << 8 : 0);
+  if (sh.changed[w]) {
+    get(w, y);
+    store(q, y);
+  }
+  __syncthreads();  // the slots are free, and C and J in place for the workgroup
+  return all;
+}
+
+// Blocks of a problem, an even number of them (with one that is none).
+__host__ __device__ __forceinline__ int jac_blocks(int l) {
+  return ((l + kJacBlock - 1) / kJacBlock + 1) & ~1;
+}
+
+template <int REGS>
+__global__ __launch_bounds__(kJacThreads) void k_jac_round(Prob* probs, const int32_t* list,
+                                                           int nprob, int pairs, int sweep,
+                                                           int round) {
+  extern __shared__ zt lds[];
+  __shared__ JacShared sh;
+  const int items = (list[nprob] & kJacCountMask) * pairs;
   for (int it = blockIdx.x; it < items; it += gridDim.x) {
     const int i = it / pairs, k = it - i * pairs;
     Prob& P = probs[list[i]];
-    const int l = P.l, nb = ((l + kJacBlock - 1) / kJacBlock + 1) & ~1;
+    const int nb = jac_blocks(P.l);
     if (k >= nb / 2 || round >= nb - 1 || jac_done(P.jac, sweep)) continue;
     const int a = circle_player(k, round, nb), b = circle_player(nb - 1 - k, round, nb);
     // an odd number of blocks: the last player is none (its partner's inner
     // pairs still rotate)
-    if (round > 0 && (a > b ? a : b) * kJacBlock >= l) continue;
-    const int p = (a < b ? a : b) * kJacBlock + w, q = (a < b ? b : a) * kJacBlock + w;
-    const double tol = DBL_EPSILON * sqrt(double(l));
-    const bool start = sweep == 0 && round == 0;
-    auto load = [&](int col, JacColumn<REGS>& x) {
-      const int cc = col < l ? col : l - 1;
-#pragma unroll
-      for (int u = 0; u < REGS; ++u) {
-        const int r = lane + 64 * u, rc = r < l ? r : l - 1;
-        const bool in = r < l && col < l;
-        const zt v = start ? zconj(P.Rb[size_t(rc) * l + cc]) : P.C[size_t(cc) * l + rc];
-        const zt vj = start ? make_double2(r == col ? 1.0 : 0.0, 0.0) : P.J[size_t(cc) * l + rc];
-        x.c[u] = make_double2(in ? v.x : 0.0, in ? v.y : 0.0);
-        x.j[u] = make_double2(in ? vj.x : 0.0, in ? vj.y : 0.0);
-      }
-    };
-    auto store = [&](int col, const JacColumn<REGS>& x) {
-      if (col >= l) return;
-#pragma unroll
-      for (int u = 0; u < REGS; ++u) {
-        const int r = lane + 64 * u;
-        if (r < l) {
-          P.C[size_t(col) * l + r] = x.c[u];
-          P.J[size_t(col) * l + r] = x.j[u];
-        }
-      }
-    };
-    JacColumn<REGS> x, y;
-    load(p, x);
-    load(q, y);
-    int bits = 0;
-    double na = jac_norm2(x);
-    {
-      const double n = jac_norm2(y);
-      if (lane == 0) {
-        nrm[w] = n;
-        nrm[kJacBlock + w] = na;
-        changed[w] = start;
-      }
-    }
-    put(w, y);
-    bool moved = start;  // the first block's column
-    if (round == 0) {    // the pairs inside either block
-      put(kJacBlock + w, x);
-      for (int r = 0; r < kJacBlock - 1; ++r) {
-        const int h = w & (kJacBlock / 2 - 1), side = w < kJacBlock / 2 ? 0 : kJacBlock;
-        const int s0 = circle_player(h, r, kJacBlock),
-                  s1 = circle_player(kJacBlock - 1 - h, r, kJacBlock);
-        const int lo = side + (s0 < s1 ? s0 : s1), hi = side + (s0 < s1 ? s1 : s0);
-        __syncthreads();
-        get(lo, x);
-        get(hi, y);
-        double nl = nrm[lo], nh = nrm[hi];
-        const int c = jac_rotate(x, y, tol, nl, nh);
-        if (c) {
-          put(lo, x);
-          put(hi, y);
-          if (lane == 0) {
-            nrm[lo] = nl;
-            nrm[hi] = nh;
-          }
-        }
-        bits |= c;
-      }
-      const bool inner = __syncthreads_or(bits) != 0;
-      moved |= inner;
-      if (lane == 0 && inner) changed[w] = 1;
-      get(kJacBlock + w, x);
-      na = nrm[kJacBlock + w];
-    }
-    for (int s = 0; s < kJacBlock; ++s) {
-      const int slot = (w + s) & (kJacBlock - 1);
-      __syncthreads();
-      get(slot, y);
-      double n = nrm[slot];
-      const int c = jac_rotate(x, y, tol, na, n);
-      if (c) {
-        put(slot, y);
-        if (lane == 0) {
-          nrm[slot] = n;
-          changed[slot] = 1;
-        }
-        moved = true;
-      }
-      bits |= c;
-    }
-    if (moved) store(p, x);
-    const int all = (__syncthreads_or(bits & 1) ? 1 : 0) | (__syncthreads_or(bits & 2) ? 1 << 8 : 0);
-    if (changed[w]) {
-      get(w, y);
-      store(q, y);
-    }
-    if (threadIdx.x == 0 && all) atomicOr(&P.jac, all << sweep);
-    __syncthreads();  // nrm, changed and the slots are free
+    if (round > 0 && (a > b ? a : b) * kJacBlock >= P.l) continue;
+    const int bits = jac_pair<REGS>(P, a, b, round, sweep == 0 && round == 0, wave_id(), lds, sh);
+    if (threadIdx.x == 0 && bits) atomicOr(&P.jac, bits << sweep);
   }
 }
 
 // The test of all pairs after a sweep of small turns only (jacobi_rotation's,
-// norms recomputed): a wavefront per 16 x 16 tile of the Gram matrix.
+// norms recomputed).  One wavefront: tile (bi, bj) of the Gram matrix; true
+// when a pair of it would still be rotated.
+__device__ __forceinline__ bool jac_tile_bad(const Prob& P, int bi, int bj) {
+  const int lane = threadIdx.x & 63, ti = lane & 15, tk = lane >> 4, l = P.l;
+  const int p = bi * 16 + ti, q = bj * 16 + ti;
+  const zt* cp = P.C + size_t(p < l ? p : l - 1) * l;
+  const zt* cq = P.C + size_t(q < l ? q : l - 1) * l;
+  v4d re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+  double np = 0.0, nq = 0.0;
+  for (int k0 = 0; k0 < l; k0 += 16) {
+    zt u[4], v[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = k0 + 4 * s + tk, kc = k < l ? k : l - 1;
+      u[s] = cp[kc];
+      v[s] = cq[kc];
+      if (k >= l) u[s] = v[s] = make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {  // g = conj(u) v
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].x, v[s].x, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].x, v[s].y, im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].y, v[s].y, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(-u[s].y, v[s].x, im, 0, 0, 0);
+      np += zabs2(u[s]);
+      nq += zabs2(v[s]);
+    }
+  }
+  np += __shfl_xor(np, 16, 64);
+  np += __shfl_xor(np, 32, 64);
+  nq += __shfl_xor(nq, 16, 64);
+  nq += __shfl_xor(nq, 32, 64);
+  const double tol = DBL_EPSILON * sqrt(double(l));
+  bool bad = false;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {  // entry (tk + 4 r, ti) of the tile
+    const int row = tk + 4 * r;
+    const double nr = __shfl(np, row, 64), g2 = re[r] * re[r] + im[r] * im[r];
+    const bool pair = bi * 16 + row < q && q < l;
+    bad |= pair && g2 > tol * tol * (nr * nq) && g2 != 0.0;
+  }
+  return __any(bad);
+}
+
 __global__ __launch_bounds__(256) void k_jac_check(Prob* probs, const int32_t* list, int nprob,
                                                    int blocks, int sweep) {
-  const int lane = threadIdx.x & 63, ti = lane & 15, tk = lane >> 4;
   const int tiles = blocks * blocks;
   const int items = (list[nprob] & kJacCountMask) * tiles;
   for (int it = blockIdx.x * 4 + wave_id(); it < items; it += gridDim.x * 4) {
     const int i = it / tiles, t = it - i * tiles, bi = t / blocks, bj = t - bi * blocks;
     Prob& P = probs[list[i]];
-    const int l = P.l, bits = P.jac >> sweep;
-    if (bi > bj || bj * 16 >= l || !(bits & 1) || (bits & (1 << 8)) || jac_done(P.jac, sweep))
+    const int bits = P.jac >> sweep;
+    if (bi > bj || bj * 16 >= P.l || !(bits & 1) || (bits & (1 << 8)) || jac_done(P.jac, sweep))
       continue;
-    const int p = bi * 16 + ti, q = bj * 16 + ti;
-    const zt* cp = P.C + size_t(p < l ? p : l - 1) * l;
-    const zt* cq = P.C + size_t(q < l ? q : l - 1) * l;
-    v4d re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
-    double np = 0.0, nq = 0.0;
-    for (int k0 = 0; k0 < l; k0 += 16) {
-      zt u[4], v[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = k0 + 4 * s + tk, kc = k < l ? k : l - 1;
-        u[s] = cp[kc];
-        v[s] = cq[kc];
-        if (k >= l) u[s] = v[s] = make_double2(0.0, 0.0);
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {  // g = conj(u) v
-        re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].x, v[s].x, re, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].x, v[s].y, im, 0, 0, 0);
-        re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s].y, v[s].y, re, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f64_16x16x4f64(-u[s].y, v[s].x, im, 0, 0, 0);
-        np += zabs2(u[s]);
-        nq += zabs2(v[s]);
-      }
-    }
-    np += __shfl_xor(np, 16, 64);
-    np += __shfl_xor(np, 32, 64);
-    nq += __shfl_xor(nq, 16, 64);
-    nq += __shfl_xor(nq, 32, 64);
-    const double tol = DBL_EPSILON * sqrt(double(l));
-    bool bad = false;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {  // entry (tk + 4 r, ti) of the tile
-      const int row = tk + 4 * r;
-      const double nr = __shfl(np, row, 64), g2 = re[r] * re[r] + im[r] * im[r];
-      const bool pair = bi * 16 + row < q && q < l;
-      bad |= pair && g2 > tol * tol * (nr * nq) && g2 != 0.0;
-    }
-    if (__any(bad) && lane == 0) atomicOr(&P.jac, 1 << (16 + sweep));
+    if (jac_tile_bad(P, bi, bj) && (threadIdx.x & 63) == 0) atomicOr(&P.jac, 1 << (16 + sweep));
   }
 }
 
-// Classes 2 and 3 by one workgroup: one pair per wavefront at a time
-// (jacobi_core), C and J in LDS (LDS_CJ) or in the problem's global scratch.
-// resumed: both classes, after the launches above (the iteration only where
-// they did not finish it).
-template <int NT, int REGS, bool LDS_CJ>
-__global__ __launch_bounds__(NT) void k_small_svd(Prob* probs, double eps, int tebd,
-                                                  int32_t* retry_count, int resumed) {
+// The rest of the iteration (all of it without the launches above: first = 0),
+// one workgroup per problem, then the sorted outputs and the truncation.
+// PAR block pairs of a round at a time (two as long as their LDS fits).
+template <int REGS, int PAR>
+__global__ __launch_bounds__(kJacThreads* PAR) void k_small_svd(Prob* probs, double eps, int tebd,
+                                                                int32_t* retry_count, int first) {
   extern __shared__ zt lds[];
+  constexpr int NT = kJacThreads * PAR;
+  __shared__ JacShared sh[PAR];
   __shared__ double sig_s[kMaxL];
+  __shared__ double scan[kMaxL];
   __shared__ int perm_s[kMaxL];
-  __shared__ int rotated, large_turn;
-  __shared__ double nrm[kMaxL];
   Prob& P = probs[blockIdx.x];
   const int l = P.l;
-  if (l == 0 || (resumed ? svd_class(l) < 2 : svd_class(l) != (LDS_CJ ? 2 : 3))) return;
-  zt* C = LDS_CJ ? lds : P.C;
-  zt* J = LDS_CJ ? lds + l * l : P.J;
-  int converged = 1;
-  if (!resumed || !jac_done(P.jac, kJacSweeps)) {
-    if (!resumed)
-      for (int e = threadIdx.x; e < l * l; e += NT) {
-        const int c = e / l, r = e - c * l;
-        C[e] = zconj(P.Rb[size_t(r) * l + c]);
-        J[e] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+  if (l == 0 || svd_class(l) < 2) return;
+  const int nb = jac_blocks(l), blocks = (l + 15) / 16;
+  bool converged = first > 0 && jac_done(P.jac, first);
+  for (int sweep = first; sweep < kMaxSweeps && !converged; ++sweep) {
+    int bits = 0;
+    for (int round = 0; round < nb - 1; ++round)
+      for (int k0 = 0; k0 < nb / 2; k0 += PAR) {
+        const int g = wave_id() / kJacBlock, k = k0 + g;
+        const bool any = k < nb / 2;  // else a pair of blocks beyond l
+        bits |= jac_pair<REGS>(P, any ? circle_player(k, round, nb) : nb,
+                               any ? circle_player(nb - 1 - k, round, nb) : nb + 1, round,
+                               sweep == 0 && round == 0, wave_id() % kJacBlock,
+                               lds + size_t(g) * 4 * kJacBlock * 64 * REGS, sh[g]);
       }
-    __syncthreads();
-    // the all-pairs test only where C is in LDS (from global memory it costs
-    // about the sweep it would save)
-    jacobi_core<NT, REGS, LDS_CJ>(C, J, l, converged, &rotated, &large_turn, nrm);
+    bool bad = false;
+    if (sweep >= kJacCheckFrom && bits == 1) {
+      for (int t = wave_id(); t < blocks * blocks; t += NT / 64)
+        if (t / blocks <= t % blocks) bad |= jac_tile_bad(P, t / blocks, t % blocks);
+      bad = __syncthreads_or(bad) != 0;
+    }
+    converged = sweep_ended(bits & 1, bits >> 8 & 1 || bad, sweep);
   }
   if (!converged && threadIdx.x == 0) P.flags |= TEBD_DEV_JACOBI_NOCONV;
-  jacobi_finish<NT>(P, C, J, l, sig_s, perm_s);
-  truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return sig_s[perm_s[c]]; }, nrm);
+  jacobi_finish<NT>(P, P.C, P.J, l, sig_s, perm_s);
+  truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return sig_s[perm_s[c]]; }, scan);
 }
+
+// LDS of one column of C and J.
+size_t jac_column_bytes(int lmax) { return (lmax <= 128 ? 2 * 128 : 2 * 256) * sizeof(zt); }
 
 // The launches of the wide small SVD (classes 2 and 3) for at most `count`
 // problems of at most lmax columns.
 void launch_jacobi_rounds(Prob* probs, const int32_t* list, int nprob, int count, int lmax,
                           hipStream_t s) {
-  const int nb = ((lmax + kJacBlock - 1) / kJacBlock + 1) & ~1, pairs = nb / 2;
+  const int nb = jac_blocks(lmax), pairs = nb / 2;
   const int blocks = (lmax + 15) / 16;
   const int64_t items = int64_t(count) * pairs, tiles = int64_t(count) * blocks * blocks;
   const dim3 g(unsigned(items < 1024 ? items : 1024)), gt(unsigned(tiles < 4096 ? (tiles + 3) / 4 : 1024));
-  const size_t column = lmax <= 128 ? 2 * 128 * sizeof(zt) : 2 * 256 * sizeof(zt);
+  const size_t column = jac_column_bytes(lmax);
   for (int sweep = 0; sweep < kJacSweeps; ++sweep) {
     for (int r = 0; r < nb - 1; ++r) {
       const size_t lds = (r == 0 ? 2 : 1) * kJacBlock * column;
@@ -939,7 +881,8 @@ hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
     const struct {
       const void* fn;
       size_t elems;
-    } lds[] = {{reinterpret_cast<const void*>(&k_small_svd<1024, 2, true>), size_t(kLdsElems)},
+    } lds[] = {{reinterpret_cast<const void*>(&k_small_svd<2, 2>), size_t(8 * kJacBlock * 128)},
+               {reinterpret_cast<const void*>(&k_small_svd<4, 1>), size_t(4 * kJacBlock * 256)},
                {reinterpret_cast<const void*>(&k_svd_pairs<512, 1>), size_t(kPairRowsLds1)},
                {reinterpret_cast<const void*>(&k_jac_round<2>), size_t(4 * kJacBlock * 128)},
                {reinterpret_cast<const void*>(&k_jac_round<4>), size_t(4 * kJacBlock * 256)}};
@@ -965,23 +908,21 @@ hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
     TEBD_LAUNCH("k_svd_pairs<512, 1>", (k_svd_pairs<512, 1>), dim3(c.nprob), dim3(512),
                 kPairRowsLds1 * sizeof(zt), t, probs, c.eps, c.tebd, retry);
   };
-  auto small2 = [&](hipStream_t t) {
-    TEBD_LAUNCH("k_small_svd<1024, 2, true>", (k_small_svd<1024, 2, true>), dim3(c.nprob),
-                dim3(1024), size_t(kLdsElems) * sizeof(zt), t, probs, c.eps, c.tebd, retry, 0);
-  };
-  auto small3 = [&](hipStream_t t) {
+  auto wider = [&](hipStream_t t) {
     if (wide) launch_jacobi_rounds(probs, jac_list(c), c.nprob, c.wide_n, c.wide_l, t);
-    TEBD_LAUNCH("k_small_svd<1024, 4, false>", (k_small_svd<1024, 4, false>), dim3(c.nprob),
-                dim3(1024), 0, t, probs, c.eps, c.tebd, retry, wide ? 1 : 0);
+    const int first = wide ? kJacSweeps : 0;
+    const int l = wide ? c.wide_l : c.lmax;
+    const size_t lds = 2 * kJacBlock * jac_column_bytes(l);
+    if (l <= 128)
+      TEBD_LAUNCH("k_small_svd<2, 2>", (k_small_svd<2, 2>), dim3(c.nprob), dim3(2 * kJacThreads), 2 * lds, t, probs, c.eps, c.tebd, retry, first);
+    else
+      TEBD_LAUNCH("k_small_svd<4, 1>", (k_small_svd<4, 1>), dim3(c.nprob), dim3(kJacThreads), lds, t, probs, c.eps, c.tebd, retry, first);
   };
-  const std::function<void(hipStream_t)> fns[4] = {pairs0, pairs1, small2, small3};
-  std::function<void(hipStream_t)> items[4];
+  const std::function<void(hipStream_t)> fns[3] = {pairs0, pairs1, wider};
+  std::function<void(hipStream_t)> items[3];
   int n = 0;
   for (int k = lo; k <= hi && k < 2; ++k) items[n++] = fns[k];
-  if (wide)
-    items[n++] = fns[3];
-  else
-    for (int k = lo < 2 ? 2 : lo; k <= hi; ++k) items[n++] = fns[k];
+  if (hi >= 2) items[n++] = fns[2];
   return fork_join(s, items, n, c);
 }
 

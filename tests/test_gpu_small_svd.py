@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import test_gpu_rrsvd as rr
+import test_gpu_tebd as tb
 import workloads as wl
 from paper_1504_00992_amd import _lib
 
@@ -57,3 +58,25 @@ def test_a_batch_of_more_pairs_than_workgroups():
         assert np.max(np.abs(S[i][:ochi] - os_)) <= 1e-10 * os_[0]
         rec = (U[i][:, :ochi] * S[i][None, :ochi]) @ VH[i][:ochi]
         assert np.max(np.abs(rec - (ou * os_[None, :]) @ ovh)) <= 1e-10 * os_[0]
+
+
+@pytest.mark.parametrize("chi,cap,chi_max", [(70, 90, 80), (75, 100, 66), (110, 130, 125)])
+def test_rank_modes_agree_bitwise_beyond_64_columns(chi, cap, chi_max):
+    # adaptive 1 (only enqueues: a workgroup per problem) and 2 (the host knows
+    # the sizes: a launch per round) rotate in the same order
+    import torch
+    from paper_1504_00992_amd import api
+    dims, chis = [2, 2, 2, 2], [1, chi, chi, chi, 1]
+    gam, lam = tb._random_chain(dims, chis, 5)
+    gate = torch.from_numpy(wl.random_unitary(4, wl.rng(3))).cuda()
+    out = []
+    for mode in (1, 2):
+        dev = api.DeviceMPS.from_host([(gam, lam)], dims, cap)
+        prm = api._lib.params(chi_max, 10, 2, 1e-10, 1e-14, 1504, 5, 0, mode)
+        ws = api.BondWorkspace(dev, prm)
+        api.tebd_bond_update(dev, 0, 1, gate, prm, ws)
+        torch.cuda.synchronize()
+        out.append((dev.gamma.clone(), dev.lam.clone(), dev.chi.clone(), ws.disc.clone()))
+    assert int(out[0][2].max()) > 64
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
