@@ -338,10 +338,10 @@ tebd_status tebd_profile_read(int32_t capacity, const char** names, double* ms, 
  * power-iteration and projection products of Alg. 1 and Sec. IV step i per
  * launch, from the largest problem of the batch: its row count (bucketed
  * as <= 128, 256, 512, 1024, 2048, 8192) and sketch width (<= 32, 64, 80,
- * 128, 256).  variant 0: 32 x 32 output tiles (the default, also for unset
- * entries); 1: 64 x 64 tiles; 2: 16 x 16 tiles, each split over the
- * contraction depth between the four wavefronts of its workgroup; -1
- * unsets.  precision 1 (complex FP32 products) has variant 0 only.
+ * 128, 256).  variant 0: 32 x 32 output tiles; 1: 64 x 64 tiles; 2: 16 x 16
+ * tiles, each split over the contraction depth between the four wavefronts
+ * of its workgroup; -1 unsets, and an unset entry is 2 for launches of few
+ * tiles and 0 for the others.  precision 1 (complex FP32 products) has variant 0 only.
  * precision 2 is the table of the TEBD entry points' FP64 products: it is
  * read under the MPS capacities (d_max * chi_max rows, chi_max + p width)
  * instead of a batch's bounds, so that every rank mode, graph capture

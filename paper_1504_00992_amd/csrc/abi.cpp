@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "kinds.hpp"
 
 using namespace tebd;
 
@@ -789,8 +790,26 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
   da.chi_out = chi_kept;
   da.disc = disc_weight;
   da.status = dev_status;
-  int64_t tiles = 0;
-  for (int64_t b = 0; b < batch; ++b) {
+  int64_t tiles = 0, known[TK_COUNT] = {};
+  // the largest matrices first: their tiles and workgroups take longest, and
+  // the small ones then fill the end of a launch
+  std::vector<int64_t> order(static_cast<size_t>(batch));
+  for (int64_t b = 0; b < batch; ++b) order[size_t(b)] = b;
+  if (!noalloc)
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int64_t x, int64_t y) { return m[x] * n[x] > m[y] * n[y]; });
+  for (int64_t at = 0; at < batch; ++at) {
+    const int64_t b = order[size_t(at)];
+    {
+      // the tiles of the products, so that their launches have a workgroup each
+      const int64_t l = sketch_l(prm->chi_max, prm->p, m[b], n[b]);
+      known[TK_SKM] += tiles_of<TK_SKM>(m[b], l);
+      known[TK_SKN] += tiles_of<TK_SKN>(n[b], l);
+      known[TK_SKM_W] += tiles_of<TK_SKM_W>(m[b], l);
+      known[TK_SKN_W] += tiles_of<TK_SKN_W>(n[b], l);
+      known[TK_SKM_S] += tiles_of<TK_SKM_S>(m[b], l);
+      known[TK_SKN_S] += tiles_of<TK_SKN_S>(n[b], l);
+    }
     {
       const int64_t tm = (m[b] + 63) / 64, tn = (n[b] + 63) / 64;
       const int64_t tk = (prm->chi_max + 63) / 64;
@@ -815,17 +834,17 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
       c.mmin = o.m < c.mmin ? o.m : c.mmin;
       c.nmin = o.n < c.nmin ? o.n : c.nmin;
       c.lmin = l < c.lmin ? l : c.lmin;
-      if (da.count == kDescPerLaunch || b + 1 == batch) {
+      if (da.count == kDescPerLaunch || at + 1 == batch) {
         hipLaunchKernelGGL(k_noalloc_desc, dim3(1), dim3(64), 0, s, da);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
           return fail(TEBD_ERR_DEVICE, "HIP error while enqueuing: %s", hipGetErrorString(e));
-        da.first = int32_t(b + 1);
+        da.first = int32_t(at + 1);
         da.count = 0;
       }
       continue;
     }
-    Prob& P = host[b];
+    Prob& P = host[size_t(at)];
     std::memset(&P, 0, sizeof(Prob));
     P.m = int32_t(m[b]);
     P.n = int32_t(n[b]);
@@ -861,6 +880,8 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
   }
   c.offs = reinterpret_cast<int32_t*>(base + align256(size_t(batch) * sizeof(Prob)));
   c.grid = persistent_grid(tiles);
+  for (const int k : {TK_SKM, TK_SKN, TK_SKM_W, TK_SKN_W, TK_SKM_S, TK_SKN_S})
+    c.ktiles[k] = int32_t(std::min<int64_t>(known[k], kKnownGridMax));
   hipError_t e = noalloc ? hipSuccess : upload(workspace, host.data(), host.size() * sizeof(Prob), s);
   if (e == hipSuccess) e = run_pipeline(reinterpret_cast<Prob*>(workspace), c, s);
   if (e != hipSuccess) return fail(TEBD_ERR_DEVICE, "HIP error while enqueuing: %s", hipGetErrorString(e));

@@ -258,10 +258,33 @@ hipError_t launch_theta_gate(Prob* probs, const Common& c, hipStream_t s) {
 // --------------------------------------------------------------------------
 // Sketch / power iteration / projection products
 
+// Wavefront split of the depth (zgemm_tile_split16) for launches of few tiles,
+// 32 x 32 tiles otherwise: a launch of up to kSplitTiles 32 x 32 tiles leaves
+// CUs idle or with one tile each, whose chain over the whole depth is its
+// time.  Measured, the six products of a truncation, 32 x 32 / split: 96 x 80,
+// l = 34 (9 tiles) 45 / 30 us; 1 x 2048^2, l = 74 (192 tiles) 881 / 540; 4 x
+// 1024^2, l = 74 (384) 612 / 502; 60 x 200^2, l = 30 (420) 154 / 165; 120 x
+// 200^2 (840) 251 / 294; 400 x 100^2 (1600) 242 / 280.  Decided on the device,
+// by the queue's total, so that it does not depend on what the host knows.
+constexpr int kSplitTiles = 400;
+__device__ __forceinline__ bool split_depth(const int32_t* offs, int nprob, int kind, int most) {
+  return offs[size_t(kind) * (nprob + 1) + nprob] <= most;
+}
+
+template <int WHICH>
+__device__ __forceinline__ void sketch_split(Prob* probs, const int32_t* offs, int nprob, int tebd,
+                                             double* red);
+
+// split_most: the most tiles that take the split (0: none, a tuned choice)
 template <int WHICH>
 __global__ __launch_bounds__(256) void k_sketch(Prob* probs, const int32_t* offs, int nprob,
-                                                int tebd) {
+                                                int tebd, int split_most) {
   __shared__ zt smem[CfgSk::lds_elems];
+  static_assert(sizeof(smem) >= 2048 * sizeof(double), "the split's partial tiles fit");
+  if (split_depth(offs, nprob, WHICH == SK_YT_FROM_Y ? TK_SKN : TK_SKM, split_most)) {
+    sketch_split<WHICH>(probs, offs, nprob, tebd, reinterpret_cast<double*>(smem));
+    return;
+  }
   if (WHICH == SK_Y_FROM_OMEGA) {
     for_each_tile<TK_SKM>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdRowA la{P.A, P.lda};
@@ -373,11 +396,10 @@ __global__ __launch_bounds__(256) void k_sketch_wide(Prob* probs, const int32_t*
 
 // The FP64 sketch products on 16 x 16 tiles, each split over the depth
 // between the four wavefronts (zgemm_tile_split16; chosen per launch by the
-// autotune cache).
+// autotune cache, or by k_sketch itself).
 template <int WHICH>
-__global__ __launch_bounds__(256) void k_sketch_split(Prob* probs, const int32_t* offs, int nprob,
-                                                      int tebd) {
-  __shared__ double red[2048];
+__device__ __forceinline__ void sketch_split(Prob* probs, const int32_t* offs, int nprob, int tebd,
+                                             double* red) {
   if (WHICH == SK_Y_FROM_OMEGA) {
     for_each_tile<TK_SKM_S>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdRowA la{P.A, P.lda};
@@ -402,9 +424,17 @@ __global__ __launch_bounds__(256) void k_sketch_split(Prob* probs, const int32_t
   }
 }
 
+template <int WHICH>
+__global__ __launch_bounds__(256) void k_sketch_split(Prob* probs, const int32_t* offs, int nprob,
+                                                      int tebd) {
+  __shared__ double red[2048];
+  sketch_split<WHICH>(probs, offs, nprob, tebd, red);
+}
+
 // Autotune cache: variant per (precision, rows bucket, width bucket): 0 the
 // 32 x 32 tiles, 1 the 64 x 64 tiles, 2 the split-depth 16 x 16 tiles; -1
-// (unset) means the 32 x 32 tiles.  Written by tebd_tune_set between calls.
+// (unset) leaves the choice between the first and the last to k_sketch.
+// Written by tebd_tune_set between calls.
 namespace {
 constexpr int kTuneRows[6] = {128, 256, 512, 1024, 2048, 8192};
 constexpr int kTuneWidth[5] = {32, 64, 80, 128, 256};
@@ -419,11 +449,9 @@ int tune_bucket(const int* bounds, int nb, int v) {
 }  // namespace
 
 int sketch_variant(int table, int max_rows, int width) {
-  if (table == 1 || !g_tune_init) return 0;
+  if (table == 1 || !g_tune_init) return -1;
   const int br = tune_bucket(kTuneRows, 6, max_rows), bw = tune_bucket(kTuneWidth, 5, width);
-  if (br < 0 || bw < 0) return 0;
-  const int v = g_tune[table][br][bw];
-  return v < 0 ? 0 : v;
+  return br < 0 || bw < 0 ? -1 : g_tune[table][br][bw];
 }
 
 hipError_t launch_sketch(Prob* probs, const Common& c, int which, hipStream_t s) {
@@ -452,13 +480,16 @@ hipError_t launch_sketch(Prob* probs, const Common& c, int which, hipStream_t s)
       TEBD_LAUNCH("k_sketch_split<2>", k_sketch_split<SK_Y_FROM_YT>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd);
     return hipGetLastError();
   }
-  const dim3 g(grid_for(c, which == SK_YT_FROM_Y ? TK_SKN : TK_SKM));
+  const int most = variant < 0 ? kSplitTiles : 0;
+  const int kind = which == SK_YT_FROM_Y ? TK_SKN : TK_SKM;
+  const bool split = c.ktiles[kind] >= 0 && c.ktiles[kind] <= most;
+  const dim3 g(grid_for(c, !split ? kind : kind == TK_SKN ? TK_SKN_S : TK_SKM_S));
   if (which == SK_Y_FROM_OMEGA)
-    TEBD_LAUNCH("k_sketch<0>", k_sketch<SK_Y_FROM_OMEGA>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd);
+    TEBD_LAUNCH("k_sketch<0>", k_sketch<SK_Y_FROM_OMEGA>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, most);
   else if (which == SK_YT_FROM_Y)
-    TEBD_LAUNCH("k_sketch<1>", k_sketch<SK_YT_FROM_Y>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd);
+    TEBD_LAUNCH("k_sketch<1>", k_sketch<SK_YT_FROM_Y>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, most);
   else
-    TEBD_LAUNCH("k_sketch<2>", k_sketch<SK_Y_FROM_YT>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd);
+    TEBD_LAUNCH("k_sketch<2>", k_sketch<SK_Y_FROM_YT>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, most);
   return hipGetLastError();
 }
 

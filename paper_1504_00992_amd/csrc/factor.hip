@@ -243,29 +243,48 @@ hipError_t launch_plan_sweep(Prob* probs, const Common& c, const tebd_mps& mps, 
 // (problem, slice) sums |A|^2 over its slice of rows (threads along the
 // columns) into part[slice].  With the FP32 products it also writes the
 // complex64 copy of A they read.
-__global__ __launch_bounds__(256) void k_frob(Prob* probs) {
-  __shared__ double red[4];
+// A wavefront takes a row at a time, eight pieces of 64 elements in flight:
+// there are 32 workgroups to a matrix only, so each has to keep its CU's
+// share of the memory busy (two 4900 x 4900: 1470 us with one load in flight
+// per thread, 263 us so).
+constexpr int kFrobThreads = 1024;
+
+__global__ __launch_bounds__(kFrobThreads) void k_frob(Prob* probs) {
+  __shared__ double red[kFrobThreads / 64];
   const int pi = blockIdx.x / kFrobSlices, sl = blockIdx.x - pi * kFrobSlices;
   Prob& P = probs[pi];
   if (P.l == 0) return;
   const int rs = (P.m + kFrobSlices - 1) / kFrobSlices;
   const int r0 = sl * rs, r1 = r0 + rs < P.m ? r0 + rs : P.m;
+  const int lane = threadIdx.x & 63;
+  constexpr int U = 8;
   double s = 0.0;
-  for (int r = r0; r < r1; ++r) {
+  for (int r = r0 + wave_id(); r < r1; r += kFrobThreads / 64) {
     const zt* row = P.A + size_t(r) * P.lda;
     float2* rowf = P.Af ? P.Af + size_t(r) * P.n : nullptr;
-    for (int c = threadIdx.x; c < P.n; c += 256) {
-      const zt v = row[c];
-      s += zabs2(v);
-      if (rowf) rowf[c] = make_float2(float(v.x), float(v.y));
+    for (int c0 = lane; c0 < P.n; c0 += 64 * U) {
+      zt v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + 64 * u;
+        v[u] = row[c < P.n ? c : P.n - 1];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + 64 * u;
+        if (c >= P.n) break;
+        s += zabs2(v[u]);
+        if (rowf) rowf[c] = make_float2(float(v[u].x), float(v[u].y));
+      }
     }
   }
-  s = block_sum<256>(s, red);
+  s = block_sum<kFrobThreads>(s, red);
   if (threadIdx.x == 0) P.part[sl] = s;
 }
 
 hipError_t launch_frob(Prob* probs, const Common& c, hipStream_t s) {
-  TEBD_LAUNCH("k_frob", k_frob, dim3(c.nprob * kFrobSlices), dim3(256), 0, s, probs);
+  TEBD_LAUNCH("k_frob", k_frob, dim3(c.nprob * kFrobSlices), dim3(kFrobThreads), 0, s,
+              probs);
   return hipGetLastError();
 }
 

@@ -240,13 +240,17 @@ inline size_t sched_bytes(int64_t nprob) { return size_t(TK_COUNT) * size_t(npro
 // `kind2`, when two queues share the launch): their tile total when the host
 // knows it, else the capacity-based c.grid; a multiple of 8 (the XCD-aware
 // tile mapping), at least 8, at most c.grid.
+// (of matrices whose sizes the host has: kKnownGridMax; the hardware then
+// hands the next tile to whichever CU is free first).
+constexpr int32_t kKnownGridMax = 16384;
 inline int32_t grid_for(const Common& c, int kind, int kind2 = -1) {
   int32_t t = c.ktiles[kind];
   if (kind2 >= 0) t = (t < 0 || c.ktiles[kind2] < 0) ? -1 : t + c.ktiles[kind2];
   if (t < 0) return c.grid;
   int32_t g = (t + 7) / 8 * 8;
   if (g < 8) g = 8;
-  return g < c.grid ? g : c.grid;
+  const int32_t most = c.tebd ? c.grid : kKnownGridMax;
+  return g < most ? g : most;
 }
 
 

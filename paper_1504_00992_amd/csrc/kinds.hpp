@@ -164,4 +164,11 @@ struct TileKinds<Prob> {
   }
 };
 
+// Tiles of an M x N output of one kind.
+template <int KIND>
+constexpr int64_t tiles_of(int64_t M, int64_t N) {
+  constexpr int TM = TileKinds<Prob>::tile_m(KIND), TN = TileKinds<Prob>::tile_n(KIND);
+  return ((M + TM - 1) / TM) * ((N + TN - 1) / TN);
+}
+
 }  // namespace tebd

@@ -111,8 +111,10 @@ __device__ void zgemm_tile(int M, int N, int K, int m0, int n0, const LA& la, co
                            ST& st, zt* smem) {
   zt* As = smem;
   zt* Bs = smem + Cfg::BK * Cfg::LDA;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = wave_id();
   const int wr = wave / Cfg::WGN, wc = wave % Cfg::WGN;
+  // a wavefront whose part of the tile is padding only copies
+  const bool live = m0 + wr * Cfg::WM < M && n0 + wc * Cfg::WN < N;
   v4d accr[Cfg::FM][Cfg::FN], acci[Cfg::FM][Cfg::FN];
 #pragma unroll
   for (int i = 0; i < Cfg::FM; ++i)
@@ -127,6 +129,7 @@ __device__ void zgemm_tile(int M, int N, int K, int m0, int n0, const LA& la, co
     zgemm_stage<Cfg, LA, LB>(As, Bs, ra, rb);
     __syncthreads();
     if (k0 + Cfg::BK < K) zgemm_load<Cfg>(M, N, K, m0, n0, k0 + Cfg::BK, la, lb, ra, rb);
+    if (live)
 #pragma unroll
     for (int kk = 0; kk < Cfg::BK; kk += 4) {
       const int ka = kk + (lane >> 4);
