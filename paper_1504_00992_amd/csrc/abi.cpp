@@ -408,16 +408,20 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   // iterations keep that rank and orthonormalise without pivoting
   // Every QR after the first is Gram-based: its columns are graded like the
   // singular values, and scaled to unit length they are well conditioned.
-  // The first one's are not; in the standalone call and the FP32-product
-  // sweeps it tries the Gram (which then keeps every column, as the pivoted
-  // QR would), and the pivoted Householder kernels take what that refuses.
+  // The first one's are not; in the standalone call it tries the Gram (which
+  // then keeps every column, as the pivoted QR would), and the pivoted
+  // Householder kernels take what that refuses.  In a sweep, whose bonds are
+  // rank deficient while they grow, only the sketches of QR class 3 do: there
+  // the attempt costs 80 us against 1900 us of Householder (128 x 74, global
+  // memory), in LDS 60 us against 160.
   // The last QR of the range finder has to be orthonormal to rounding, and so
   // has the basis that the Accuracy Check projects on.
   // (FP32 products keep to their own Gram-based QR, and to the Householder
   // kernels for what that does not take.)
   auto qr_step = [&](int which, bool first, bool last) -> hipError_t {
-    const int mode = (last ? QRM_STRICT : 0) | (first ? QRM_FIRST : 0);
-    const bool gram = c.mixed ? gram_f32_any(c, which) : !first || c.chol;
+    const int mode = (last ? QRM_STRICT : 0) | (first ? QRM_FIRST : 0) | (c.chol ? 0 : QRM_QUIET);
+    const bool gram = c.mixed ? gram_f32_any(c, which)
+                              : !first || c.chol || tebd_size_class(0, c.mmax, c.lmax) >= 3;
     if (gram) {
       const hipError_t er = timed(PK_QR, s, [&]() {
         return c.mixed ? launch_gram_f32(probs, c, which, s) : launch_gram_qr(probs, c, which, mode, s);

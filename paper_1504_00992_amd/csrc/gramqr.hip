@@ -555,7 +555,8 @@ __device__ __forceinline__ void gram_qr_problem(Prob& P, int which, int mode, in
   if (first) {
     if (tid == 0) {
       P.chol_ok = failed ? 0 : 1;
-      if (failed && qr_class(rows, P.l1) >= 2) P.flags |= TEBD_DEV_QR_FALLBACK;
+      if (failed && !(mode & QRM_QUIET) && qr_class(rows, P.l1) >= 2)
+        P.flags |= TEBD_DEV_QR_FALLBACK;
     }
     return;
   }

@@ -79,3 +79,29 @@ def test_refused_sketches_reach_the_householder_class_of_their_size(n, chi_max):
     large = _lib.tebd_size_class(0, n, chi_max + 10) >= 2
     assert bool(st[0] & _lib.DEV_QR_FALLBACK) == large
     rr._compare(mats, (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, 10, 2, 1e-10)
+
+
+@pytest.mark.parametrize("chi_m", [10, 100])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_first_sketch_of_a_large_bond(chi_m, mode):
+    # 200 x 110 (QR class 3): of rank 40 at most (the attempt is refused, the
+    # pivoted QR reveals the rank) and of full rank; a sweep reports neither
+    import torch
+    from oracle import philox, mps as omps
+    from paper_1504_00992_amd import api
+    assert _lib.tebd_size_class(0, 200, 110) == 3
+    dims, chis = [2, 2, 2, 2], [1, 100, chi_m, 100, 1]
+    gam, lam = tb._random_chain(dims, chis, 31)
+    gate = wl.random_unitary(4, wl.rng(3))
+    dev = api.DeviceMPS.from_host([(gam, lam)], dims, 100)
+    prm = api._lib.params(100, 10, 2, 1e-10, 1e-14, 1504, 5, 0, mode)
+    ws = api.BondWorkspace(dev, prm)
+    api.tebd_bond_update(dev, 0, 1, torch.from_numpy(gate).cuda(), prm, ws)
+    torch.cuda.synchronize()
+    ref = omps.MPS(gam, lam)
+    info = omps.bond_update(ref, 1, gate, 100, 1e-10, "rrsvd",
+                            philox.gaussian_omega(200, 110, 1504, 1, 5), 2)
+    g_gam, g_lam = dev.to_host(0)
+    assert len(g_lam[1]) == info["chi"]
+    assert np.max(np.abs(g_lam[1] - ref.lambdas[1])) < 1e-10
+    assert not int(ws.status.view(-1)[1 if ws.status.numel() > 1 else 0]) & _lib.DEV_QR_FALLBACK
