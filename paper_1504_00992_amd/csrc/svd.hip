@@ -17,37 +17,6 @@
 
 namespace tebd {
 
-// Column kernels over the strided rows r0, r0 + G, ... < rows, four rows per
-// iteration with independent partial sums, so that the LDS loads of four
-// rows are in flight together instead of one load latency per row.
-__device__ __forceinline__ zt col_dot(const zt* u, const zt* y, int r0, int rows, int G) {
-  double a0 = 0.0, b0 = 0.0, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0, a3 = 0.0, b3 = 0.0;
-  int r = r0;
-  for (; r + 3 * G < rows; r += 4 * G) {
-    const zt u0 = u[r], u1 = u[r + G], u2 = u[r + 2 * G], u3 = u[r + 3 * G];
-    const zt y0 = y[r], y1 = y[r + G], y2 = y[r + 2 * G], y3 = y[r + 3 * G];
-    zdot_acc(u0, y0, a0, b0);
-    zdot_acc(u1, y1, a1, b1);
-    zdot_acc(u2, y2, a2, b2);
-    zdot_acc(u3, y3, a3, b3);
-  }
-  for (; r < rows; r += G) zdot_acc(u[r], y[r], a0, b0);
-  return make_double2((a0 + a1) + (a2 + a3), (b0 + b1) + (b2 + b3));
-}
-
-__device__ __forceinline__ double col_norm2(const zt* y, int r0, int rows, int G) {
-  double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0;
-  int r = r0;
-  for (; r + 3 * G < rows; r += 4 * G) {
-    n0 += zabs2(y[r]);
-    n1 += zabs2(y[r + G]);
-    n2 += zabs2(y[r + 2 * G]);
-    n3 += zabs2(y[r + 3 * G]);
-  }
-  for (; r < rows; r += G) n0 += zabs2(y[r]);
-  return (n0 + n1) + (n2 + n3);
-}
-
 // --------------------------------------------------------------------------
 // Small SVD of B (l x n) from B^H = Q_B R_B: one-sided Jacobi on C = R_B^H
 // (l x l).  Column pairs are rotated in the round-robin order of the circle
@@ -312,154 +281,213 @@ __host__ __device__ __forceinline__ int svd_class(int l) {
   return 3;
 }
 
-// C and J in LDS, and all l/2 pairs of a round rotated at once by 16 lanes
-// each: lane h of a pair loads every 16th row of both columns of C and J into
-// registers, sums its part of g = c_p^H c_q, the group sum (DPP) combines
-// them, and the same lanes rotate the rows they hold and store them; one
-// barrier per round.  A round is bound by the instructions of a wavefront
-// (about five cycles each, a branch twenty), so the columns are padded with
-// zero rows to a multiple of 16 (an odd stride) and no row is tested: the
-// rotation keeps them zero.  Half of a round is LDS traffic: C and J are read
-// and written whole (2 x 52 KB at l = 34, 128 B a cycle).  Measured, one
-// problem of l = 34: 270 us with a test per row and the library's square root
-// and division, 240 us so.
+// One column's rows of C and J: lane h of n holds rows h + n i.
+template <int REGS>
+struct JacColumn {
+  zt c[REGS], j[REGS];
+};
+
+// All l/2 pairs of a round are rotated at once by 16 lanes each (a group), in
+// the odd-even order: the columns stand in a row of lp = l (+ 1) positions,
+// rounds rotate the pairs of positions (0 1)(2 3)... and (1 2)(3 4)... in
+// turn, and every pair changes places as it is rotated, so that after lp rounds
+// each two columns have met once and the row is reversed.
+// Group k keeps the columns at positions 2k and 2k + 1 in registers (lane h
+// rows h, h + 16, ... of C and J, zeros beyond l); only the column at 2k goes
+// to group k - 1 and back, through LDS, one transfer and one barrier a round.
+// A round is bound by the instructions of a wavefront (about five cycles
+// each, a branch twenty) and the LDS traffic: the rows per lane are a template
+// argument, and a pair that need not rotate has the rotation by zero.
+// Measured, one problem, l = 34 / l = 42: 240 / 229 us with every column of C
+// and J read from LDS and written back in each round (104 KB at l = 34), 141 /
+// 156 us so; rotation parameters without the branch around them 154 / 176 us;
+// J one round behind C, in the gaps of C's chain, 177 / 174 us.
+// Same rotation, tolerance, carried norms (recomputed in every sweep) and
+// sweep limit as jac_pair.
 constexpr int kPairGroup = 16;
-constexpr int kPairRowsLds0 = 2 * 32 * 33, kPairRowsLds1 = 2 * 64 * 65;  // elements of C and J
+
+// Rotation of columns (x, y) that change places: x becomes sn x + cs em y, y
+// becomes cs x - sn em y.  Bit 0 of the result: rotated, bit 1: by more than a
+// small turn.
+template <int RPR>
+__device__ __forceinline__ int pair_rotate(JacColumn<RPR>& x, JacColumn<RPR>& y, double tol,
+                                           double& na, double& nb) {
+  double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+  for (int i = 0; i < RPR; ++i) zdot_acc(x.c[i], y.c[i], g0, g1);
+  g0 = group_sum(g0, kPairGroup);
+  g1 = group_sum(g1, kPairGroup);
+  double ag, t, cs, sn;
+  zt em;
+  const bool on = jacobi_rotation(g0, g1, na, nb, tol, ag, t, cs, sn, em);
+  const double turn = on ? t * ag : 0.0;
+  cs = on ? cs : 1.0;
+  sn = on ? sn : 0.0;
+  em.x = on ? em.x : 1.0;
+  em.y = on ? em.y : 0.0;
+#pragma unroll
+  for (int i = 0; i < RPR; ++i) {
+    const zt u = x.c[i], v = zmul(em, y.c[i]), uj = x.j[i], vj = zmul(em, y.j[i]);
+    x.c[i] = zrot_hi(u, v, cs, sn);
+    y.c[i] = zrot_lo(u, v, cs, sn);
+    x.j[i] = zrot_hi(uj, vj, cs, sn);
+    y.j[i] = zrot_lo(uj, vj, cs, sn);
+  }
+  const int r = !on ? 0 : ag * ag > kSmallTurn * (na * nb) ? 3 : 1;
+  const double a = na;
+  na = nb + turn;
+  nb = fmax(a - turn, 0.0);
+  return r;
+}
+
+// LDS elements: the columns in transfer, or C for pairs_below_tol.
+constexpr int pair_lds(int groups, int rpr) {
+  return 2 * groups * (kPairGroup * rpr + 1);
+}
+
+template <int NT, int RPR>
+__device__ __forceinline__ void svd_pairs(Prob& P, int l, double eps, int tebd,
+                                          int32_t* retry_count, zt* lds, double* nrm,
+                                          double* sig_s, double* srt_s) {
+  constexpr int G = kPairGroup, RP = G * RPR, S = RP + 1;
+  const int tid = threadIdx.x, k = tid / G, h = tid & (G - 1);
+  const int np = (l + 1) / 2, lp = 2 * np;  // groups with columns, positions
+  const double tol = DBL_EPSILON * sqrt(double(l));
+  JacColumn<RPR> x, y;
+  auto load = [&](int c, JacColumn<RPR>& v) {
+    const int cc = c < l ? c : l - 1;
+#pragma unroll
+    for (int i = 0; i < RPR; ++i) {
+      const int r = h + G * i;
+      const zt a = P.Rb[size_t(r < l ? r : l - 1) * l + cc];
+      const bool in = r < l && c < l;
+      v.c[i] = make_double2(in ? a.x : 0.0, in ? -a.y : 0.0);
+      v.j[i] = make_double2(in && r == c ? 1.0 : 0.0, 0.0);
+    }
+  };
+  load(2 * k, x);
+  load(2 * k + 1, y);
+  // slot k: C and J of the column at position 2k, and its norm
+  auto put = [&](int slot, const JacColumn<RPR>& v, double n) {
+    zt* at = lds + slot * 2 * RP + h;
+#pragma unroll
+    for (int i = 0; i < RPR; ++i) {
+      at[G * i] = v.c[i];
+      at[RP + G * i] = v.j[i];
+    }
+    if (h == 0) nrm[slot] = n;
+  };
+  auto get = [&](int slot, JacColumn<RPR>& v) {
+    const zt* at = lds + slot * 2 * RP + h;
+#pragma unroll
+    for (int i = 0; i < RPR; ++i) {
+      v.c[i] = at[G * i];
+      v.j[i] = at[RP + G * i];
+    }
+    return nrm[slot];
+  };
+  auto norm2 = [&](const JacColumn<RPR>& v) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < RPR; ++i) s += zabs2(v.c[i]);
+    return group_sum(s, G);
+  };
+  const bool have = k < np, right = k + 1 < np, left = k > 0 && have;
+  bool converged = l == 1;
+  int sweep = 0;
+  for (; sweep < kMaxSweeps && !converged; ++sweep) {
+    double na = norm2(x), nb = norm2(y);
+    int bits = 0;
+    for (int round = 0; round < np; ++round) {
+      if (have) {
+        bits |= pair_rotate(x, y, tol, na, nb);
+        put(k, x, na);
+      }
+      __syncthreads();
+      if (right) {
+        JacColumn<RPR> z;
+        double nz = get(k + 1, z);
+        bits |= pair_rotate(y, z, tol, nb, nz);
+        put(k + 1, z, nz);
+      }
+      __syncthreads();
+      if (left) na = get(k, x);
+    }
+    const bool rotated = __syncthreads_or(bits & 1) != 0;
+    const bool turned_far = __syncthreads_or(bits & 2) != 0;
+    converged = !rotated;
+    if (rotated && !turned_far) {
+      // every pair at once, C by position (the empty one, if any, is first or
+      // last: it has no column in C below and above)
+      const int skip = lp > l && !(sweep & 1) ? 1 : 0;
+      na = norm2(x);
+      nb = norm2(y);
+      auto column = [&](int pos, const JacColumn<RPR>& v, double n) {
+        const int c = pos - skip;
+        if (c < 0 || c >= l) return;
+#pragma unroll
+        for (int i = 0; i < RPR; ++i) lds[c * S + h + G * i] = v.c[i];
+        if (h == 0) sig_s[c] = n;
+      };
+      if (have) {
+        column(2 * k, x, na);
+        column(2 * k + 1, y, nb);
+      }
+      __syncthreads();
+      converged = pairs_below_tol<NT>(lds, S, l, tol, sig_s);
+    }
+  }
+  if (!converged && tid == 0) P.flags |= TEBD_DEV_JACOBI_NOCONV;
+  // singular values, descending order, sorted outputs; the empty position is
+  // the last one after an even number of sweeps, the first one else
+  const int skip = lp > l && (sweep & 1) ? 1 : 0;
+  const int cx = have ? 2 * k - skip : -1, cy = have ? 2 * k + 1 - skip : -1;
+  const double sx = sqrt(norm2(x)), sy = sqrt(norm2(y));
+  __syncthreads();
+  if (h == 0 && cx >= 0 && cx < l) sig_s[cx] = sx;
+  if (h == 0 && cy >= 0 && cy < l) sig_s[cy] = sy;
+  __syncthreads();
+  auto out = [&](int c, double sv, const JacColumn<RPR>& v) {
+    if (c < 0 || c >= l) return;
+    int rank = 0;
+    for (int i = h; i < l; i += G) {
+      const double si = sig_s[i];
+      rank += (si > sv) || (si == sv && i < c);
+    }
+    rank = static_cast<int>(group_sum(double(rank), G));
+    const double inv = sv > 0.0 ? 1.0 / sv : 0.0;
+#pragma unroll
+    for (int i = 0; i < RPR; ++i) {
+      const int r = h + G * i;
+      if (r < l) {
+        P.X[size_t(rank) * l + r] = zscale(v.c[i], inv);
+        P.W[size_t(rank) * l + r] = v.j[i];
+      }
+    }
+    if (h == 0) {
+      srt_s[rank] = sv;
+      P.sig[rank] = sv;
+    }
+  };
+  out(cx, sx, x);
+  out(cy, sy, y);
+  truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return srt_s[c]; }, nrm);
+}
 
 template <int NT, int CLS>
 __global__ __launch_bounds__(NT) void k_svd_pairs(Prob* probs, double eps, int tebd,
                                                   int32_t* retry_count) {
-  extern __shared__ zt lds[];  // C, then J: l columns of stride S each
-  __shared__ double nrm[64];
-  __shared__ double sig_s[64];
+  extern __shared__ zt lds[];
+  __shared__ double nrm[64], sig_s[64];
   __shared__ double srt_s[64];  // singular values in descending order
-  __shared__ int perm_s[64];
   Prob& P = probs[blockIdx.x];
   const int l = P.l;
   if (l == 0 || svd_class(l) != CLS) return;
-  constexpr int G = kPairGroup;
-  constexpr int RPR = (CLS == 0 ? 32 : 64) / G;  // rows per lane, at most
-  static_assert(NT / (CLS == 0 ? 16 : 32) >= G, "pairs of a round fit at 16 lanes");
-  const int rp = (l + G - 1) & ~(G - 1);  // padded rows
-  const int S = rp | 1;
-  zt* Cs = lds;
-  zt* Js = lds + l * S;
-  const int tid = threadIdx.x;
-  const zt zero = make_double2(0.0, 0.0);  // value, never addressed
-  for (int c = tid / G; c < l; c += NT / G)
-    for (int r = tid & (G - 1); r < rp; r += G) {
-      const zt v = zload_if(r < l, P.Rb + size_t(r) * l + c);
-      Cs[c * S + r] = zconj(v);
-      Js[c * S + r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
-    }
-  const int lp = l + (l & 1);
-  const int k = tid / G, h = tid - k * G;
-  int lc2 = 1;
-  while (lc2 < l) lc2 <<= 1;
-  const int GN = NT / lc2 < G ? NT / lc2 : G;  // lanes per column
-  const int cn = tid / GN, hn = tid - cn * GN;
-  const double tol = DBL_EPSILON * sqrt(double(l));
-  bool converged = (l == 1);
-  __syncthreads();
-  for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
-    double s = 0.0;
-    if (cn < l) s = col_norm2(Cs + cn * S, hn, l, GN);
-    s = group_sum(s, GN);
-    if (cn < l && hn == 0) nrm[cn] = s;
-    __syncthreads();
-    int any = 0, large = 0;
-    for (int round = 0; round < lp - 1; ++round) {
-      const int a = circle_player(k, round, lp), b = circle_player(lp - 1 - k, round, lp);
-      const int p = a < b ? a : b, q = a < b ? b : a;
-      if (k < lp / 2 && q < l) {
-        zt x[RPR], y[RPR], xj[RPR], yj[RPR];
-        zt* cp = Cs + p * S + h;
-        zt* cq = Cs + q * S + h;
-        zt* jp = Js + p * S + h;
-        zt* jq = Js + q * S + h;
-        const double app = nrm[p], aqq = nrm[q];
-        double g0 = 0.0, g1 = 0.0;
-#pragma unroll
-        for (int i = 0; i < RPR; ++i) {
-          if (G * i >= l) break;  // uniform
-          x[i] = cp[G * i];
-          y[i] = cq[G * i];
-          xj[i] = jp[G * i];
-          yj[i] = jq[G * i];
-        }
-#pragma unroll
-        for (int i = 0; i < RPR; ++i) {
-          if (G * i >= l) break;
-          zdot_acc(x[i], y[i], g0, g1);
-        }
-        const double gr = group_sum(g0, G), gi = group_sum(g1, G);
-        double ag, t, cs, sn;
-        zt em;  // e^{-i phi}
-        if (jacobi_rotation(gr, gi, app, aqq, tol, ag, t, cs, sn, em)) {
-#pragma unroll
-          for (int i = 0; i < RPR; ++i) {
-            if (G * i >= l) break;
-            const zt ey = zmul(em, y[i]), eyj = zmul(em, yj[i]);
-            cp[G * i] = zrot_lo(x[i], ey, cs, sn);
-            cq[G * i] = zrot_hi(x[i], ey, cs, sn);
-            jp[G * i] = zrot_lo(xj[i], eyj, cs, sn);
-            jq[G * i] = zrot_hi(xj[i], eyj, cs, sn);
-          }
-          if (h == 0) {
-            nrm[p] = fmax(app - t * ag, 0.0);
-            nrm[q] = aqq + t * ag;
-          }
-          any = 1;
-          if (ag * ag > kSmallTurn * (app * aqq)) large = 1;
-        }
-      }
-      __syncthreads();
-    }
-    const bool rotated = __syncthreads_or(any) != 0;
-    const bool turned_far = __syncthreads_or(large) != 0;
-    converged = !rotated;
-    if (rotated && !turned_far) {
-      double s2 = 0.0;
-      if (cn < l) s2 = col_norm2(Cs + cn * S, hn, l, GN);
-      s2 = group_sum(s2, GN);
-      if (cn < l && hn == 0) nrm[cn] = s2;
-      __syncthreads();
-      converged = pairs_below_tol<NT>(Cs, S, l, tol, nrm);
-    }
-  }
-  if (!converged && tid == 0) P.flags |= TEBD_DEV_JACOBI_NOCONV;
-  // singular values, descending order, sorted outputs
-  {
-    double s = 0.0;
-    if (cn < l) s = col_norm2(Cs + cn * S, hn, l, GN);
-    s = group_sum(s, GN);
-    if (cn < l && hn == 0) sig_s[cn] = sqrt(s);
-  }
-  __syncthreads();
-  if (tid < l) {
-    const double sj = sig_s[tid];
-    int rank = 0;
-    for (int i = 0; i < l; ++i) {
-      const double si = sig_s[i];
-      rank += (si > sj) || (si == sj && i < tid);
-    }
-    perm_s[rank] = tid;
-  }
-  __syncthreads();
-  for (int e = tid; e < l * l; e += NT) {
-    const int c = e / l, r = e - c * l;
-    const int src = perm_s[c];
-    const double sv = sig_s[src];
-    const zt x = Cs[src * S + r];
-    P.X[e] = sv > 0.0 ? zscale(x, 1.0 / sv) : zero;
-    P.W[e] = Js[src * S + r];
-  }
-  if (tid < l) {
-    const double v = sig_s[perm_s[tid]];
-    srt_s[tid] = v;
-    P.sig[tid] = v;
-  }
-  truncate_tail<NT>(P, l, eps, tebd, retry_count, [&](int c) { return srt_s[c]; }, nrm);
+  static_assert(NT / kPairGroup == (CLS == 0 ? 16 : 32), "a group for every two columns");
+  if (l <= (CLS == 0 ? 16 : 48))
+    svd_pairs<NT, (CLS == 0 ? 1 : 3)>(P, l, eps, tebd, retry_count, lds, nrm, sig_s, srt_s);
+  else
+    svd_pairs<NT, (CLS == 0 ? 2 : 4)>(P, l, eps, tebd, retry_count, lds, nrm, sig_s, srt_s);
 }
 
 // --------------------------------------------------------------------------
@@ -534,12 +562,6 @@ __global__ __launch_bounds__(1024) void k_jac_list(Prob* probs, int nprob, int32
   }
 }
 constexpr int kJacCountMask = (1 << 22) - 1;
-
-// One column's rows of C and J: lane h holds rows h + 64 i.
-template <int REGS>
-struct JacColumn {
-  zt c[REGS], j[REGS];
-};
 
 template <int REGS>
 __device__ __forceinline__ double jac_norm2(const JacColumn<REGS>& x) {
@@ -883,7 +905,7 @@ hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
       size_t elems;
     } lds[] = {{reinterpret_cast<const void*>(&k_small_svd<2, 2>), size_t(8 * kJacBlock * 128)},
                {reinterpret_cast<const void*>(&k_small_svd<4, 1>), size_t(4 * kJacBlock * 256)},
-               {reinterpret_cast<const void*>(&k_svd_pairs<512, 1>), size_t(kPairRowsLds1)},
+               {reinterpret_cast<const void*>(&k_svd_pairs<512, 1>), size_t(pair_lds(32, 4))},
                {reinterpret_cast<const void*>(&k_jac_round<2>), size_t(4 * kJacBlock * 128)},
                {reinterpret_cast<const void*>(&k_jac_round<4>), size_t(4 * kJacBlock * 256)}};
     for (const auto& f : lds) {
@@ -902,11 +924,11 @@ hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
   if (c.wide_n == 0 && hi > 1) hi = 1;
   auto pairs0 = [&](hipStream_t t) {
     TEBD_LAUNCH("k_svd_pairs<256, 0>", (k_svd_pairs<256, 0>), dim3(c.nprob), dim3(256),
-                kPairRowsLds0 * sizeof(zt), t, probs, c.eps, c.tebd, retry);
+                pair_lds(16, 2) * sizeof(zt), t, probs, c.eps, c.tebd, retry);
   };
   auto pairs1 = [&](hipStream_t t) {
     TEBD_LAUNCH("k_svd_pairs<512, 1>", (k_svd_pairs<512, 1>), dim3(c.nprob), dim3(512),
-                kPairRowsLds1 * sizeof(zt), t, probs, c.eps, c.tebd, retry);
+                pair_lds(32, 4) * sizeof(zt), t, probs, c.eps, c.tebd, retry);
   };
   auto wider = [&](hipStream_t t) {
     if (wide) launch_jacobi_rounds(probs, jac_list(c), c.nprob, c.wide_n, c.wide_l, t);
