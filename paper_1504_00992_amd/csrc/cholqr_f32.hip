@@ -27,22 +27,59 @@ constexpr int kCholLdsL = 96;  // Gram in LDS up to this width (147 KiB), else i
 
 using CfgGram = ZCfg<kSketchTileM, kSketchTileN, 16, 2, 2>;
 
-// G = Y^H Y into C (l x l column-major): the tiles that meet the lower
-// triangle, all that the factorisation reads.  In the second pass only the
+// G = Y^H Y into C (l x l column-major), the 16 x 16 tiles of the lower
+// triangle, all that the factorisation reads: a wavefront each, operands
+// straight from memory kAhead slabs of 16 rows ahead (a 32 x 32 tile takes
+// four of the queue's wavefronts).  The sums run over the rows in order, four to a
+// matrix-core step, as in zgemm_tile.  Eight 1024 x 74 sketches: 108 us
+// through LDS with a barrier per slab, 96 us so (columns 16 KB apart share a
+// cache channel; 26 us of it is matrix-core time).  In the second pass only the
 // problems whose first pass succeeded take part.
+constexpr int kAhead = 4;
+
 template <int WHICH>
 __global__ __launch_bounds__(256) void k_gram_f32(Prob* probs, const int32_t* offs, int nprob,
                                                   int tebd, int pass) {
-  __shared__ zt smem[CfgGram::lds_elems];
+  const int lane = threadIdx.x & 63, ti = lane & 15, tk = lane >> 4, w = wave_id();
   for_each_tile<TK_GRAM>(probs, offs, nprob, tebd, [&](Prob& P, int, int, int m0, int n0, int) {
     if (!(P.chol & (WHICH ? kGramF32N : kGramF32M)) || (pass && !P.chol_ok)) return;
-    if (n0 > m0) return;
-    const int rows = WHICH ? P.n : P.m;
-    const zt* Yc = WHICH ? P.Yt : P.Y;
-    LdAdjColA la{Yc, rows};
-    LdColB lb{Yc, rows};
-    StCol st{P.C, P.l};
-    zgemm_tile<CfgGram>(P.l, P.l, rows, m0, n0, la, lb, st, smem);
+    const int rows = WHICH ? P.n : P.m, l = P.l;
+    const int r0 = m0 + (w >> 1) * 16, c0 = n0 + (w & 1) * 16;
+    if (c0 > r0 || r0 >= l) return;
+    const zt* Y = WHICH ? P.Yt : P.Y;
+    const zt* pa = Y + size_t(r0 + ti < l ? r0 + ti : l - 1) * rows;
+    const zt* pb = Y + size_t(c0 + ti < l ? c0 + ti : l - 1) * rows;
+    auto load = [&](int k0, zt (&a)[4], zt (&b)[4]) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = k0 + 4 * s + tk, kc = k < rows ? k : rows - 1;
+        a[s] = pa[kc];
+        b[s] = pb[kc];
+        if (k >= rows) a[s] = b[s] = make_double2(0.0, 0.0);
+      }
+    };
+    v4d re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+    zt a[kAhead][4], b[kAhead][4];
+#pragma unroll
+    for (int p = 0; p < kAhead; ++p) load(16 * p, a[p], b[p]);
+    for (int k0 = 0; k0 < rows; k0 += 16 * kAhead) {
+#pragma unroll
+      for (int p = 0; p < kAhead; ++p) {  // (slabs beyond the rows are zeros)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {  // conj(a) b
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(a[p][s].x, b[p][s].x, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[p][s].x, b[p][s].y, im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(a[p][s].y, b[p][s].y, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[p][s].y, b[p][s].x, im, 0, 0, 0);
+        }
+        load(k0 + 16 * (p + kAhead), a[p], b[p]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = r0 + tk + 4 * r, col = c0 + ti;
+      if (row < l && col < l) P.C[row + size_t(col) * l] = make_double2(re[r], im[r]);
+    }
   });
 }
 
@@ -63,9 +100,136 @@ __global__ __launch_bounds__(256) void k_qapply_f32(Prob* probs, const int32_t* 
 }
 
 // Cholesky G = L L^H of the Gram in C (column-major l x l, lower triangle
-// used), then X = R^-1 = (L^-1)^H, upper triangular, into J: column c of
-// L^-1 by forward substitution, one wavefront per column, the column held
-// across the lanes (lane t keeps rows t, t + 64, ...).
+// used), then X = R^-1 = (L^-1)^H, upper triangular, into J.
+//
+// Up to kCholLdsL columns: the Gram in registers, element (i, k) with thread
+// (i mod 32, k mod 32), the scaled column of a step broadcast through LDS (one
+// barrier a step); L goes to LDS by rows for the inverse.  There column c of
+// L^-1 by forward substitution, four columns per wavefront, 16 lanes each: the
+// sum of row i adds 64 products in a binary tree over the columns k mod 64
+// (lane u holds k = 4u ... 4u + 3), so LDS holds a row with those four 16
+// apart, and no read conflicts.  l = 74, eight problems: 250 us column by
+// column in LDS and with a wavefront per column, 84 us so.
+__device__ __forceinline__ int chol_slot(int k) {  // place of column k in a row
+  const int u = (k >> 2) & 15, m = k & 3;
+  return k < 64 ? 16 * m + u : 64 + 8 * m + u;
+}
+__device__ __forceinline__ int chol_ld(int l) { return l > 64 ? 97 : 65; }
+static_assert(kCholLdsL <= 96, "chol_slot: two blocks of 64 and 32 columns");
+
+struct CholShared {
+  zt L[kCholLdsL * (kCholLdsL + 1)];
+  zt col[2][kCholLdsL];
+  double diag[kCholLdsL];
+};
+
+// False when a pivot is refused (uniform).
+__device__ __forceinline__ bool chol_factor(const zt* G, int l, double dmax, CholShared& sh,
+                                            int* fail_s) {
+  constexpr int NB = kCholLdsL / 32;
+  const int tid = threadIdx.x, ti = tid & 31, tk = tid >> 5, ld = chol_ld(l);
+  zt g[NB][NB];
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b) {
+      const int i = ti + 32 * a, k = tk + 32 * b;
+      g[a][b] = zload_if(i < l && k <= i, G + i + size_t(k) * l);
+    }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    for (int jt = 0; jt < 32; ++jt) {
+      const int j = 32 * b + jt;
+      if (j >= l) break;
+      zt* col = sh.col[j & 1];
+      if (tk == jt) {  // the half wavefront that holds column j
+        const double d = __shfl(g[b][b].x, (tid & 32) | jt, 64);
+        if (!(d > kCholTol * dmax) || !isfinite(d)) {
+          *fail_s = 1;
+        } else {
+          const double root = sqrt(d), inv = 1.0 / root;
+          if (ti == jt) sh.diag[j] = root;
+#pragma unroll
+          for (int a = b; a < NB; ++a) {
+            const int i = ti + 32 * a;
+            if (i > j && i < l) {
+              const zt v = zscale(g[a][b], inv);
+              col[i] = v;
+              sh.L[i * ld + chol_slot(j)] = v;
+            }
+          }
+        }
+      }
+      __syncthreads();
+      if (*fail_s) return false;
+#pragma unroll
+      for (int c = b; c < NB; ++c) {  // rows and columns beyond j (the others are done with)
+        const zt lkj = col[tk + 32 * c];
+#pragma unroll
+        for (int a = c; a < NB; ++a) {
+          const zt lij = col[ti + 32 * a];
+          g[a][c] = zsub(g[a][c], zmul(lij, zconj(lkj)));
+        }
+      }
+    }
+  }
+  __syncthreads();
+  return true;
+}
+
+__device__ __forceinline__ void chol_inverse(zt* X, int l, const CholShared& sh) {
+  const int lane = threadIdx.x & 63, u = lane & 15, ld = chol_ld(l);
+  for (int c0 = 4 * wave_id(); c0 < l; c0 += 64) {
+    const int c = c0 + (lane >> 4);
+    zt x[2][4];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) x[q][m] = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int qi = 0; qi < 2; ++qi) {
+      const int from = c0 > 64 * qi ? (c0 - 64 * qi) >> 2 : 0;
+      for (int v = from; v < 16 && 64 * qi + 4 * v < l; ++v) {
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi) {
+          const int i = 64 * qi + 4 * v + mi;
+          if (i >= l) break;
+          const zt* row = sh.L + i * ld + u;
+          double sr[4], si[4];
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            sr[m] = 0.0;
+            si[m] = 0.0;
+#pragma unroll
+            for (int q = 0; q <= qi; ++q) {
+              const int k = 64 * q + 4 * u + m;
+              zt lik = row[q == 0 ? 16 * m : 64 + 8 * m];
+              if (k >= i) lik = make_double2(0.0, 0.0);
+              sr[m] += lik.x * x[q][m].x - lik.y * x[q][m].y;
+              si[m] += lik.x * x[q][m].y + lik.y * x[q][m].x;
+            }
+          }
+          const double tr = group_sum((sr[0] + sr[1]) + (sr[2] + sr[3]), 16);
+          const double ts = group_sum((si[0] + si[1]) + (si[2] + si[3]), 16);
+          const double lii = sh.diag[i];
+          const zt xi = i == c ? make_double2(1.0 / lii, 0.0) : make_double2(-tr / lii, -ts / lii);
+          if (u == v && i >= c) x[qi][mi] = xi;
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int i = 64 * q + 4 * u + m;
+        if (i < l && c < l)
+          X[c + size_t(i) * l] = i >= c ? zconj(x[q][m]) : make_double2(0.0, 0.0);
+      }
+  }
+}
+
+// Wider ones work on the Gram in global memory, a wavefront per column of the
+// inverse (lane t keeps rows t, t + 64, ...).
 template <int WHICH>
 __global__ __launch_bounds__(1024) void k_chol_f32(Prob* probs, int pass) {
   Prob& P = probs[blockIdx.x];
@@ -75,21 +239,32 @@ __global__ __launch_bounds__(1024) void k_chol_f32(Prob* probs, int pass) {
     if (tid == 0 && pass == 0) P.chol_ok = 0;
     return;
   }
-  __shared__ zt g_lds[kCholLdsL * kCholLdsL];
+  __shared__ CholShared sh;
   __shared__ double dmax_s;
   __shared__ int fail_s;
   const bool in_lds = l <= kCholLdsL;
-  zt* G = in_lds ? g_lds : P.C;
-  if (in_lds)
-    for (int e = tid; e < l * l; e += 1024) g_lds[e] = P.C[e];
-  __syncthreads();
-  if (tid == 0) {
+  zt* G = P.C;
+  if (wave == 0) {
     double dm = 0.0;
-    for (int j = 0; j < l; ++j) dm = fmax(dm, G[j + size_t(j) * l].x);
-    dmax_s = dm;
-    fail_s = !(dm > 0.0) || !isfinite(dm);
+    for (int j = lane; j < l; j += 64) {
+      const double d = G[j + size_t(j) * l].x;
+      dm = fmax(dm, d);
+    }
+    dm = wave_max(dm);
+    if (lane == 0) {
+      dmax_s = dm;
+      fail_s = !(dm > 0.0) || !isfinite(dm);
+    }
   }
   __syncthreads();
+  if (in_lds && !fail_s) {
+    if (chol_factor(G, l, dmax_s, sh, &fail_s)) chol_inverse(P.J, l, sh);
+    __syncthreads();
+    if (!fail_s) {
+      if (tid == 0) P.chol_ok = 1;
+      return;
+    }
+  }
   for (int j = 0; j < l && !fail_s; ++j) {
     if (tid == 0) {
       const double d = G[j + size_t(j) * l].x;

@@ -105,3 +105,26 @@ def test_first_sketch_of_a_large_bond(chi_m, mode):
     assert len(g_lam[1]) == info["chi"]
     assert np.max(np.abs(g_lam[1] - ref.lambdas[1])) < 1e-10
     assert not int(ws.status.view(-1)[1 if ws.status.numel() > 1 else 0]) & _lib.DEV_QR_FALLBACK
+
+
+@pytest.mark.parametrize("m,n,chi_max", [(300, 280, 50), (260, 255, 54), (250, 255, 55), (300, 300, 71),
+                                         (300, 310, 86), (320, 300, 87), (260, 270, 118)])
+def test_widths_of_the_fp32_product_path(m, n, chi_max):
+    # l = 60, 64, 65, 81, 96, 97, 128: the factor in registers and LDS, and beyond;
+    # the bound stated for FP32 products (1e-5 of s_1)
+    import torch
+    from paper_1504_00992_amd import api
+    gen = wl.rng(m + n)
+    a = wl.known_spectrum(m, n, np.exp(-np.arange(min(m, n)) / 25.0), gen)
+    U, S, VH, chi, w, st = api.rrsvd_truncate([torch.from_numpy(a).cuda()], chi_max, 10, 2, 1e-10,
+                                              1504, 0, precision=1)
+    torch.cuda.synchronize()
+    ou, os_, ovh, ochi, ow, ost = rr._oracle(a, 0, chi_max, 10, 2, 1e-10)
+    c = int(chi[0])
+    assert c == ochi and not int(st[0]) & _lib.DEV_QR_FALLBACK
+    s = S[0].cpu().numpy()[:c]
+    u, vh = U[0].cpu().numpy()[:, :c], VH[0].cpu().numpy()[:c]
+    assert np.max(np.abs(s - os_)) <= 1e-5 * os_[0]
+    assert np.max(np.abs((u * s) @ vh - (ou * os_) @ ovh)) <= 1e-5 * os_[0]
+    assert np.allclose(u.conj().T @ u, np.eye(c), atol=1e-12)
+    assert np.allclose(vh @ vh.conj().T, np.eye(c), atol=1e-12)
