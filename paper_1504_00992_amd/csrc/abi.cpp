@@ -411,9 +411,11 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   // The first one's are not; in the standalone call it tries the Gram (which
   // then keeps every column, as the pivoted QR would), and the pivoted
   // Householder kernels take what that refuses.  In a sweep, whose bonds are
-  // rank deficient while they grow, only the sketches of QR class 3 do: there
-  // the attempt costs 80 us against 1900 us of Householder (128 x 74, global
-  // memory), in LDS 60 us against 160.
+  // rank deficient while they grow, it does for the bonds at capacity and the
+  // sketches of QR class 3 (plan_item): an attempt costs 27 us against 84 us of
+  // Householder (64 x 42), 60 against 160 (LDS), 80 against 1900 (128 x 74,
+  // global memory).  The launch is left out where the host knows that there
+  // is none.
   // The last QR of the range finder has to be orthonormal to rounding, and so
   // has the basis that the Accuracy Check projects on.
   // (FP32 products keep to their own Gram-based QR, and to the Householder
@@ -421,7 +423,7 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   auto qr_step = [&](int which, bool first, bool last) -> hipError_t {
     const int mode = (last ? QRM_STRICT : 0) | (first ? QRM_FIRST : 0) | (c.chol ? 0 : QRM_QUIET);
     const bool gram = c.mixed ? gram_f32_any(c, which)
-                              : !first || c.chol || tebd_size_class(0, c.mmax, c.lmax) >= 3;
+                              : !first || c.chol || c.ktiles[TK_GQ_F] != 0;
     if (gram) {
       const hipError_t er = timed(PK_QR, s, [&]() {
         return c.mixed ? launch_gram_f32(probs, c, which, s) : launch_gram_qr(probs, c, which, mode, s);
@@ -552,9 +554,9 @@ tebd_status enqueue_sweep(const tebd_mps* mps, const tebd_z* gates, int64_t gate
   // thread, with a quarter of headroom: any grid covers every tile (the
   // launches are persistent), so the estimate only affects speed.
   static thread_local int32_t last_tiles[2][TK_COUNT] = {
-      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1},
-      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1}};
-  static_assert(TK_COUNT == 18, "one -1 per tile kind above");
+      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1},
+      {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1}};
+  static_assert(TK_COUNT == 19, "one -1 per tile kind above");
   if (c.adaptive == 3) {
     c.acc_count = c.retry_count + kAccCountSlot;
     c.acc_lcap = int32_t(pl.lcap);
@@ -609,8 +611,10 @@ tebd_status enqueue_sweep(const tebd_mps* mps, const tebd_z* gates, int64_t gate
 // Static scratch of rrsvd_truncate_noalloc, one copy per device (the code
 // object's global), used through the address hipGetSymbolAddress gives on
 // each device: the array's name is not a device address in host code.
-constexpr size_t kScratchBytes = size_t(64) << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// 64 MiB and, outside that count, 32 bytes of each descriptor and its queue
+// entries (batches that filled the scratch when those were smaller still fit).
+constexpr size_t kScratchBytes = size_t(64) << 20, kScratchSpare = size_t(1) << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSpare];
 
 constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
@@ -741,14 +745,14 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
   st = tebd_workspace_size(nullptr, batch, m, n, prm, &need);
   if (st != TEBD_OK) return st;
   if (noalloc) {
-    if (need > kScratchBytes)
+    if (need > kScratchBytes + std::min(kScratchSpare, size_t(batch) * 32))
       return fail(TEBD_ERR_WORKSPACE,
                   "the batch needs %zu bytes of scratch; rrsvd_truncate_noalloc has %zu "
                   "(use rrsvd_truncate with a workspace)", need, kScratchBytes);
     hipError_t e = scratch_address(&workspace);
     if (e != hipSuccess)
       return fail(TEBD_ERR_DEVICE, "static scratch address: %s", hipGetErrorString(e));
-    ws_bytes = kScratchBytes;
+    ws_bytes = kScratchBytes + kScratchSpare;
   }
   if (!workspace) return fail(TEBD_ERR_WORKSPACE, "argument 16 (workspace) is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
@@ -797,13 +801,12 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
   int64_t tiles = 0, known[TK_COUNT] = {};
   // the largest matrices first: their tiles and workgroups take longest, and
   // the small ones then fill the end of a launch
-  std::vector<int64_t> order(static_cast<size_t>(batch));
-  for (int64_t b = 0; b < batch; ++b) order[size_t(b)] = b;
-  if (!noalloc)
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int64_t x, int64_t y) { return m[x] * n[x] > m[y] * n[y]; });
+  std::vector<int64_t> order(noalloc ? 0 : size_t(batch));
+  for (size_t i = 0; i < order.size(); ++i) order[i] = int64_t(i);
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int64_t x, int64_t y) { return m[x] * n[x] > m[y] * n[y]; });
   for (int64_t at = 0; at < batch; ++at) {
-    const int64_t b = order[size_t(at)];
+    const int64_t b = noalloc ? at : order[size_t(at)];
     {
       // the tiles of the products, so that their launches have a workgroup each
       const int64_t l = sketch_l(prm->chi_max, prm->p, m[b], n[b]);

@@ -102,7 +102,7 @@ struct Prob {
   int32_t tape_ldu, tape_ldvh;
 };
 
-constexpr int TK_COUNT_MAX = 18;  // tile kinds of the forward pipeline (enum below)
+constexpr int TK_COUNT_MAX = 19;  // tile kinds of the forward pipeline (enum below)
 
 // Parameters of a launch sequence that are common to all problems.
 struct Common {
@@ -126,7 +126,7 @@ struct Common {
   int32_t* bounds_dev = nullptr;  // host-mapped pinned memory: k_schedule writes {min, max}
                                   // of m, n, l1 there, then the tile total of every kind
   int32_t ktiles[TK_COUNT_MAX] = {-1, -1, -1, -1, -1, -1, -1, -1, -1,
-                                  -1, -1, -1, -1, -1, -1, -1, -1, -1};  // host copy of the totals (-1: unknown)
+                                  -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};  // host copy of the totals (-1: unknown)
   int32_t* offs;     // device: per tile kind, exclusive prefix sums of tile counts [nprob + 1]
   int32_t grid;      // workgroups of the persistent contraction launches (multiple of 8)
   // TEBD sweeps: the capacity sizes (d_max chi_cap rows, the fixed-rank sketch
@@ -198,7 +198,8 @@ enum {
   TK_SKN_S = 15, // TK_SKN on 16 x 16 tiles
   TK_GQ_L = 16,  // Gram-based QR: one item per problem of a workgroup
   TK_GQ_S = 17,  // Gram-based QR: one item per problem of a wavefront
-  TK_COUNT = 18
+  TK_GQ_F = 18,  // one item per problem whose first QR tries the Gram
+  TK_COUNT = 19
 };
 
 static_assert(TK_COUNT == TK_COUNT_MAX, "Common::ktiles holds one total per kind");

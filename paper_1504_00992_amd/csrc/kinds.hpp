@@ -133,6 +133,9 @@ struct TileKinds<Prob> {
       case TK_GQ_S:
         M = N = gram_small(P.m, P.n, P.l1) ? 1 : 0;
         break;
+      case TK_GQ_F:
+        M = N = P.chol & kGramFirst ? 1 : 0;
+        break;
       case TK_QAPM:  // strips of 64 rows; FP32 products: a 64 x 64 tile here is a 32 x 32 one
         if (P.chol & kGramF32M) {
           M = 2 * P.m;

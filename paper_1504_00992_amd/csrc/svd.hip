@@ -7,7 +7,6 @@
 // discarded weight of Sec. II.C, Eq. (defdiscweigt), evaluated with the
 // Frobenius identity of Sec. IV.
 #include <cfloat>
-#include <functional>
 #include <type_traits>
 
 #include "householder.hpp"
@@ -940,11 +939,22 @@ hipError_t launch_small_svd(Prob* probs, const Common& c, hipStream_t s) {
     else
       TEBD_LAUNCH("k_small_svd<4, 1>", (k_small_svd<4, 1>), dim3(c.nprob), dim3(kJacThreads), lds, t, probs, c.eps, c.tebd, retry, first);
   };
-  const std::function<void(hipStream_t)> fns[3] = {pairs0, pairs1, wider};
-  std::function<void(hipStream_t)> items[3];
+  auto run = [&](int k, hipStream_t t) {
+    if (k == 0)
+      pairs0(t);
+    else if (k == 1)
+      pairs1(t);
+    else
+      wider(t);
+  };
+  struct Item {
+    const decltype(run)* fn;
+    int k;
+    void operator()(hipStream_t t) const { (*fn)(k, t); }
+  };
+  Item items[3];
   int n = 0;
-  for (int k = lo; k <= hi && k < 2; ++k) items[n++] = fns[k];
-  if (hi >= 2) items[n++] = fns[2];
+  for (int k = lo < 2 ? lo : 2; k <= (hi < 2 ? hi : 2); ++k) items[n++] = {&run, k};
   return fork_join(s, items, n, c);
 }
 
