@@ -16,6 +16,7 @@
 #include "householder.hpp"
 #include "sidestreams.hpp"
 #include "kinds.hpp"
+#include "zgemm.hpp"
 
 namespace tebd {
 
@@ -796,6 +797,9 @@ hipError_t launch_qr(Prob* probs, const Common& c, int which, int want_r, int pi
 // TEBD_DEV_ACC_CAPPED.  The check goes on while MAX > tol and l <= n - r;
 // problems still probing are counted in count[round & 1] for the host, and
 // count[(round + 1) & 1] is cleared for the next round.
+// Both products are a tile wide (r <= 16) and run on the matrix cores, a tile
+// per wavefront straight from memory: 22.7 us a round with a wavefront per
+// column and a thread per row (a sweep of 4 x 40 spin-boson sites), 6.9 us so.
 __global__ __launch_bounds__(256) void k_acc_resid(Prob* probs, double eps, int32_t* count,
                                                    int round) {
   Prob& P = probs[blockIdx.x];
@@ -806,54 +810,81 @@ __global__ __launch_bounds__(256) void k_acc_resid(Prob* probs, double eps, int3
     if (tid == 0) P.ac_grow = 0;
     return;
   }
-  const int m = P.m;
+  const int m = P.m, ti = lane & 15, tk = lane >> 4;
   const zt* Q = P.Y;
   const zt* B = P.Y + size_t(l) * m;
   __shared__ zt cs[kMaxL * kAccMaxR];  // C = Q^H B, l x r, column j of Q in row j
-  __shared__ double part[4][kAccMaxR];
-  // one wavefront per column of Q, its lanes over the rows
-  for (int j = wave; j < l; j += 4) {
-    double cr[kAccMaxR], ci[kAccMaxR];
+  __shared__ double part[4][kAccMaxR], frob_s[64];
+  static_assert(kAccMaxR <= 16, "the probes are one tile wide");
+  const int npart = gate_partials(P.dl * P.dr, P.gcol0, P.chi_l * P.chi_r);
+  if (wave == 3 && lane < npart) frob_s[lane] = P.part[lane];
+  const zt zero = make_double2(0.0, 0.0);
+  const zt* bi = B + size_t(ti < r ? ti : r - 1) * m;
+  // one wavefront per 16 columns of Q
+  for (int j0 = 16 * wave; j0 < l; j0 += 64) {
+    const zt* qj = Q + size_t(j0 + ti < l ? j0 + ti : l - 1) * m;
+    v4d re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < m; k0 += 16) {
+      zt u[4], v[4];
 #pragma unroll
-    for (int i = 0; i < kAccMaxR; ++i) cr[i] = ci[i] = 0.0;
-    const zt* qj = Q + size_t(j) * m;
-    for (int row = lane; row < m; row += 64) {
-      const zt q = qj[row];
+      for (int t = 0; t < 4; ++t) {
+        const int k = k0 + 4 * t + tk, kc = k < m ? k : m - 1;
+        u[t] = qj[kc];
+        v[t] = bi[kc];
+        if (k >= m) u[t] = v[t] = zero;
+      }
 #pragma unroll
-      for (int i = 0; i < kAccMaxR; ++i)
-        if (i < r) zdot_acc(q, B[size_t(i) * m + row], cr[i], ci[i]);
+      for (int t = 0; t < 4; ++t) {  // conj(u) v
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[t].x, v[t].x, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(u[t].x, v[t].y, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[t].y, v[t].y, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(-u[t].y, v[t].x, im, 0, 0, 0);
+      }
     }
 #pragma unroll
-    for (int i = 0; i < kAccMaxR; ++i) {
-      if (i >= r) break;  // uniform
-      const double xr = wave_sum(cr[i]), xi = wave_sum(ci[i]);
-      if (lane == 0) cs[j * kAccMaxR + i] = make_double2(xr, xi);
+    for (int q = 0; q < 4; ++q) {
+      const int j = j0 + tk + 4 * q;
+      if (j < l && ti < r) cs[j * kAccMaxR + ti] = make_double2(re[q], im[q]);
     }
   }
   __syncthreads();
-  double nrm[kAccMaxR];
+  // 16 rows of D = B - Q C per wavefront
+  double nrm = 0.0;  // of column ti, this lane's rows
+  for (int r0 = 16 * wave; r0 < m; r0 += 64) {
+    const zt* qr = Q + (r0 + ti < m ? r0 + ti : m - 1);
+    v4d re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+    zt d[4];
 #pragma unroll
-  for (int i = 0; i < kAccMaxR; ++i) nrm[i] = 0.0;
-  for (int row = tid; row < m; row += 256) {
-    zt d[kAccMaxR];  // row `row` of B - Q C, every Q entry read once
+    for (int q = 0; q < 4; ++q) {
+      const int row = r0 + tk + 4 * q;
+      d[q] = bi[row < m ? row : m - 1];
+    }
+    for (int k0 = 0; k0 < l; k0 += 16) {
+      zt u[4], v[4];
 #pragma unroll
-    for (int i = 0; i < kAccMaxR; ++i)
-      d[i] = i < r ? B[size_t(i) * m + row] : make_double2(0.0, 0.0);
-    for (int j = 0; j < l; ++j) {
-      const zt q = Q[size_t(j) * m + row];
+      for (int t = 0; t < 4; ++t) {
+        const int k = k0 + 4 * t + tk, kc = k < l ? k : l - 1;
+        u[t] = qr[size_t(kc) * m];
+        v[t] = cs[kc * kAccMaxR + (ti < r ? ti : r - 1)];
+        if (k >= l) u[t] = v[t] = zero;
+      }
 #pragma unroll
-      for (int i = 0; i < kAccMaxR; ++i)
-        if (i < r) d[i] = zsub(d[i], zmul(q, cs[j * kAccMaxR + i]));
+      for (int t = 0; t < 4; ++t) {
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(u[t].x, v[t].x, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(u[t].x, v[t].y, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(-u[t].y, v[t].y, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(u[t].y, v[t].x, im, 0, 0, 0);
+      }
     }
 #pragma unroll
-    for (int i = 0; i < kAccMaxR; ++i)
-      if (i < r) nrm[i] += zabs2(d[i]);
+    for (int q = 0; q < 4; ++q) {
+      const zt v = make_double2(d[q].x - re[q], d[q].y - im[q]);
+      if (r0 + tk + 4 * q < m) nrm += zabs2(v);
+    }
   }
-#pragma unroll
-  for (int i = 0; i < kAccMaxR; ++i) {
-    const double v = wave_sum(nrm[i]);
-    if (lane == 0) part[wave][i] = v;
-  }
+  nrm += __shfl_xor(nrm, 16, 64);
+  nrm += __shfl_xor(nrm, 32, 64);
+  if (lane < r) part[wave][lane] = nrm;
   __syncthreads();
   if (tid != 0) return;
   double mx = 0.0;
@@ -864,8 +895,7 @@ __global__ __launch_bounds__(256) void k_acc_resid(Prob* probs, double eps, int3
     mx = fmax(mx, sqrt(v));
   }
   double frob2 = 0.0;
-  const int npart = gate_partials(P.dl * P.dr, P.gcol0, P.chi_l * P.chi_r);
-  for (int i = 0; i < npart; ++i) frob2 += P.part[i];
+  for (int i = 0; i < npart; ++i) frob2 += i < 64 ? frob_s[i] : P.part[i];
   const double tol = sqrt(eps) * sqrt(frob2) / kAccConst;
   const bool grow = finite && mx > tol;
   int lnew = l;
