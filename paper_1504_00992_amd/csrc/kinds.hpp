@@ -32,6 +32,8 @@ __device__ __forceinline__ int updated_bond_extent(const Prob& P) {
   return e < P.chi_cap ? e : P.chi_cap;
 }
 
+constexpr int kTileChunk = 32;
+
 // Whether the Gram of a problem's sketches may be split into row chunks.
 __device__ __forceinline__ bool gram_room(const Prob& P) {
   return P.Qc && !(P.chol & (kGramF32M | kGramF32N));
@@ -62,6 +64,12 @@ struct TileKinds<Prob> {
   // column block run one after another, on one XCD, and share its Theta
   // columns in that XCD's L2; the whole gate matrix stays there too.
   static constexpr bool col_major(int kind) { return kind == TK_GATE; }
+  // Tiles of caller matrices go to the XCDs in short runs: the queue starts
+  // with the largest matrices, and one XCD must not get all their long tiles
+  // (10 sizes from 300 to 2000 twice, l = 74: sketch products 3.65 ms with an
+  // eighth of the queue per XCD, 2.52 ms so; runs of 96 2.91 ms; 256 matrices
+  // up to 2048 46 and 35 ms).  A run still shares operands in the XCD's L2.
+  static __device__ int chunk(int, int tebd) { return tebd ? 0 : kTileChunk; }
   __device__ static __forceinline__ void shape(int kind, const Prob& P, int tebd, int& M, int& N) {
     M = N = 0;
     if (kind == TK_GATE) {

@@ -16,8 +16,9 @@
 // (64 x 64 unless a kind's shapes call for another),
 //   static constexpr bool col_major(int kind);   tiles of a problem numbered
 // down the columns (the row tiles of one column block consecutive) instead
-// of along the rows, and, for
-// k_schedule<PT, true>, static __device__ bool dims(const PT&, int d[3])
+// of along the rows,
+//   static __device__ int chunk(int kind, int flag);   virtual_block's
+// and, for k_schedule<PT, true>, static __device__ bool dims(const PT&, int d[3])
 // (false for an inactive problem).
 #pragma once
 
@@ -173,9 +174,13 @@ __device__ __forceinline__ int find_problem(const int32_t* off, int nprob, int t
   return lo;
 }
 
-__device__ __forceinline__ int virtual_block() {
-  const int g = gridDim.x, i = blockIdx.x;
-  return (i & 7) * (g >> 3) + (i >> 3);
+// chunk > 0: the blocks of an XCD take that many consecutive indices at a time
+// (its last, shorter run too), the next XCD the following ones.
+__device__ __forceinline__ int virtual_block(int chunk = 0) {
+  const int per = gridDim.x >> 3, x = blockIdx.x & 7, j = blockIdx.x >> 3;
+  if (chunk == 0) return x * per + j;
+  const int full = per / chunk * chunk, c = j / chunk;
+  return j < full ? (c * 8 + x) * chunk + (j - c * chunk) : 8 * full + x * (per - full) + (j - full);
 }
 
 // Run global tile t of one kind: body(P, M, N, m0, n0, tile_index_within_problem).
@@ -211,7 +216,7 @@ __device__ __forceinline__ void for_each_tile(PT* probs, const int32_t* offs, in
                                               Body body) {
   const int32_t* off = offs + size_t(KIND) * (nprob + 1);
   const int total = off[nprob];
-  for (int t = virtual_block(); t < total; t += gridDim.x)
+  for (int t = virtual_block(TileKinds<PT>::chunk(KIND, flag)); t < total; t += gridDim.x)
     run_tile<KIND>(probs, off, nprob, flag, t, body);
 }
 
