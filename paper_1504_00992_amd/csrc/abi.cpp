@@ -392,9 +392,9 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   // the bounds arrive while Theta, the gate and Omega run: the first sketch
   // product already takes the tile variant and grid of the batch's real sizes
   if (c.bounds_dev) {
-    int32_t b[6 + TK_COUNT];
-    static_assert(kBoundsSlot + 6 + TK_COUNT <= 64, "bounds fit the pinned buffer");
-    TRY(bounds_wait(b, 6 + TK_COUNT));
+    int32_t b[8 + TK_COUNT];
+    static_assert(kBoundsSlot + 8 + TK_COUNT <= 64, "bounds fit the pinned buffer");
+    TRY(bounds_wait(b, 8 + TK_COUNT));
     c.mmin = b[0];
     c.mmax = b[1];
     c.nmin = b[2];
@@ -402,6 +402,7 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
     c.lmin = b[4];
     c.lmax = b[5];
     for (int k = 0; k < TK_COUNT; ++k) c.ktiles[k] = b[6 + k];
+    for (int i = 0; i < 2; ++i) c.split[i] = b[6 + TK_COUNT + i];
   }
   TIMED(PK_SKETCH_AOM, sketch(SK_Y_FROM_OMEGA));
   // the first QR reveals the sketch's rank (column pivoting); the power
@@ -459,6 +460,7 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
     c.lmax = widest;
     c.lmin = 1;
     for (int k = 0; k < TK_COUNT; ++k) c.ktiles[k] = -1;
+    c.split[0] = c.split[1] = -1;
     Common cr = c;
     cr.bounds_dev = nullptr;
     TIMED(PK_SCHEDULE, launch_schedule(probs, cr, s));
@@ -589,6 +591,7 @@ tebd_status enqueue_sweep(const tebd_mps* mps, const tebd_z* gates, int64_t gate
     c.lmax = std::min(l2, std::min(c.mmax, c.nmax));
     c.bounds_dev = nullptr;
     for (int k = 0; k < TK_COUNT; ++k) c.ktiles[k] = -1;  // the second pass schedules anew
+    c.split[0] = c.split[1] = -1;
   }
   bool second = c.adaptive == 1 || c.adaptive == 2;
   if (e == hipSuccess && c.adaptive == 2) {
@@ -889,6 +892,8 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
   c.grid = persistent_grid(tiles);
   for (const int k : {TK_SKM, TK_SKN, TK_SKM_W, TK_SKN_W, TK_SKM_S, TK_SKN_S})
     c.ktiles[k] = int32_t(std::min<int64_t>(known[k], kKnownGridMax));
+  c.split[0] = TileKinds<Prob>::few(c.ktiles[TK_SKM], 0, c.nprob, 0);
+  c.split[1] = TileKinds<Prob>::few(c.ktiles[TK_SKN], 0, c.nprob, 0);
   hipError_t e = noalloc ? hipSuccess : upload(workspace, host.data(), host.size() * sizeof(Prob), s);
   if (e == hipSuccess) e = run_pipeline(reinterpret_cast<Prob*>(workspace), c, s);
   if (e != hipSuccess) return fail(TEBD_ERR_DEVICE, "HIP error while enqueuing: %s", hipGetErrorString(e));

@@ -45,6 +45,8 @@ struct TileKinds<AdjProb> {
   static constexpr int tile_n(int) { return 64; }
   static constexpr bool col_major(int) { return false; }
   static __device__ int chunk(int, int) { return 0; }
+  static constexpr int rule(int) { return -1; }
+  static __device__ bool few(int, int, int, int) { return false; }
   __device__ static __forceinline__ void shape(int kind, const AdjProb& P, int, int& M, int& N) {
     M = N = 0;
     if (P.L == 0) return;

@@ -258,30 +258,19 @@ hipError_t launch_theta_gate(Prob* probs, const Common& c, hipStream_t s) {
 // --------------------------------------------------------------------------
 // Sketch / power iteration / projection products
 
-// Wavefront split of the depth (zgemm_tile_split16) for launches of few tiles,
-// 32 x 32 tiles otherwise: a launch of up to kSplitTiles 32 x 32 tiles leaves
-// CUs idle or with one tile each, whose chain over the whole depth is its
-// time.  Measured, the six products of a truncation, 32 x 32 / split: 96 x 80,
-// l = 34 (9 tiles) 45 / 30 us; 1 x 2048^2, l = 74 (192 tiles) 881 / 540; 4 x
-// 1024^2, l = 74 (384) 612 / 502; 60 x 200^2, l = 30 (420) 154 / 165; 120 x
-// 200^2 (840) 251 / 294; 400 x 100^2 (1600) 242 / 280.  Decided on the device,
-// by the queue's total, so that it does not depend on what the host knows.
-constexpr int kSplitTiles = 400;
-__device__ __forceinline__ bool split_depth(const int32_t* offs, int nprob, int kind, int most) {
-  return offs[size_t(kind) * (nprob + 1) + nprob] <= most;
-}
-
 template <int WHICH>
 __device__ __forceinline__ void sketch_split(Prob* probs, const int32_t* offs, int nprob, int tebd,
                                              double* red);
 
-// split_most: the most tiles that take the split (0: none, a tuned choice)
+// The depth of the tiles is split between wavefronts (zgemm_tile_split16) where
+// the scheduler's verdict says so (TileKinds<Prob>::few: decided from the queue,
+// so that it does not depend on what the host knows) and none was tuned.
 template <int WHICH>
 __global__ __launch_bounds__(256) void k_sketch(Prob* probs, const int32_t* offs, int nprob,
-                                                int tebd, int split_most) {
+                                                int tebd, int tuned) {
   __shared__ zt smem[CfgSk::lds_elems];
   static_assert(sizeof(smem) >= 2048 * sizeof(double), "the split's partial tiles fit");
-  if (split_depth(offs, nprob, WHICH == SK_YT_FROM_Y ? TK_SKN : TK_SKM, split_most)) {
+  if (!tuned && offs[size_t(TK_COUNT) * (nprob + 1) + (WHICH == SK_YT_FROM_Y ? 1 : 0)]) {
     sketch_split<WHICH>(probs, offs, nprob, tebd, reinterpret_cast<double*>(smem));
     return;
   }
@@ -480,16 +469,16 @@ hipError_t launch_sketch(Prob* probs, const Common& c, int which, hipStream_t s)
       TEBD_LAUNCH("k_sketch_split<2>", k_sketch_split<SK_Y_FROM_YT>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd);
     return hipGetLastError();
   }
-  const int most = variant < 0 ? kSplitTiles : 0;
+  const int tuned = variant < 0 ? 0 : 1;
   const int kind = which == SK_YT_FROM_Y ? TK_SKN : TK_SKM;
-  const bool split = c.ktiles[kind] >= 0 && c.ktiles[kind] <= most;
+  const bool split = !tuned && c.split[kind == TK_SKN] > 0;
   const dim3 g(grid_for(c, !split ? kind : kind == TK_SKN ? TK_SKN_S : TK_SKM_S));
   if (which == SK_Y_FROM_OMEGA)
-    TEBD_LAUNCH("k_sketch<0>", k_sketch<SK_Y_FROM_OMEGA>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, most);
+    TEBD_LAUNCH("k_sketch<0>", k_sketch<SK_Y_FROM_OMEGA>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, tuned);
   else if (which == SK_YT_FROM_Y)
-    TEBD_LAUNCH("k_sketch<1>", k_sketch<SK_YT_FROM_Y>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, most);
+    TEBD_LAUNCH("k_sketch<1>", k_sketch<SK_YT_FROM_Y>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, tuned);
   else
-    TEBD_LAUNCH("k_sketch<2>", k_sketch<SK_Y_FROM_YT>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, most);
+    TEBD_LAUNCH("k_sketch<2>", k_sketch<SK_Y_FROM_YT>, g, dim3(256), 0, s, probs, c.offs, c.nprob, c.tebd, tuned);
   return hipGetLastError();
 }
 

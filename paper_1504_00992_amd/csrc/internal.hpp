@@ -127,6 +127,7 @@ struct Common {
                                   // of m, n, l1 there, then the tile total of every kind
   int32_t ktiles[TK_COUNT_MAX] = {-1, -1, -1, -1, -1, -1, -1, -1, -1,
                                   -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};  // host copy of the totals (-1: unknown)
+  int32_t split[2] = {-1, -1};  // host copy of the verdicts on TK_SKM, TK_SKN (-1: unknown)
   int32_t* offs;     // device: per tile kind, exclusive prefix sums of tile counts [nprob + 1]
   int32_t grid;      // workgroups of the persistent contraction launches (multiple of 8)
   // TEBD sweeps: the capacity sizes (d_max chi_cap rows, the fixed-rank sketch
@@ -235,7 +236,9 @@ __host__ __device__ inline int gate_partials_cap(int rows, int cols) {
   return ((rows + kGateTileM - 1) / kGateTileM) * ((cols + kGateTileN - 1) / kGateTileN + 1);
 }
 
-inline size_t sched_bytes(int64_t nprob) { return size_t(TK_COUNT) * size_t(nprob + 1) * sizeof(int32_t); }
+inline size_t sched_bytes(int64_t nprob) {
+  return (size_t(TK_COUNT) * size_t(nprob + 1) + 2) * sizeof(int32_t);  // two verdicts (schedule_body)
+}
 
 // Workgroups of a persistent launch over the tiles of `kind` (and of
 // `kind2`, when two queues share the launch): their tile total when the host

@@ -18,6 +18,7 @@
 // down the columns (the row tiles of one column block consecutive) instead
 // of along the rows,
 //   static __device__ int chunk(int kind, int flag);   virtual_block's
+//   static constexpr int rule(int kind), few(...): see schedule_body
 // and, for k_schedule<PT, true>, static __device__ bool dims(const PT&, int d[3])
 // (false for an inactive problem).
 #pragma once
@@ -50,6 +51,9 @@ __device__ __forceinline__ int kind_tiles(int kind, const PT& P, int flag) {
 // over the active problems, {min, max} of each of TileKinds<PT>::dims
 // (three values), to bounds[0..6) (an empty batch gives {1, 1} each), and
 // the tile total of every kind to bounds[6..6 + count).
+// For the kinds with TileKinds<PT>::rule(kind) = i >= 0 (two at most), verdict
+// TileKinds<PT>::few(total, largest of a problem, nprob, flag) goes to word i
+// after the offsets (and to bounds[6 + count + i]).
 constexpr int kScheduleThreads = 1024;
 
 // The body, for a workgroup of kScheduleThreads threads (also run at the end
@@ -60,17 +64,23 @@ __device__ __forceinline__ void schedule_body(const PT* probs, int nprob, int fl
   constexpr int NK = TileKinds<PT>::count, NT = kScheduleThreads, NW = NT / 64;
   __shared__ int32_t wsum[NK][NW];
   __shared__ int32_t wext[6][NW];  // per-wavefront {min, max} of the three sizes
+  __shared__ int32_t wbig[2][NW];  // per-wavefront largest tile counts of the kinds with a rule
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int chunk = (nprob + NT - 1) / NT;
   const int p0 = min(nprob, tid * chunk), p1 = min(nprob, p0 + chunk);
   int32_t own[NK], incl[NK];
-  int32_t lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {0, 0, 0};
+  int32_t lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {0, 0, 0}, big[2] = {0, 0};
 #pragma unroll
   for (int k = 0; k < NK; ++k) own[k] = 0;
   for (int p = p0; p < p1; ++p) {
     const PT& P = probs[p];
 #pragma unroll
-    for (int k = 0; k < NK; ++k) own[k] += kind_tiles(k, P, flag);
+    for (int k = 0; k < NK; ++k) {
+      const int32_t t = kind_tiles(k, P, flag);
+      own[k] += t;
+      const int i = TileKinds<PT>::rule(k);
+      if (i >= 0) big[i & 1] = max(big[i & 1], t);
+    }
     if constexpr (BOUNDS) {
       int d[3];
       if (TileKinds<PT>::dims(P, d))
@@ -87,6 +97,11 @@ __device__ __forceinline__ void schedule_body(const PT* probs, int nprob, int fl
     const int32_t v = wave_scan_i32(own[k], 0, add);
     incl[k] = v;
     if (lane == 63) wsum[k][wave] = v;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    big[i] = wave_scan_i32(big[i], 0, [](int32_t a, int32_t b) { return a > b ? a : b; });
+    if (lane == 63) wbig[i][wave] = big[i];
   }
   if constexpr (BOUNDS) {  // wavefront minima and maxima (empty lanes: INT32_MAX, 0), in lane 63
     const auto mn = [](int32_t a, int32_t b) { return a < b ? a : b; };
@@ -123,6 +138,14 @@ __device__ __forceinline__ void schedule_body(const PT* probs, int nprob, int fl
     }
     offs[size_t(tid) * (nprob + 1) + nprob] = acc;
     if (BOUNDS) bounds[6 + tid] = acc;
+    const int i = TileKinds<PT>::rule(tid);
+    if (i >= 0) {
+      int32_t most = 0;
+      for (int w = 0; w < NW; ++w) most = max(most, wbig[i][w]);
+      const int32_t few = TileKinds<PT>::few(acc, most, nprob, flag) ? 1 : 0;
+      offs[size_t(NK) * (nprob + 1) + i] = few;
+      if (BOUNDS) bounds[6 + NK + i] = few;
+    }
   }
   __syncthreads();
   int32_t run[NK];

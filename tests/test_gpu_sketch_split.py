@@ -32,3 +32,28 @@ def test_an_unsorted_batch_keeps_its_places():
     shapes = [(20, 30), (300, 200), (20, 30), (90, 100), (5, 7), (300, 200), (64, 400)]
     mats = [wl.known_spectrum(m, n, np.exp(-np.arange(min(m, n)) / 4.0), gen) for m, n in shapes]
     rr._compare(mats, rr._gpu(mats, 20, 10, 2, 1e-10), 20, 10, 2, 1e-10)
+
+
+def test_a_sweep_of_unlike_bonds():
+    # 16 chains whose front moves through: sweeps of 300 to 1000 tiles, whose
+    # largest bonds at first have many times the average's, so that the verdict
+    # changes on the way.  Chain 0 alone (few tiles, always split) gives the
+    # same bonds and Schmidt values; the rank modes decide alike, bit for bit.
+    import torch
+    from paper_1504_00992_amd import api, models as pm
+    dims, hb = pm.spin_boson(40, 6)
+    runs = {}
+    for chains, mode in ((16, 1), (16, 2), (1, 2)):
+        dev = api.DeviceMPS.product_state(chains, dims, [0] * 40, 24)
+        drv = api.TEBD(dev, hb, 0.1, 24, p=6, q=2, trunc_eps=1e-10, seed=11, adaptive=mode)
+        for _ in range(20):
+            drv.step()
+        torch.cuda.synchronize()
+        runs[chains, mode] = (dev.gamma.clone(), dev.lam.clone(), dev.chi.clone(), drv.ws.status.clone())
+    for a, b in zip(runs[16, 1], runs[16, 2]):
+        assert torch.equal(a, b)
+    n = runs[1, 2][2].numel()
+    assert torch.equal(runs[16, 2][2].flatten()[:n], runs[1, 2][2].flatten())
+    assert int(runs[1, 2][2].max()) >= 8
+    lam = runs[1, 2][1].flatten()
+    assert float((runs[16, 2][1].flatten()[:lam.numel()] - lam).abs().max()) <= 1e-10
