@@ -697,7 +697,7 @@ __global__ __launch_bounds__(kGqThreads) void k_gram_qr(Prob* probs, const int32
       }
     }
     if (lane == 0) sh.todo[wave] = mine;
-    __syncthreads();
+    if (!__syncthreads_or(mine >= 0)) continue;  // (todo is not read)
     for (int w = 0; w < kGqWaves; ++w) {
       const int p = sh.todo[w];
       if (p < 0) continue;
