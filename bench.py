@@ -109,6 +109,11 @@ def qr_bytes(rows, l, with_r=False):
     return 16.0 * (2 * rows * l + (l * l if with_r else 0))
 
 
+# The QRs without pivoting run as k_gram_qr, or as k_gram, k_chol and k_qapply for
+# large sketches, counted together under that name with a Householder QR's work.
+# A run that has no such kernel (FP32 products apart) took the Householder ones.
+GRAM_QR = "k_gram_qr"
+GRAM_PARTS = ("k_gram<", "k_chol<", "k_qapply<")
 QR_KERNELS = ("k_qr_reg<512, 8, {}>", "k_qr_reg<1024, 12, {}>", "k_qr_lds<1024>", "k_qr_glb<1024>")
 
 
@@ -118,6 +123,7 @@ class Work:
     def __init__(self, lib):
         self.lib = lib
         self.k = {}
+        self.unpivoted = {}   # the part of each QR kernel's entry that the Gram-based QR does
         self._cls = {}
 
     def add(self, name, flops, nbytes):
@@ -134,6 +140,11 @@ class Work:
     def qr(self, rows, l_class, l, pivot, with_r=False):
         name = QR_KERNELS[self.qr_class(rows, l_class)].format("true" if pivot else "false")
         self.add(name, qr_flops(rows, l), qr_bytes(rows, l, with_r))
+        if not pivot:
+            self.add(GRAM_QR, qr_flops(rows, l), qr_bytes(rows, l, with_r))
+            e = self.unpivoted.setdefault(name, [0.0, 0.0])
+            e[0] += qr_flops(rows, l)
+            e[1] += qr_bytes(rows, l, with_r)
 
     def rrsvd_pass(self, m, n, l, q, mixed, chi_new, form=True):
         """Kernels of Alg. 1 and steps i-iii for one problem at width l
@@ -234,7 +245,7 @@ def measured_traffic(kernel, workload):
     return None, os.path.basename(path)
 
 
-ALU_KERNELS = ("k_qr_", "k_svd_pairs", "k_small_svd", "k_omega", "k_schedule",
+ALU_KERNELS = ("k_qr_", "k_svd_pairs", "k_small_svd", "k_jac_", "k_omega", "k_schedule",
                "k_plan", "k_stage2", "k_frob")
 
 
@@ -242,10 +253,12 @@ def merge_tile_variants(prof):
     """The tile variants of a sketch product (k_sketch<i> on 32 x 32,
     k_sketch_wide<i> on 64 x 64, k_sketch_split<i> on split-depth 16 x 16
     tiles, picked per launch by the autotune cache) do the same work: count
-    them as one kernel, k_sketch<i>."""
+    them as one kernel, k_sketch<i>.  The parts of the large sketches' Gram-based
+    QR count as k_gram_qr."""
     out = {}
     for k, (ms, n) in prof.items():
         key = k.replace("k_sketch_wide<", "k_sketch<").replace("k_sketch_split<", "k_sketch<")
+        key = GRAM_QR if key.startswith(GRAM_PARTS) else key
         a = out.get(key, (0.0, 0))
         out[key] = (a[0] + ms, a[1] + n)
     return out
@@ -267,6 +280,8 @@ def kernel_roofline(prof, work, workload, name=None):
         e["note_variants"] = ("launches of the tile variants k_sketch<i>, k_sketch_wide<i> "
                               "and k_sketch_split<i> counted together")
     fl, by = work.k.get(name, (0.0, 0.0))
+    if GRAM_QR in prof and name in work.unpivoted:
+        fl, by = fl - work.unpivoted[name][0], by - work.unpivoted[name][1]
     f32 = name.startswith("k_sketch_f32")
     if fl > 0 and ms > 0:
         ach = fl / (ms * 1e-3) / 1e12
@@ -414,6 +429,10 @@ def history_work(lib, hist, dims, chi_max, p, q, adaptive, mixed=False, times=1)
                    bonds=(b,), gate_bytes=first)
         for name, (fl, by) in one.k.items():
             w.add(name, k * fl, k * by)
+        for name, (fl, by) in one.unpivoted.items():
+            e = w.unpivoted.setdefault(name, [0.0, 0.0])
+            e[0] += k * fl
+            e[1] += k * by
     return w
 
 

@@ -160,7 +160,7 @@ tebd_status tebd_workspace_size(const tebd_mps* mps, int64_t batch, const int64_
                                 const int64_t* n, const tebd_params* prm, size_t* bytes);
 
 /* Batched truncated SVD by RRSVD (Sec. IV: Alg. 1 with q power iterations
- * re-orthonormalised by Householder QR, then B = Q^H A, the SVD of B and
+ * re-orthonormalised by QR, then B = Q^H A, the SVD of B and
  * U = Q U_B; singular values sorted descending), followed by the truncation
  * rule on the relative discarded weight.  Drop-in for a truncated SVD call.
  *
@@ -360,10 +360,11 @@ int32_t tebd_tune_get(int32_t precision, int32_t max_rows, int32_t width);
 /* Size class, hence kernel, that a factorisation of the given shape runs
  * in (a planning query; no device work).  factorization 0: the Householder
  * QR of a rows x l sketch (the class follows the sketch width l the problem
- * started with); 1: the small SVD of an l x l factor (rows is ignored).
+ * started with; QRs that a Gram matrix does well are not Householder's);
+ * 1: the small SVD of an l x l factor (rows is ignored).
  * QR classes: 0 k_qr_reg<512, 8, *>, 1 k_qr_reg<1024, 12, *>, 2 k_qr_lds,
  * 3 k_qr_glb; small-SVD classes: 0 k_svd_pairs<256, 0>, 1 k_svd_pairs<512, 1>,
- * 2 k_small_svd<1024, 2, true>, 3 k_small_svd<1024, 4, false>.  Returns -1
+ * 2 and 3 k_jac_round and k_small_svd (2 up to l = 69).  Returns -1
  * for sizes outside [1, 8192] x [1, 256] or an unknown factorization. */
 int32_t tebd_size_class(int32_t factorization, int32_t rows, int32_t l);
 

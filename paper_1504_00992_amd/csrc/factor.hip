@@ -4,11 +4,8 @@
 //
 // Paper: Tamascelli, Rosenbach, Plenio, arXiv:1504.00992.  QR steps of Alg. 1
 // (the paper leaves the QR method open; Householder reflections are used
-// because the sketch of a TEBD Theta is often rank deficient), the SVD of
-// B = Q^H A of Sec. IV step ii (computed as B^H = Q_B R_B, then a one-sided
-// Jacobi SVD of R_B^H, which keeps small singular values to high relative
-// accuracy), and the discarded weight of Sec. II.C, Eq. (defdiscweigt),
-// evaluated with the Frobenius identity of Sec. IV.
+// because the sketch of a TEBD Theta is often rank deficient; the QRs after
+// the first are Gram-based, gramqr.hip), and the Accuracy Check of Sec. IV.
 #include <algorithm>
 #include <cfloat>
 #include <type_traits>
