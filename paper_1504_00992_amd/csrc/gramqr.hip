@@ -660,12 +660,12 @@ __device__ __forceinline__ bool gram_qr_small(Prob& P, int which, int mode, zt* 
 }
 
 // Items of the launch: packs of kGqWaves small problems, a wavefront each,
-// then the problems of a workgroup each.  direct: item i stands for the
-// problems 8 i ... 8 i + 7, then for problem i - packs, whichever of them are
-// small or not; else both kinds come from their queues (TK_GQ_S, TK_GQ_L).
-// The queues cost two dependent reads before a problem is known, the direct
-// items workgroups that find nothing to do, which a batch of up to one
-// workgroup per CU does not notice.
+// then the problems of a workgroup each, both from their queues (TK_GQ_S,
+// TK_GQ_L).  direct, a batch of up to one problem per CU: item i is problem i,
+// a small one taken by the first wavefront.  The queues cost two dependent
+// reads before a problem is known, and wavefronts of a pack wait for each
+// other's instructions on a CU while others idle: 90 launches over 14 bonds
+// of a few states each take 0.68 ms in packs, 0.53 so.
 constexpr int kGqDirect = 256;
 
 __global__ __launch_bounds__(kGqThreads) void k_gram_qr(Prob* probs, const int32_t* offs, int nprob,
@@ -677,23 +677,23 @@ __global__ __launch_bounds__(kGqThreads) void k_gram_qr(Prob* probs, const int32
   const bool direct = nprob <= kGqDirect;
   const int32_t* ol = offs + size_t(TK_GQ_L) * (nprob + 1);
   const int32_t* os = offs + size_t(TK_GQ_S) * (nprob + 1);
-  const int nl = direct ? nprob : ol[nprob], ns = direct ? nprob : os[nprob];
+  const int nl = direct ? nprob : ol[nprob], ns = direct ? 0 : os[nprob];
   const int packs = (ns + kGqWaves - 1) / kGqWaves, items = nl + packs;
   for (int it = blockIdx.x; it < items; it += gridDim.x) {
     int mine = -1;  // a problem for the workgroup
     if (it >= packs) {
       if (wave == 0) {
-        mine = direct ? it - packs : find_problem(ol, nprob, it - packs);
-        if (direct && gram_small(probs[mine].m, probs[mine].n, probs[mine].l1)) mine = -1;
+        mine = direct ? it : find_problem(ol, nprob, it - packs);
+        if (direct) {
+          Prob& P = probs[mine];
+          if (gram_small(P.m, P.n, P.l1) && gram_qr_small(P, which, mode, smem)) mine = -1;
+        }
       }
     } else {
       const int t = it * kGqWaves + wave;
       if (t < ns) {
-        const int p = direct ? t : find_problem(os, nprob, t);
-        Prob& P = probs[p];
-        if ((!direct || gram_small(P.m, P.n, P.l1)) &&
-            !gram_qr_small(P, which, mode, smem + wave * 272))
-          mine = p;
+        const int p = find_problem(os, nprob, t);
+        if (!gram_qr_small(probs[p], which, mode, smem + wave * 272)) mine = p;
       }
     }
     if (lane == 0) sh.todo[wave] = mine;
@@ -898,14 +898,14 @@ hipError_t launch_gram_qr(Prob* probs, const Common& c, int which, int mode, hip
   // the sketches of a workgroup or a wavefront each, unless every one of the batch is large
   if (e == hipSuccess && !(queue && gram_queue_size(which ? c.nmin : c.mmin, c.lmin))) {
     // LDS for the sketch too, up to the CU's whole: a workgroup per CU suffices
-    // (the small problems go eight to a workgroup)
+    // (in a batch of more than kGqDirect the small problems go eight to a workgroup)
     const int64_t want = int64_t(base) + int64_t(gq_ldy(which ? c.nmax : c.mmax)) * c.lmax;
     int elems = int(want < kGqLdsMax ? want : kGqLdsMax);
     if (elems < kGqWaves * 272) elems = kGqWaves * 272;
     const int nl = c.ktiles[TK_GQ_L], ns = c.ktiles[TK_GQ_S];
     int g = nl + (ns + kGqWaves - 1) / kGqWaves;
     if (c.nprob <= kGqDirect)
-      g = c.nprob + (c.nprob + kGqWaves - 1) / kGqWaves;
+      g = c.nprob;
     else if (nl < 0 || ns < 0)
       g = c.nprob;
     TEBD_LAUNCH("k_gram_qr", k_gram_qr, dim3(g < 1 ? 1 : g), dim3(kGqThreads),
