@@ -128,3 +128,23 @@ def test_widths_of_the_fp32_product_path(m, n, chi_max):
     assert np.max(np.abs((u * s) @ vh - (ou * os_) @ ovh)) <= 1e-5 * os_[0]
     assert np.allclose(u.conj().T @ u, np.eye(c), atol=1e-12)
     assert np.allclose(vh @ vh.conj().T, np.eye(c), atol=1e-12)
+
+
+@pytest.mark.parametrize("count", [256, 257])
+def test_around_one_problem_per_cu(count):
+    # a workgroup per problem up to 256, from there the small ones eight to a
+    # workgroup: small, wide and refused (zero) sketches side by side
+    gen = wl.rng(count)
+    small = [wl.known_spectrum(30, 28, np.exp(-np.arange(28) / 2.0), gen) for _ in range(3)]
+    mats = [small[i % 3] for i in range(count)]
+    mats[5] = np.zeros((30, 28), dtype=np.complex128)
+    mats[100] = wl.known_spectrum(150, 120, np.exp(-np.arange(120) / 5.0), gen)
+    res = rr._gpu(mats, 6, 5, 2, 1e-10)
+    assert not np.any(np.asarray(res[1][5]))
+    for i in (0, 4, 6, 7, 8, 100, count - 1):
+        ou, os_, ovh, ochi, ow, ost = rr._oracle(mats[i], i, 6, 5, 2, 1e-10)
+        U, S, VH, chi, w, st = (r[i] for r in res)
+        assert chi == ochi
+        assert np.max(np.abs(S[:ochi] - os_)) <= 1e-10 * os_[0]
+        rec = (U[:, :ochi] * S[None, :ochi]) @ VH[:ochi]
+        assert np.max(np.abs(rec - (ou * os_[None, :]) @ ovh)) <= 1e-10 * os_[0]
