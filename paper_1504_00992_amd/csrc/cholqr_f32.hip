@@ -2,11 +2,13 @@
 // where its products run in FP32: two passes of G = Y^H Y, G = L L^H,
 // Y <- Y L^-H (into Qc, then Qc and Y trade places).
 //
-// Its sums keep one fixed order.  An FP32 product rounds Q first, so a last
-// bit of Q that differs flips a rounding of 6e-8 here and there, and one flip
-// moves the truncated matrix by 1e-9 to 7e-8 (measured, 900 x 700 to 1024^2,
-// l = 74 to 110): another order of the FP64 sums gives results that agree to
-// the FP32 products' precision only.  Elsewhere rounding differences stay
+// Its sums keep one fixed order, and of each complex product the same real
+// products are fused (zmul_fixed: left to the compiler, copies of one unrolled
+// loop choose differently).  An FP32 product rounds Q first, so a last bit of Q
+// that differs flips a rounding of 6e-8 here and there, and one flip moves the
+// truncated matrix by 1e-9 to 7e-8 (measured, 900 x 700 to 1024^2, l = 74 to
+// 110; 2 matrices in 100): another order or rounding of the FP64 sums gives
+// results that agree to the FP32 products' precision only.  Elsewhere rounding differences stay
 // 1e-14 and the faster gramqr.hip takes over (here too for the QR of B^H,
 // after the last FP32 product).
 //
@@ -24,6 +26,14 @@ namespace tebd {
 
 constexpr double kCholTol = 1e-14;
 constexpr int kCholLdsL = 96;  // Gram in LDS up to this width (147 KiB), else in global memory
+
+// a b and a conj(b), the second real product of each sum rounded on its own.
+__device__ __forceinline__ zt zmul_fixed(zt a, zt b) {
+  return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y));
+}
+__device__ __forceinline__ zt zmul_conj_fixed(zt a, zt b) {
+  return make_double2(fma(a.x, b.x, a.y * b.y), fma(a.y, b.x, -(a.x * b.y)));
+}
 
 using CfgGram = ZCfg<kSketchTileM, kSketchTileN, 16, 2, 2>;
 
@@ -168,7 +178,7 @@ __device__ __forceinline__ bool chol_factor(const zt* G, int l, double dmax, Cho
 #pragma unroll
         for (int a = c; a < NB; ++a) {
           const zt lij = col[ti + 32 * a];
-          g[a][c] = zsub(g[a][c], zmul(lij, zconj(lkj)));
+          g[a][c] = zsub(g[a][c], zmul_conj_fixed(lij, lkj));
         }
       }
     }
@@ -205,8 +215,9 @@ __device__ __forceinline__ void chol_inverse(zt* X, int l, const CholShared& sh)
               const int k = 64 * q + 4 * u + m;
               zt lik = row[q == 0 ? 16 * m : 64 + 8 * m];
               if (k >= i) lik = make_double2(0.0, 0.0);
-              sr[m] += lik.x * x[q][m].x - lik.y * x[q][m].y;
-              si[m] += lik.x * x[q][m].y + lik.y * x[q][m].x;
+              const zt t = zmul_fixed(lik, x[q][m]);
+              sr[m] += t.x;
+              si[m] += t.y;
             }
           }
           const double tr = group_sum((sr[0] + sr[1]) + (sr[2] + sr[3]), 16);
@@ -284,7 +295,7 @@ __global__ __launch_bounds__(1024) void k_chol_f32(Prob* probs, int pass) {
       if (ii < kk) continue;
       const int k = j + 1 + kk, i = j + 1 + ii;
       const zt lij = G[i + size_t(j) * l], lkj = G[k + size_t(j) * l];
-      G[i + size_t(k) * l] = zsub(G[i + size_t(k) * l], zmul(lij, zconj(lkj)));
+      G[i + size_t(k) * l] = zsub(G[i + size_t(k) * l], zmul_conj_fixed(lij, lkj));
     }
     __syncthreads();
   }
@@ -308,8 +319,9 @@ __global__ __launch_bounds__(1024) void k_chol_f32(Prob* probs, int pass) {
         const int k = lane + 64 * q;
         if (k >= c && k < i) {
           const zt lik = G[i + size_t(k) * l];
-          sr += lik.x * xr[q].x - lik.y * xr[q].y;
-          si += lik.x * xr[q].y + lik.y * xr[q].x;
+          const zt t = zmul_fixed(lik, xr[q]);
+          sr += t.x;
+          si += t.y;
         }
       }
       sr = wave_sum(sr);

@@ -1,0 +1,65 @@
+"""Truncated SVDs with complex FP32 products return the numbers they always
+returned: the Gram-based QR between those products keeps one order and one
+rounding of its sums (a last bit of Q that differs flips a rounding of 6e-8
+here and there, which moves the truncated matrix by 1e-9 to 7e-8).
+
+tests/golden/fp32_products.txt holds samples of results recorded from the
+library's first version of that QR, column by column in LDS: per matrix the
+largest singular values and entries of U diag(S) V^H x.  The inputs are exact
+products, so that their bits do not depend on a BLAS.  Tolerance: 1e-12 of s_1;
+the FP64 steps after the last FP32 product may round differently (about
+1e-14), one flipped rounding is at least ten times the tolerance.
+"""
+import os
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "fp32_products.txt")
+KEPT = 8  # singular values, and as many entries of U diag(S) V^H x
+
+
+def matrix(m, n, seed):
+    """G diag(s) H of rank 212, s_i = 2^20 0.96^i: integers throughout, whose sums
+    stay below 2^53, so that no order of a matrix product rounds."""
+    gen = np.random.default_rng(seed)
+    s = np.rint(2.0 ** 20 * np.cumprod(np.full(212, 0.96)))
+    g, h = (gen.integers(-63, 64, shape) + 1j * gen.integers(-63, 64, shape)
+            for shape in ((m, 212), (212, n)))
+    return (g * s) @ h
+
+
+def samples(mats, chi_max):
+    import torch
+    from paper_1504_00992_amd import api
+    U, S, VH, chi, w, st = api.rrsvd_truncate([torch.from_numpy(a).cuda() for a in mats], chi_max, 10,
+                                              2, 0.0, 1504, 0, precision=1)
+    torch.cuda.synchronize()
+    assert not st.cpu().numpy().any() and np.all(chi.cpu().numpy() == chi_max)
+    out = []
+    for i, a in enumerate(mats):
+        m, n = a.shape
+        u, s, vh = (t[i].cpu().numpy() for t in (U, S, VH))
+        x = np.where(np.arange(n) % 3 == 0, 1.0, -0.5)
+        y = (u[:, :chi_max] * s[:chi_max]) @ (vh[:chi_max] @ x) / np.sqrt(n)
+        at = np.arange(KEPT) * 3
+        out.append(np.concatenate([s[:KEPT], y[at].real, y[at].imag]))
+    return out
+
+
+def cases():
+    """(m, n, chi_max, seed) and the recorded samples, line by line."""
+    with open(GOLDEN) as f:
+        for line in f:
+            if not line.startswith("#"):
+                w = line.split()
+                yield tuple(int(v) for v in w[:4]), np.array([float.fromhex(v) for v in w[4:]])
+
+
+@pytest.mark.parametrize("case,want", [pytest.param(c, w, id="-".join(map(str, c))) for c, w in cases()])
+def test_results_of_fp32_products_stay(case, want):
+    m, n, chi_max, seed = case
+    got, = samples([matrix(m, n, seed)], chi_max)
+    assert np.max(np.abs(got - want)) <= 1e-12 * want[0]
