@@ -131,11 +131,13 @@ struct CholShared {
   zt L[kCholLdsL * (kCholLdsL + 1)];
   zt col[2][kCholLdsL];
   double diag[kCholLdsL];
+  int refused[2];  // verdict on the pivots of the even and the odd steps
 };
 
-// False when a pivot is refused (uniform).
-__device__ __forceinline__ bool chol_factor(const zt* G, int l, double dmax, CholShared& sh,
-                                            int* fail_s) {
+// False when a pivot is refused (uniform).  sh.refused is zero on entry.  Step j
+// writes its verdict before its barrier and everyone reads it after; the slot
+// is next written in step j + 2, past the barrier of step j + 1.
+__device__ __forceinline__ bool chol_factor(const zt* G, int l, double dmax, CholShared& sh) {
   constexpr int NB = kCholLdsL / 32;
   const int tid = threadIdx.x, ti = tid & 31, tk = tid >> 5, ld = chol_ld(l);
   zt g[NB][NB];
@@ -155,7 +157,7 @@ __device__ __forceinline__ bool chol_factor(const zt* G, int l, double dmax, Cho
       if (tk == jt) {  // the half wavefront that holds column j
         const double d = __shfl(g[b][b].x, (tid & 32) | jt, 64);
         if (!(d > kCholTol * dmax) || !isfinite(d)) {
-          *fail_s = 1;
+          sh.refused[j & 1] = 1;
         } else {
           const double root = sqrt(d), inv = 1.0 / root;
           if (ti == jt) sh.diag[j] = root;
@@ -171,7 +173,7 @@ __device__ __forceinline__ bool chol_factor(const zt* G, int l, double dmax, Cho
         }
       }
       __syncthreads();
-      if (*fail_s) return false;
+      if (sh.refused[j & 1]) return false;
 #pragma unroll
       for (int c = b; c < NB; ++c) {  // rows and columns beyond j (the others are done with)
         const zt lkj = col[tk + 32 * c];
@@ -265,18 +267,14 @@ __global__ __launch_bounds__(1024) void k_chol_f32(Prob* probs, int pass) {
     if (lane == 0) {
       dmax_s = dm;
       fail_s = !(dm > 0.0) || !isfinite(dm);
+      sh.refused[0] = sh.refused[1] = 0;
     }
   }
   __syncthreads();
-  if (in_lds && !fail_s) {
-    if (chol_factor(G, l, dmax_s, sh, &fail_s)) chol_inverse(P.J, l, sh);
-    __syncthreads();
-    if (!fail_s) {
-      if (tid == 0) P.chol_ok = 1;
-      return;
-    }
-  }
-  for (int j = 0; j < l && !fail_s; ++j) {
+  bool refused = fail_s != 0;
+  __syncthreads();  // fail_s is read before a step writes it
+  if (in_lds && !refused) refused = !chol_factor(G, l, dmax_s, sh);
+  for (int j = 0; j < l && !in_lds && !refused; ++j) {
     if (tid == 0) {
       const double d = G[j + size_t(j) * l].x;
       if (!(d > kCholTol * dmax_s) || !isfinite(d))
@@ -285,7 +283,8 @@ __global__ __launch_bounds__(1024) void k_chol_f32(Prob* probs, int pass) {
         G[j + size_t(j) * l] = make_double2(sqrt(d), 0.0);
     }
     __syncthreads();
-    if (fail_s) break;
+    refused = fail_s != 0;  // (two barriers before the next step's write)
+    if (refused) break;
     const double inv = 1.0 / G[j + size_t(j) * l].x;
     for (int i = j + 1 + tid; i < l; i += 1024) G[i + size_t(j) * l] = zscale(G[i + size_t(j) * l], inv);
     __syncthreads();
@@ -299,11 +298,16 @@ __global__ __launch_bounds__(1024) void k_chol_f32(Prob* probs, int pass) {
     }
     __syncthreads();
   }
-  if (fail_s) {
+  if (refused) {
     if (tid == 0) {
       P.chol_ok = 0;
       P.flags |= TEBD_DEV_QR_FALLBACK;
     }
+    return;
+  }
+  if (in_lds) {
+    chol_inverse(P.J, l, sh);
+    if (tid == 0) P.chol_ok = 1;
     return;
   }
   // X = (L^-1)^H: row c of X holds conj of column c of L^-1

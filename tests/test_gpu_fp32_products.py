@@ -63,3 +63,36 @@ def test_results_of_fp32_products_stay(case, want):
     m, n, chi_max, seed = case
     got, = samples([matrix(m, n, seed)], chi_max)
     assert np.max(np.abs(got - want)) <= 1e-12 * want[0]
+
+
+@pytest.mark.parametrize("chi_max", [50, 64, 86, 118])
+def test_refused_sketches_of_fp32_products(chi_max):
+    # l = 60, 74, 96 (the factor in LDS) and 128 (in global memory).  Only 20 rows
+    # are not zero, so that the Gram of A Omega has rank 20 to FP64 rounding and
+    # a pivot on the way is refused; a zero matrix, refused before the first
+    # pivot; and between them one that is kept.  The bounds stated for FP32
+    # products: 1e-5 of s_1, orthonormal to rounding.
+    import torch
+    import test_gpu_rrsvd as rr
+    import workloads as wl
+    from paper_1504_00992_amd import _lib, api
+    gen = wl.rng(chi_max)
+    thin = np.zeros((400, 400), dtype=np.complex128)
+    thin[3::20] = wl.known_spectrum(20, 400, np.linspace(1.0, 0.1, 20), gen)
+    mats = [thin, wl.known_spectrum(400, 380, np.exp(-np.arange(380) / 25.0), gen),
+            np.zeros((380, 400), dtype=np.complex128)]
+    assert _lib.tebd_size_class(0, 380, chi_max + 10) >= 2
+    U, S, VH, chi, w, st = api.rrsvd_truncate([torch.from_numpy(a).cuda() for a in mats], chi_max, 10, 2,
+                                              1e-10, rr.SEED, 0, precision=1)
+    torch.cuda.synchronize()
+    assert [bool(v & _lib.DEV_QR_FALLBACK) for v in st.cpu().numpy()] == [True, False, True]
+    for i, a in enumerate(mats):
+        ou, os_, ovh, ochi, ow, ost = rr._oracle(a, i, chi_max, 10, 2, 1e-10)
+        c = int(chi[i])
+        assert c == ochi
+        u, s, vh = U[i].cpu().numpy()[:, :c], S[i].cpu().numpy()[:c], VH[i].cpu().numpy()[:c]
+        assert np.max(np.abs(s - os_)) <= 1e-5 * os_[0]
+        assert np.max(np.abs((u * s) @ vh - (ou * os_) @ ovh)) <= 1e-5 * os_[0]
+        u = u[:, s > 0]
+        assert np.allclose(u.conj().T @ u, np.eye(u.shape[1]), atol=1e-12)
+        assert np.allclose(vh @ vh.conj().T, np.eye(c), atol=1e-12)
