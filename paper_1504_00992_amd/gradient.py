@@ -175,18 +175,29 @@ def expectation(gamma, lam, op, site):
     # without O) are one up to the site and a stacked pair from there on: a
     # loss is bound by the number of torch operations (40 sites, forward and
     # backward: 21 ms with an einsum per environment, 6 ms so).
-    if gamma.dtype != torch.complex128:
-        raise RuntimeError(f"gamma must be complex128, not {gamma.dtype}")
     n, dmax, cap = gamma.shape[0], gamma.shape[1], gamma.shape[-1]
+    if gamma.dtype != torch.complex128 or gamma.dim() != 4:
+        raise RuntimeError(f"gamma must be [N, d_max, cap, cap] complex128, not {list(gamma.shape)} {gamma.dtype}")
     op = torch.as_tensor(op, dtype=torch.complex128, device=gamma.device)
-    a = torch.cat([gamma[:-1] * lam[: n - 1, None, None, :], gamma[-1:]])
+    if n < 2:
+        a = gamma
+    else:
+        if len(lam) < n - 1:
+            raise IndexError(f"lam has {len(lam)} rows for {n} sites")
+        if isinstance(lam, (list, tuple)):  # a vector per bond, of cap entries or one
+            lam = torch.stack([v[:].expand(cap) for v in lam[: n - 1]])
+        a = torch.cat([gamma[:-1] * lam[: n - 1, None, None, :], gamma[-1:]])
     bra = a.reshape(n, dmax * cap, cap).mH.unbind(0)
     env = torch.zeros((1, 1, cap, cap), dtype=torch.complex128, device=gamma.device)
     env[0, 0, 0, 0] = 1.0
     for k, ket in enumerate(a.unbind(0)):
         t = torch.matmul(env, ket).flatten(1, 2)
         if k == site:
-            o = torch.matmul(op, ket.reshape(dmax, cap * cap)).reshape(dmax, cap, cap)
+            if op.dim() != 2:
+                raise RuntimeError(f"op must be a matrix, not {list(op.shape)}")
+            # a dimension of one, of op or of the site, stands for all of the other's
+            o = op.sum().reshape(1, 1) if dmax == 1 else op.expand(dmax, dmax)
+            o = torch.matmul(o, ket.reshape(dmax, cap * cap)).reshape(dmax, cap, cap)
             t = torch.cat([torch.matmul(env, o).flatten(1, 2), t])
         env = torch.matmul(bra[k], t)[:, None]
     return (env[0, 0, 0, 0] / env[-1, 0, 0, 0]).real
