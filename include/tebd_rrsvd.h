@@ -66,7 +66,11 @@ typedef enum {
 /* Per-problem device status bits. */
 enum {
   TEBD_DEV_NONFINITE = 1,     /* NaN/Inf met in the input or the factors     */
-  TEBD_DEV_QR_FALLBACK = 2,   /* reserved: fast QR refused, fallback taken   */
+  TEBD_DEV_QR_FALLBACK = 2,   /* a Gram-based QR was refused and a Householder
+                                 QR taken (info): any QR of size class 2 or 3
+                                 (tebd_size_class) in rrsvd_truncate and in
+                                 TEBD with precision = 1; FP64 sweeps do not
+                                 report                                      */
   TEBD_DEV_JACOBI_NOCONV = 4, /* small SVD hit its sweep limit               */
   TEBD_DEV_LAMBDA_FLOOR = 8,  /* a lambda <= lambda_floor was not inverted   */
   TEBD_DEV_CHI_BOUND = 16,    /* chi_max (or l) binds before w <= trunc_eps  */

@@ -421,8 +421,9 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   // has the basis that the Accuracy Check projects on.
   // (FP32 products keep to their own Gram-based QR, and to the Householder
   // kernels for what that does not take.)
+  const int quiet = c.chol ? 0 : QRM_QUIET;
   auto qr_step = [&](int which, bool first, bool last) -> hipError_t {
-    const int mode = (last ? QRM_STRICT : 0) | (first ? QRM_FIRST : 0) | (c.chol ? 0 : QRM_QUIET);
+    const int mode = (last ? QRM_STRICT : 0) | (first ? QRM_FIRST : 0) | quiet;
     const bool gram = c.mixed ? gram_f32_any(c, which)
                               : !first || c.chol || c.ktiles[TK_GQ_F] != 0;
     if (gram) {
@@ -474,7 +475,7 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   TIMED(PK_SKETCH_AHQ, launch_sketch(probs, c, SK_YT_FROM_Y, s));  // B^H = A^H Q
   // B^H = Q_B R_B in column order: the one-sided Jacobi on R_B^H that follows
   // converges in as many sweeps as after a pivoted QR, and the QR is cheaper.
-  TIMED(PK_QR_R, launch_gram_qr(probs, c, 1, QRM_STRICT | QRM_WANT_R, s));
+  TIMED(PK_QR_R, launch_gram_qr(probs, c, 1, QRM_STRICT | QRM_WANT_R | quiet, s));
   if (gram_on_queue(c, 1)) TIMED(PK_QR_R, launch_qr(probs, c, 1, 1, 0, s, 2));
   {
     // the small SVD works on the revealed rank, anywhere in [1, l1]; each

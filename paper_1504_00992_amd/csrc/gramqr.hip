@@ -87,6 +87,12 @@ __device__ __forceinline__ int pivot_verdict(double d, double g, bool first, dou
   return (ok ? 0 : 1) | (d >= kRelStrict * g ? 0 : 2);
 }
 
+// Whether a refused sketch sets TEBD_DEV_QR_FALLBACK: in any QR, on the tile
+// queue or by a workgroup, in the size classes 2 and 3.
+__device__ __forceinline__ bool refusal_reported(const Prob& P, int rows, int mode) {
+  return !(mode & QRM_QUIET) && qr_class(rows, P.l1) >= 2;
+}
+
 // One wavefront: G = L L^H of a 16 x 16 Hermitian tile (both triangles valid)
 // by Gaussian elimination on [G | I], both in one array: step j subtracts m_i
 // times row j from the rows i > j, m_i = G_ij / d_j, d_j = G_jj; columns k > j
@@ -552,12 +558,9 @@ __device__ __forceinline__ void gram_qr_problem(Prob& P, int which, int mode, in
     if (!again) break;
     __syncthreads();
   }
+  if (tid == 0 && failed && refusal_reported(P, rows, mode)) P.flags |= TEBD_DEV_QR_FALLBACK;
   if (first) {
-    if (tid == 0) {
-      P.chol_ok = failed ? 0 : 1;
-      if (failed && !(mode & QRM_QUIET) && qr_class(rows, P.l1) >= 2)
-        P.flags |= TEBD_DEV_QR_FALLBACK;
-    }
+    if (tid == 0) P.chol_ok = failed ? 0 : 1;
     return;
   }
   if (failed) {
@@ -804,7 +807,7 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Prob* probs, int pass, in
     if (tid == 0) {
       if (pass == 0) {
         P.chol_ok = 0;
-        if (qr_class(rows, P.l1) >= 2) P.flags |= TEBD_DEV_QR_FALLBACK;
+        if (refusal_reported(P, rows, mode)) P.flags |= TEBD_DEV_QR_FALLBACK;
       }
       P.chol_again = 0;
     }

@@ -334,7 +334,7 @@ enum {
   QRM_FIRST = 1,   // the QR of Y0 = A Omega: the Householder kernels reveal the rank of what it refuses
   QRM_STRICT = 2,  // the columns must be orthonormal to rounding (a second pass where one is not enough)
   QRM_WANT_R = 4,  // also R (into Rb, column order)
-  QRM_QUIET = 8    // a refusal is not reported (TEBD_DEV_QR_FALLBACK)
+  QRM_QUIET = 8    // a refusal is not reported (TEBD_DEV_QR_FALLBACK; else in size classes 2, 3)
 };
 hipError_t launch_gram_qr(Prob* probs, const Common& c, int which, int mode, hipStream_t s);
 // Whether any problem of the batch may take the tile queue for this sketch.

@@ -148,3 +148,29 @@ def test_around_one_problem_per_cu(count):
         assert np.max(np.abs(S[:ochi] - os_)) <= 1e-10 * os_[0]
         rec = (U[:, :ochi] * S[None, :ochi]) @ VH[:ochi]
         assert np.max(np.abs(rec - (ou * os_[None, :]) @ ovh)) <= 1e-10 * os_[0]
+
+
+def _graded(n, l, low, gen):
+    """A matrix of rank 2 l whose first singular value is 1 and the others at most
+    `low`, and a test matrix whose sketch has orthonormal columns that all
+    contain the first singular vector: A^H Q then has columns almost parallel.
+    Also its factors, and the smallest scaled pivot of that Gram matrix (the
+    squared sine between a column and those before it, by Householder QR)."""
+    s = np.concatenate([[1.0], low * np.linspace(1.0, 0.5, l - 1), low * np.linspace(0.1, 0.05, l)])
+    u, v, w = (wl.haar_isometry(k, c, gen) for k, c in ((n, 2 * l), (n, 2 * l), (l, l)))
+    a, omega = (u * s) @ v.conj().T, np.ascontiguousarray((v[:, :l] / s[:l]) @ w)
+    b = a.conj().T @ np.linalg.qr(a @ omega)[0]
+    pivot = np.min(np.abs(np.diag(np.linalg.qr(b)[1])) / np.linalg.norm(b, axis=0)) ** 2
+    return a, omega, u, s, v, pivot
+
+
+@pytest.mark.parametrize("low", [1e-2, 1e-7])
+@pytest.mark.parametrize("n,q", [(300, 0), (300, 2), (400, 0), (400, 2), (600, 0), (600, 2)])
+def test_a_refused_later_sketch_is_reported(n, q, low):
+    # l = 20: by a workgroup in QR classes 1 and 2, on the tile queue in class 3.
+    # Refused below a scaled pivot of 1e-10, and reported in classes 2 and 3
+    # whichever route refuses.
+    a, omega, u, s, v, pivot = _graded(n, 20, low, wl.rng(n + q))
+    assert (pivot < 1e-12) == (low == 1e-7) and not 1e-12 < pivot < 1e-6
+    st = rr._gpu([a], 12, 8, q, 0.0, omegas=[omega])[5]
+    assert st[0] == (_lib.DEV_QR_FALLBACK if low == 1e-7 and _lib.tebd_size_class(0, n, 20) >= 2 else 0)
