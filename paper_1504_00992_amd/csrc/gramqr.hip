@@ -95,14 +95,18 @@ __device__ __forceinline__ bool refusal_reported(const Prob& P, int rows, int mo
 
 // One wavefront: G = L L^H of a 16 x 16 Hermitian tile (both triangles valid)
 // by Gaussian elimination on [G | I], both in one array: step j subtracts m_i
-// times row j from the rows i > j, m_i = G_ij / d_j, d_j = G_jj; columns k > j
-// of a row belong to G, columns k < j to the growing inverse, each scaled by
-// d_k, and column j turns from G_ij into -G_ij = -m_i d_j (the pivot row
-// carries 2 d_j there).  On return column k < i of row i holds d_k times the
-// unit-lower inverse, the diagonal the pivots and columns k > i the pivot
-// rows.
+// times row j from the rows i > j, m_i = conj(G_ji) / d_j, d_j = G_jj; columns
+// k > j of a row belong to G, columns k < j to the growing inverse, each scaled
+// by d_k, and column j becomes -conj(G_ji) = -m_i d_j (its old entries are
+// dropped, the pivot row holds 1 there).  On return column k < i of row i holds
+// d_k times the unit-lower inverse, the diagonal the pivots and columns k > i
+// the pivot rows.
+// The inverse takes nothing from the lower triangle of G, which differs from
+// the upper one by its rounding, u |G|: with it, X R = I held to u / (smallest
+// scaled pivot) only, and so did the QR of B^H (measured with pivots of 5e-6:
+// singular values off by 4e-12 s_1, 1e-15 so, for 40 cycles a step).
 // A step is bound by its instructions (five cycles each for one wavefront, a
-// branch about twenty) and the LDS round trip, about 440 cycles, so it has no
+// branch about twenty) and the LDS round trip, about 480 cycles, so it has no
 // branch but the loop's own and leaves tests and scalings to the end.  One
 // wavefront does a whole tile: with the rows spread over eight, a barrier per
 // step and the multipliers by readlane, a step took 900.  Row j goes through
@@ -126,15 +130,18 @@ __device__ __forceinline__ void chol_tile(ZTile& w, zt* buf, int n) {
       for (int r = rj; r < 4; ++r) m[r] = buf[tk + 4 * r];
       asm volatile("" ::: "memory");
       const double inv = rcp_pos(d);
-      rv.x *= ti == j ? inv + inv : inv;
-      rv.y *= inv;
       const bool below = tk > tj;  // rows of register rj up to j stay
+      const double keep = ti == j ? 0.0 : 1.0;
+      const double rj_keep = ti == j && below ? 0.0 : 1.0;
+      rv.x = ti == j ? 1.0 : rv.x * inv;
+      rv.y = ti == j ? 0.0 : rv.y * inv;
       const zt rj_v = make_double2(below ? rv.x : 0.0, below ? rv.y : 0.0);
 #pragma unroll
-      for (int r = rj; r < 4; ++r) {  // w -= conj(m) rv
+      for (int r = rj; r < 4; ++r) {  // w -= conj(m) rv, in column j w = -conj(m)
         const zt v = r == rj ? rj_v : rv;
-        w.re[r] = fma(-m[r].x, v.x, fma(-m[r].y, v.y, w.re[r]));
-        w.im[r] = fma(-m[r].x, v.y, fma(m[r].y, v.x, w.im[r]));
+        const double k = r == rj ? rj_keep : keep;
+        w.re[r] = fma(-m[r].x, v.x, fma(-m[r].y, v.y, w.re[r] * k));
+        w.im[r] = fma(-m[r].x, v.y, fma(m[r].y, v.x, w.im[r] * k));
       }
     }
   }

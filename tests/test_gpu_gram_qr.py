@@ -174,3 +174,39 @@ def test_a_refused_later_sketch_is_reported(n, q, low):
     assert (pivot < 1e-12) == (low == 1e-7) and not 1e-12 < pivot < 1e-6
     st = rr._gpu([a], 12, 8, q, 0.0, omegas=[omega])[5]
     assert st[0] == (_lib.DEV_QR_FALLBACK if low == 1e-7 and _lib.tebd_size_class(0, n, 20) >= 2 else 0)
+
+
+@pytest.mark.parametrize("low", [1e-3, 1e-4, 2e-5, 1e-7])
+@pytest.mark.parametrize("n,q", [(300, 2), (400, 2), (600, 1), (600, 2)])
+def test_later_sketches_near_the_refusal(n, q, low):
+    # Kept down to a scaled pivot of 1e-10, else refused.  Against the exact truncation: a kept pass
+    # of pivot d perturbs the basis by u / sqrt(d) <= 1e-11 in directions that A
+    # weights with `low`, a Householder QR by u: both below 1e-13 of s_1.
+    gen = wl.rng(n + q)
+    a, omega, u, s, v, pivot = _graded(n, 20, low, gen)
+    assert not 0.5e-10 < pivot < 2e-10
+    U, S, VH, chi, w, st = rr._gpu([a], 12, 8, q, 0.0, omegas=[omega])
+    report = pivot < 1e-10 and _lib.tebd_size_class(0, n, 20) >= 2
+    assert chi[0] == 12 and st[0] == (_lib.DEV_QR_FALLBACK if report else 0)
+    assert np.max(np.abs(S[0] - s[:12])) <= 1e-13
+    assert np.max(np.abs((U[0] * S[0]) @ VH[0] - (u[:, :12] * s[:12]) @ v[:, :12].conj().T)) <= 1e-13
+    assert np.allclose(U[0].conj().T @ U[0], np.eye(12), atol=1e-12)
+    assert np.allclose(VH[0] @ VH[0].conj().T, np.eye(12), atol=1e-12)
+
+
+@pytest.mark.parametrize("low", [1e-3, 1e-4, 2e-5, 1e-7])
+@pytest.mark.parametrize("n", [300, 400, 600])
+def test_factor_of_almost_parallel_columns(n, low):
+    # no power iteration: the QR of B^H itself has the small pivots, kept in two
+    # passes or refused.  Its factor R has B's singular values to a backward
+    # error of some u s_1 either way: 1e-13 (the sketch's own error, u / low of
+    # the test matrix, enters squared).
+    gen = wl.rng(n)
+    a, omega, u, s, v, pivot = _graded(n, 20, low, gen)
+    assert not 0.5e-10 < pivot < 2e-10
+    U, S, VH, chi, w, st = rr._gpu([a], 12, 8, 0, 0.0, omegas=[omega])
+    report = pivot < 1e-10 and _lib.tebd_size_class(0, n, 20) >= 2
+    assert chi[0] == 12 and st[0] == (_lib.DEV_QR_FALLBACK if report else 0)
+    assert np.max(np.abs(S[0] - s[:12])) <= 1e-13
+    assert np.allclose(U[0].conj().T @ U[0], np.eye(12), atol=1e-12)
+    assert np.allclose(VH[0] @ VH[0].conj().T, np.eye(12), atol=1e-12)
