@@ -17,9 +17,8 @@
 //
 // Scheduling: problem sizes live on the device, so every contraction kind
 // runs as one persistent launch over a global queue of output tiles (32 x 32
-// for Theta, the sketches and U, V^H; 64 x 16 or 64 x 64 for the gate
-// groups; 64 x 64 for the others; prefix sums over problems
-// built by k_schedule).  Workgroup i takes the
+// for Theta, the sketches and U, V^H; 16 x 16 for the gate groups; 64 x 64
+// for the others; prefix sums over problems built by k_schedule).  Workgroup i takes the
 // virtual index (i mod 8) * G/8 + i / 8, so the consecutive tiles of one
 // problem, which share operand rows, land on the same XCD and its L2.
 #include "kinds.hpp"
@@ -264,7 +263,8 @@ __device__ __forceinline__ void sketch_split(Prob* probs, const int32_t* offs, i
 
 // The depth of the tiles is split between wavefronts (zgemm_tile_split16) where
 // the scheduler's verdict says so (TileKinds<Prob>::few: decided from the queue,
-// so that it does not depend on what the host knows) and none was tuned.
+// so that it does not depend on what the host knows) and none was tuned.  Both
+// give the same bits, so that a result does not depend on its companions.
 template <int WHICH>
 __global__ __launch_bounds__(256) void k_sketch(Prob* probs, const int32_t* offs, int nprob,
                                                 int tebd, int tuned) {
@@ -279,21 +279,21 @@ __global__ __launch_bounds__(256) void k_sketch(Prob* probs, const int32_t* offs
       LdRowA la{P.A, P.lda};
       LdRowB lb{P.om, P.ldom};
       StCol st{P.Y, P.m};
-      zgemm_tile<CfgSk>(M, N, P.n, m0, n0, la, lb, st, smem);
+      zgemm_tile<CfgSk, true>(M, N, P.n, m0, n0, la, lb, st, smem);
     });
   } else if (WHICH == SK_YT_FROM_Y) {
     for_each_tile<TK_SKN>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdAdjA la{P.A, P.lda};
       LdColB lb{P.Y, P.m};
       StCol st{P.Yt, P.n};
-      zgemm_tile<CfgSk>(M, N, P.m, m0, n0, la, lb, st, smem);
+      zgemm_tile<CfgSk, true>(M, N, P.m, m0, n0, la, lb, st, smem);
     });
   } else {
     for_each_tile<TK_SKM>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdRowA la{P.A, P.lda};
       LdColB lb{P.Yt, P.n};
       StCol st{P.Y, P.m};
-      zgemm_tile<CfgSk>(M, N, P.n, m0, n0, la, lb, st, smem);
+      zgemm_tile<CfgSk, true>(M, N, P.n, m0, n0, la, lb, st, smem);
     });
   }
 }
@@ -394,21 +394,21 @@ __device__ __forceinline__ void sketch_split(Prob* probs, const int32_t* offs, i
       LdRowA la{P.A, P.lda};
       LdRowB lb{P.om, P.ldom};
       StCol st{P.Y, P.m};
-      zgemm_tile_split16(M, N, P.n, m0, n0, la, lb, st, red);
+      zgemm_tile_split16<true>(M, N, P.n, m0, n0, la, lb, st, red);
     });
   } else if (WHICH == SK_YT_FROM_Y) {
     for_each_tile<TK_SKN_S>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdAdjA la{P.A, P.lda};
       LdColB lb{P.Y, P.m};
       StCol st{P.Yt, P.n};
-      zgemm_tile_split16(M, N, P.m, m0, n0, la, lb, st, red);
+      zgemm_tile_split16<true>(M, N, P.m, m0, n0, la, lb, st, red);
     });
   } else {
     for_each_tile<TK_SKM_S>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdRowA la{P.A, P.lda};
       LdColB lb{P.Yt, P.n};
       StCol st{P.Y, P.m};
-      zgemm_tile_split16(M, N, P.n, m0, n0, la, lb, st, red);
+      zgemm_tile_split16<true>(M, N, P.n, m0, n0, la, lb, st, red);
     });
   }
 }

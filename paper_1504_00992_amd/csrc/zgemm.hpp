@@ -105,8 +105,13 @@ __device__ __forceinline__ void zgemm_stage(zt* As, zt* Bs, const zt (&ra)[Cfg::
   }
 }
 
+// Depth of a quarter of K, in whole slabs of 16.
+__device__ __forceinline__ int depth_quarter(int K) { return (K + 63) / 64 * 16; }
+
 // C tile at (m0, n0) of size up to BM x BN; K loop over the whole depth.
-template <class Cfg, class LA, class LB, class ST>
+// QUARTERS: one sum per quarter of the depth, added in order: the same bits as
+// zgemm_tile_split16's.
+template <class Cfg, bool QUARTERS = false, class LA, class LB, class ST>
 __device__ void zgemm_tile(int M, int N, int K, int m0, int n0, const LA& la, const LB& lb,
                            ST& st, zt* smem) {
   zt* As = smem;
@@ -123,9 +128,36 @@ __device__ void zgemm_tile(int M, int N, int K, int m0, int n0, const LA& la, co
       accr[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
       acci[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
     }
+  constexpr int TM = QUARTERS ? Cfg::FM : 1, TN = QUARTERS ? Cfg::FN : 1;
+  static_assert(!QUARTERS || Cfg::BK == 16, "a quarter is whole slabs");
+  v4d totr[TM][TN], toti[TM][TN];  // the quarters before this one
+  if constexpr (QUARTERS)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        totr[i][j] = accr[i][j];
+        toti[i][j] = acci[i][j];
+      }
+  const int quarter = QUARTERS ? depth_quarter(K) : K;
+  int next = quarter;
   zt ra[Cfg::NA], rb[Cfg::NB];
   if (K > 0) zgemm_load<Cfg>(M, N, K, m0, n0, 0, la, lb, ra, rb);
   for (int k0 = 0; k0 < K; k0 += Cfg::BK) {
+    if constexpr (QUARTERS) {
+      if (k0 == next) {
+        next += quarter;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            totr[i][j] += accr[i][j];
+            toti[i][j] += acci[i][j];
+            accr[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+            acci[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+          }
+      }
+    }
     zgemm_stage<Cfg, LA, LB>(As, Bs, ra, rb);
     __syncthreads();
     if (k0 + Cfg::BK < K) zgemm_load<Cfg>(M, N, K, m0, n0, k0 + Cfg::BK, la, lb, ra, rb);
@@ -172,19 +204,24 @@ __device__ void zgemm_tile(int M, int N, int K, int m0, int n0, const LA& la, co
       for (int r = 0; r < 4; ++r) {
         const int row = m0 + wr * Cfg::WM + i * 16 + (lane >> 4) + 4 * r;
         const int col = n0 + wc * Cfg::WN + j * 16 + (lane & 15);
-        if (row < M && col < N) st(row, col, make_double2(accr[i][j][r], acci[i][j][r]));
+        double vr = accr[i][j][r], vi = acci[i][j][r];
+        if constexpr (QUARTERS) {
+          vr = totr[i][j][r] + vr;
+          vi = toti[i][j][r] + vi;
+        }
+        if (row < M && col < N) st(row, col, make_double2(vr, vi));
       }
 }
 
 // 16 x 16 tile of C = op(A) op(B) by the four wavefronts of a 256-thread
-// workgroup, each over every fourth k-step of 4 (wavefront w: k in
-// [4w, 4w + 4), [4w + 16, 4w + 20), ...), with the operands read by each
-// lane straight into its matrix-core registers (lane t: A[t % 16][k + t / 16]
+// workgroup, each over a quarter of the depth (QUARTERS) or over every fourth
+// k-step of 4 (wavefront w: k in [4w, 4w + 4), [4w + 16, 4w + 20), ...), with
+// the operands read by each lane straight into its matrix-core registers (lane t: A[t % 16][k + t / 16]
 // and B[k + t / 16][t % 16]), four k-steps in flight.  No LDS staging and no
 // barrier in the loop; the four partial tiles meet in LDS (red: 2048
 // doubles) and are added in wavefront order.  The chain of dependent matrix-
 // core steps is a quarter of a single wavefront's over the full depth.
-template <class LA, class LB, class ST>
+template <bool QUARTERS = false, class LA, class LB, class ST>
 __device__ void zgemm_tile_split16(int M, int N, int K, int m0, int n0, const LA& la,
                                    const LB& lb, ST& st, double* red) {
   constexpr int U = 4;  // k-steps loaded ahead
@@ -193,11 +230,14 @@ __device__ void zgemm_tile_split16(int M, int N, int K, int m0, int n0, const LA
   const bool rin = r < M, cin = c < N;
   const zt zero = make_double2(0.0, 0.0);
   v4d accr = {0.0, 0.0, 0.0, 0.0}, acci = {0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 4 * wave; k0 < K; k0 += 16 * U) {
+  const int quarter = depth_quarter(K), step = QUARTERS ? 4 : 16;  // between k-steps
+  const int from = QUARTERS ? wave_id() * quarter : 4 * wave;
+  const int to = QUARTERS && from + quarter < K ? from + quarter : K;
+  for (int k0 = from; k0 < to; k0 += step * U) {
     zt a[U], b[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int k = k0 + 16 * u + kl;
+      const int k = k0 + step * u + kl;
       a[u] = (rin && k < K) ? la(r, k) : zero;
       b[u] = (cin && k < K) ? lb(k, c) : zero;
     }

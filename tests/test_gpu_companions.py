@@ -1,0 +1,70 @@
+"""A result does not depend on what else is in the batch: the same bits alone,
+beside a few matrices or chains and beside many (so that the launches take other
+grids, tile variants and kernels' widths)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _first(mats, chi_max, p, precision):
+    import torch
+    from paper_1504_00992_amd import api
+    res = api.rrsvd_truncate(mats, chi_max, p, 2, 1e-10, 1504, 0, precision=precision)
+    torch.cuda.synchronize()
+    return [r[0].clone() for r in res]
+
+
+def _matrix_among_others(m, n, chi_max, p, precision, others):
+    # the matrix comes first, so that its test matrix is the same
+    import torch
+    gen = wl.rng(m)
+
+    def mat(rows, cols):
+        a = wl.known_spectrum(rows, cols, np.exp(-np.arange(min(rows, cols)) / 12.0), gen)
+        return torch.from_numpy(a).cuda()
+    a = mat(m, n)
+    alone = _first([a], chi_max, p, precision)
+    for rows, cols, count in others:
+        for x, y in zip(alone, _first([a] + [mat(rows, cols)] * count, chi_max, p, precision)):
+            assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("m,n,chi_max,p", [(30, 28, 8, 6), (96, 80, 24, 10), (300, 400, 48, 10)])
+def test_a_matrix_among_others(m, n, chi_max, p, precision):
+    # fewer than the 400 tiles to which sketch products split their depth, and more
+    _matrix_among_others(m, n, chi_max, p, precision,
+                         [(28, 28, 300), (260, 250, 1), (260, 250, 70), (900, 800, 20)])
+
+
+@pytest.mark.parametrize("mode", [0, 2, 3])
+@pytest.mark.parametrize("model", ["tfim", "spin_boson"])
+def test_a_chain_among_others(model, mode):
+    # 16 chains whose bonds grow: sweeps of up to 1500 tiles of sketch products,
+    # those of one chain stay below 100
+    import torch
+    from paper_1504_00992_amd import api, models as pm
+    dims, hb = pm.transverse_ising(40) if model == "tfim" else pm.spin_boson(24, 8)
+    state = []
+    for chains in (1, 16):
+        dev = api.DeviceMPS.product_state(chains, dims, [0] * len(dims), 32)
+        drv = api.TEBD(dev, hb, 0.1, 32, p=6, q=2, trunc_eps=1e-12, seed=11, adaptive=mode)
+        for _ in range(20):
+            drv.step()
+        torch.cuda.synchronize()
+        state.append((dev.gamma[0].clone(), dev.lam[0].clone(), dev.chi[0].clone()))
+    assert int(state[0][2].max()) >= 8
+    for x, y in zip(*state):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("m,n,chi_max,p", [(80, 90, 100, 100), (140, 150, 60, 68), (500, 450, 64, 10),
+                                           (70, 75, 190, 10)])
+def test_a_wide_small_svd_among_others(m, n, chi_max, p, precision):
+    # l = 80, 128, 74, 70, beside widths up to 200: the small SVD's kernels hold two
+    # or four rows of a column per lane, by the widest problem
+    _matrix_among_others(m, n, chi_max, p, precision, [(28, 28, 300), (260, 250, 1), (900, 800, 20)])
