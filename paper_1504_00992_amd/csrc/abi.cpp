@@ -615,9 +615,15 @@ tebd_status enqueue_sweep(const tebd_mps* mps, const tebd_z* gates, int64_t gate
 // Static scratch of rrsvd_truncate_noalloc, one copy per device (the code
 // object's global), used through the address hipGetSymbolAddress gives on
 // each device: the array's name is not a device address in host code.
-// 64 MiB and, outside that count, 32 bytes of each descriptor and its queue
-// entries (batches that filled the scratch when those were smaller still fit).
+// 64 MiB and, outside that count, what descriptors and queues have grown by since
+// the limit was set (batches that filled the scratch then still fit).
 constexpr size_t kScratchBytes = size_t(64) << 20, kScratchSpare = size_t(1) << 20;
+size_t header_growth(int64_t batch) {
+  constexpr size_t prob = 448, kinds = 16;
+  const size_t b = size_t(batch);
+  return align256(b * sizeof(Prob)) - align256(b * prob) + align256(sched_bytes(batch)) -
+         align256(kinds * (b + 1) * sizeof(int32_t));
+}
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSpare];
 
 constexpr int kMaxScratchDevices = 64;
@@ -749,7 +755,7 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
   st = tebd_workspace_size(nullptr, batch, m, n, prm, &need);
   if (st != TEBD_OK) return st;
   if (noalloc) {
-    if (need > kScratchBytes + std::min(kScratchSpare, size_t(batch) * 32))
+    if (need > kScratchBytes + std::min(kScratchSpare, header_growth(batch)))
       return fail(TEBD_ERR_WORKSPACE,
                   "the batch needs %zu bytes of scratch; rrsvd_truncate_noalloc has %zu "
                   "(use rrsvd_truncate with a workspace)", need, kScratchBytes);

@@ -84,3 +84,17 @@ def test_noalloc_matches_workspace_entry_point_twice():
         ref = _run(mats, chi_max, 10, 2, 1e-10, False, sid)
         got = _run(mats, chi_max, 10, 2, 1e-10, True, sid)
         _same(ref, got)
+
+
+@pytest.mark.parametrize("n3,fits", [(3260, True), (3261, False)])
+def test_a_batch_that_fills_the_scratch(n3, fits):
+    # three matrices whose 64 MiB were full to the byte when the limit was set: the
+    # growth of descriptors and queues since is outside it
+    from paper_1504_00992_amd import _lib
+    mats = _mats([(437, 364), (882, 561), (1082, n3)], 3)
+    if fits:
+        _same(_run(mats, 190, 10, 1, 1e-10, False, 5), _run(mats, 190, 10, 1, 1e-10, True, 5))
+    else:
+        with pytest.raises(_lib.TebdError) as e:
+            _run(mats, 190, 10, 1, 1e-10, True, 5)
+        assert e.value.status == _lib.TEBD_ERR_WORKSPACE
