@@ -210,3 +210,18 @@ def test_factor_of_almost_parallel_columns(n, low):
     assert np.max(np.abs(S[0] - s[:12])) <= 1e-13
     assert np.allclose(U[0].conj().T @ U[0], np.eye(12), atol=1e-12)
     assert np.allclose(VH[0] @ VH[0].conj().T, np.eye(12), atol=1e-12)
+
+
+@pytest.mark.parametrize("n,chi_max,p,decay", [(400, 12, 8, 0.4), (400, 2, 3, 2.0), (400, 70, 3, 0.1),
+                                               (400, 70, 3, 0.15)])
+def test_a_kept_sketch_of_one_pass_is_not_orthonormal(n, chi_max, p, decay):
+    # as test_second_pass_of_an_ill_conditioned_sketch, but kept for sure: kappa of
+    # A Omega is 1e4 to 1e6, and no refusal is reported (QR classes 2 and 3, by a
+    # workgroup and on the tile queue), so that the second pass is what makes
+    # the result orthonormal to 1e-12 (one pass: u kappa^2 >= 1e-8)
+    assert _lib.tebd_size_class(0, n, chi_max + p) >= 2
+    gen = wl.rng(int(100 * decay))
+    a = wl.known_spectrum(n, n - 20, np.exp(-decay * np.arange(n - 20)), gen)
+    res = rr._gpu([a], chi_max, p, 0, 0.0)
+    assert not res[5][0] & _lib.DEV_QR_FALLBACK
+    rr._compare([a], res, chi_max, p, 0, 0.0)
