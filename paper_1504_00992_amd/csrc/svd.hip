@@ -115,6 +115,14 @@ __device__ __forceinline__ bool pairs_below_tol(const zt* C, int S, int l, doubl
   return __syncthreads_or(bad) == 0;
 }
 
+// Whether singular value a of column i comes before b of column j: descending,
+// equal ones by column, NaN last (every column has a place of its own: places
+// without a column would be read from uninitialised LDS).
+__device__ __forceinline__ bool sorts_before(double a, int i, double b, int j) {
+  const bool na = a != a, nb = b != b;
+  return a > b || (nb && !na) || ((a == b || (na && nb)) && i < j);
+}
+
 // Column norms, descending order, and the sorted outputs X, W, sig.
 template <int NT>
 __device__ __forceinline__ void jacobi_finish(Prob& P, const zt* C, const zt* J, int l,
@@ -131,10 +139,7 @@ __device__ __forceinline__ void jacobi_finish(Prob& P, const zt* C, const zt* J,
   for (int j = tid; j < l; j += NT) {
     const double sj = sig_s[j];
     int rank = 0;
-    for (int i = 0; i < l; ++i) {
-      const double si = sig_s[i];
-      rank += (si > sj) || (si == sj && i < j);
-    }
+    for (int i = 0; i < l; ++i) rank += sorts_before(sig_s[i], i, sj, j);
     perm_s[rank] = j;
   }
   __syncthreads();
@@ -449,10 +454,7 @@ __device__ __forceinline__ void svd_pairs(Prob& P, int l, double eps, int tebd,
   auto out = [&](int c, double sv, const JacColumn<RPR>& v) {
     if (c < 0 || c >= l) return;
     int rank = 0;
-    for (int i = h; i < l; i += G) {
-      const double si = sig_s[i];
-      rank += (si > sv) || (si == sv && i < c);
-    }
+    for (int i = h; i < l; i += G) rank += sorts_before(sig_s[i], i, sv, c);
     rank = static_cast<int>(group_sum(double(rank), G));
     const double inv = sv > 0.0 ? 1.0 / sv : 0.0;
 #pragma unroll

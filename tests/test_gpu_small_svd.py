@@ -80,3 +80,19 @@ def test_rank_modes_agree_bitwise_beyond_64_columns(chi, cap, chi_max):
     assert int(out[0][2].max()) > 64
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("l", [20, 60, 74, 128, 200])
+def test_a_factor_that_overflowed(l):
+    # finite entries of 1e200 and a test matrix of 1e-200: A Omega is harmless and
+    # keeps its rank, A^H Q and every column of the factor are not finite.  Reported,
+    # and the matrix before it keeps its bits.
+    gen = wl.rng(l)
+    n = l + 60
+    a = wl.known_spectrum(n, n - 5, np.linspace(1.0, 0.5, n - 5), gen)
+    omega = np.ascontiguousarray(wl.ginibre(n - 5, l, gen))
+    alone = rr._gpu([a], l - 10, 10, 1, 1e-10, omegas=[omega])
+    U, S, VH, chi, w, st = rr._gpu([a, a * 1e200], l - 10, 10, 1, 1e-10, omegas=[omega, omega * 1e-200])
+    assert st[0] == alone[5][0] and st[1] & _lib.DEV_NONFINITE and 1 <= chi[1] <= l - 10
+    for x, y in zip((U[0], S[0], VH[0]), (r[0] for r in alone[:3])):
+        assert np.array_equal(x, y)
