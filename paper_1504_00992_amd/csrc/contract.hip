@@ -348,7 +348,10 @@ hipError_t launch_sketch_f32(Prob* probs, const Common& c, int which, hipStream_
 }
 
 // The FP64 sketch products on 64 x 64 output tiles (fewer operand reloads
-// for large problems; chosen per launch by the autotune cache).
+// for large problems; chosen per launch by the autotune cache).  The sums by
+// quarters of the depth, so that every variant gives the same bits, fit the 256
+// registers that two waves per SIMD leave: 8 x 2048^2, l = 110, 3.65 ms (3.71
+// with one sum), 2 x 4900^2, l = 200, 15.4 (15.2).
 template <int WHICH, class Cfg, int KM, int KN>
 __device__ __forceinline__ void sketch_tiles(Prob* probs, const int32_t* offs, int nprob, int tebd,
                                              zt* smem) {
@@ -357,28 +360,28 @@ __device__ __forceinline__ void sketch_tiles(Prob* probs, const int32_t* offs, i
       LdRowA la{P.A, P.lda};
       LdRowB lb{P.om, P.ldom};
       StCol st{P.Y, P.m};
-      zgemm_tile<Cfg>(M, N, P.n, m0, n0, la, lb, st, smem);
+      zgemm_tile<Cfg, true>(M, N, P.n, m0, n0, la, lb, st, smem);
     });
   } else if (WHICH == SK_YT_FROM_Y) {
     for_each_tile<KN>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdAdjA la{P.A, P.lda};
       LdColB lb{P.Y, P.m};
       StCol st{P.Yt, P.n};
-      zgemm_tile<Cfg>(M, N, P.m, m0, n0, la, lb, st, smem);
+      zgemm_tile<Cfg, true>(M, N, P.m, m0, n0, la, lb, st, smem);
     });
   } else {
     for_each_tile<KM>(probs, offs, nprob, tebd, [&](Prob& P, int M, int N, int m0, int n0, int) {
       LdRowA la{P.A, P.lda};
       LdColB lb{P.Yt, P.n};
       StCol st{P.Y, P.m};
-      zgemm_tile<Cfg>(M, N, P.n, m0, n0, la, lb, st, smem);
+      zgemm_tile<Cfg, true>(M, N, P.n, m0, n0, la, lb, st, smem);
     });
   }
 }
 
 template <int WHICH>
-__global__ __launch_bounds__(256) void k_sketch_wide(Prob* probs, const int32_t* offs, int nprob,
-                                                     int tebd) {
+__global__ __launch_bounds__(256, 2) void k_sketch_wide(Prob* probs, const int32_t* offs,
+                                                        int nprob, int tebd) {
   __shared__ zt smem[Cfg64::lds_elems];
   sketch_tiles<WHICH, Cfg64, TK_SKM_W, TK_SKN_W>(probs, offs, nprob, tebd, smem);
 }

@@ -755,9 +755,10 @@ __global__ __launch_bounds__(256) void k_gram(Prob* probs, const int32_t* offs, 
 }
 
 // The sum of the partial Gram matrices, Cholesky and inverse; X = L^-1 goes
-// to C and what follows it (row-major, ld padded to whole blocks; a sketch of
-// the queue has at least 18 columns, and the padded matrix fits the four l x l
-// buffers from C on).
+// to C and what follows it (row-major, ld padded to whole blocks).  It fits the
+// four buffers from C on, which have room for the l1 x l1 the pass began with: a
+// sketch of the queue has l1 >= 8 (kGramQueueMinL), where one block of 16 x 16 is
+// 4 x 8 x 8, and (16 ceil(l1 / 16))^2 <= 4 l1^2 beyond.
 constexpr int kCholThreads = 512, kCholWaves = kCholThreads / 64;
 
 template <int WHICH>

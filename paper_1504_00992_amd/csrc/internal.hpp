@@ -45,7 +45,7 @@ struct Prob {
   // Gram-based QR: kGram* bits (where its steps run), 1 while the current QR
   // needs no Householder kernel, and 1 when its second pass is wanted
   int32_t chol, chol_ok, chol_again;
-  int32_t jac;                       // wide small SVD: JacBits of its sweeps
+  int32_t jac;                       // wide small SVD: what its sweeps did (bits: sweep_ended)
   // Gate groups (TEBD): consecutive problems of one bond that share its gate
   // form one product G [Theta_1 | Theta_2 | ...] over all their columns.
   // gtot: the group's columns (every member), gn: members (the first member

@@ -70,13 +70,14 @@ struct TileKinds<Prob> {
   // launch's time; and those of a sweep whose largest bond has over 2.5 times
   // the average's tiles, where such chains are its end, up to 1000 tiles.
   // Measured, the six products of a truncation, 32 x 32 / split: 96 x 80, l = 34
-  // (9 tiles) 45 / 30 us; 1 x 2048^2, l = 74 (192 tiles) 881 / 540; 4 x 1024^2
-  // (384) 612 / 502; 60 x 200^2, l = 30 (420) 154 / 165; 120 x 200^2 (840) 251 /
-  // 294; 400 x 100^2 (1600) 242 / 280.  Sweeps of equal bonds 0.51 / 0.74 ms (8
-  // chains of 40 spins, chi = 33); 16 chains whose front moves through, split
-  // to 400 / 1000 tiles 45.8 / 41.7 ms (100 sites, 200 steps) and 0.22 / 0.19
-  // (60 sites); to 4000 tiles the first is 37.9, but a step of 16 x 100 sites
-  // at chi = 19 goes from 0.42 to 0.47.
+  // (9 tiles) 51 / 31 us; 1 x 2048^2, l = 74 (192 tiles) 894 / 549; 4 x 1024^2
+  // (384) 622 / 526; 60 x 200^2, l = 30 (420) 159 / 168; 120 x 200^2 (840) 254 /
+  // 290; 400 x 100^2 (1600) 257 / 271.  Sweeps of 16 chains whose front moves
+  // through, split to 400 / 1000 tiles 45.8 / 41.9 ms (100 sites, 200 steps) and
+  // 0.22 / 0.20 (60 sites); to 4000 tiles the first was 37.9, but a step of 16 x
+  // 100 sites at chi = 19 went from 0.42 to 0.47.  The factor, 1.25 / 2.5 / 5: the
+  // first 40.7 / 41.9 / 47.6 ms, the second 0.15 / 0.20 / 0.23, and 8 chains of 40
+  // spins with equal bonds (chi = 33) 0.65 / 0.52 / 0.52.
   static constexpr int rule(int kind) { return kind == TK_SKM ? 0 : kind == TK_SKN ? 1 : -1; }
   static __host__ __device__ bool few(int total, int most, int nprob, int tebd) {
     return total <= 400 || (tebd && total <= 1000 && 2ll * most * nprob > 5ll * total);

@@ -68,3 +68,27 @@ def test_a_wide_small_svd_among_others(m, n, chi_max, p, precision):
     # l = 80, 128, 74, 70, beside widths up to 200: the small SVD's kernels hold two
     # or four rows of a column per lane, by the widest problem
     _matrix_among_others(m, n, chi_max, p, precision, [(28, 28, 300), (260, 250, 1), (900, 800, 20)])
+
+
+def test_tile_variants_give_the_same_bits():
+    # the tuned variants of the sketch products (32 x 32, 64 x 64 and split-depth
+    # 16 x 16 tiles), which are chosen by the largest matrix of a batch; depths
+    # around the quarters' slabs of 16 and below one
+    import torch
+    from paper_1504_00992_amd import _lib, api
+    gen = wl.rng(31)
+    shapes = [(300, 200), (700, 650), (64, 65), (63, 128), (129, 17), (16, 15), (80, 49), (5, 3)]
+    mats = [torch.from_numpy(wl.known_spectrum(m, n, np.exp(-np.arange(min(m, n)) / 9.0), gen)).cuda()
+            for m, n in shapes]
+    outs = []
+    try:
+        for v in (-1, 0, 1, 2):
+            assert _lib.tebd_tune_set(0, 700, 74, v) == 0
+            U, S, VH, chi, w, st = api.rrsvd_truncate(mats, 64, 10, 2, 1e-10, 1504, 0)
+            torch.cuda.synchronize()
+            outs.append([*U, *S, *VH, chi, w, st])
+    finally:
+        _lib.tebd_tune_set(0, 700, 74, -1)
+    for o in outs[1:]:
+        for x, y in zip(outs[0], o):
+            assert torch.equal(x, y)
