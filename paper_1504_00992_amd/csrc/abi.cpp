@@ -475,8 +475,17 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   TIMED(PK_SKETCH_AHQ, launch_sketch(probs, c, SK_YT_FROM_Y, s));  // B^H = A^H Q
   // B^H = Q_B R_B in column order: the one-sided Jacobi on R_B^H that follows
   // converges in as many sweeps as after a pivoted QR, and the QR is cheaper.
-  TIMED(PK_QR_R, launch_gram_qr(probs, c, 1, QRM_STRICT | QRM_WANT_R | quiet, s));
-  if (gram_on_queue(c, 1)) TIMED(PK_QR_R, launch_qr(probs, c, 1, 1, 0, s, 2));
+  // (with FP32 products the Householder kernels take what the Gram refuses, and in
+  // sweeps all of the register classes: one truncation 60 x 60 of rank 6, l = 26,
+  // 437 us with the Householder QR inside k_gram_qr; a sweep of such bonds 12 us of
+  // k_qr_reg against 33)
+  {
+    const bool some = !c.mixed || !c.tebd || gram_f32_any(c, 1);
+    const int leave = !c.mixed ? 0 : QRM_LEAVE | (c.tebd ? QRM_LARGE : 0);
+    if (some) TIMED(PK_QR_R, launch_gram_qr(probs, c, 1, QRM_STRICT | QRM_WANT_R | quiet | leave, s));
+    if (c.mixed || gram_on_queue(c, 1))
+      TIMED(PK_QR_R, launch_qr(probs, c, 1, 1, 0, s, some ? 2 : 0));
+  }
   {
     // the small SVD works on the revealed rank, anywhere in [1, l1]; each
     // launch ends with the truncation of its problems

@@ -767,7 +767,7 @@ hipError_t launch_qr(Prob* probs, const Common& c, int which, int want_r, int pi
   const int hi = qr_class(rows_max, c.lmax);
   // gate 2 of a QR that every sketch took the Gram in: only sketches of the
   // tile queue's size may be left, in their classes
-  if (gate == 2 && !pivot && (want_r || !c.mixed)) {
+  if (gate == 2 && !pivot && !c.mixed) {
     int least = 3;
     for (int l = c.lmin; l <= c.lmax && least > lo; ++l) {
       const int rows = std::max(rows_min, gram_queue_rows(l));

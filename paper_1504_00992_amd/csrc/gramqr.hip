@@ -570,6 +570,10 @@ __device__ __forceinline__ void gram_qr_problem(Prob& P, int which, int mode, in
     if (tid == 0) P.chol_ok = failed ? 0 : 1;
     return;
   }
+  if (failed && (mode & QRM_LEAVE) && qr_class(rows, P.l1) < 2) {
+    if (tid == 0) P.chol_ok = 0;
+    return;
+  }
   if (failed) {
     __syncthreads();
     zt* rdiag = smem;
@@ -580,6 +584,12 @@ __device__ __forceinline__ void gram_qr_problem(Prob& P, int which, int mode, in
   if (want_r)
     for (int c = tid; c < l; c += kGqThreads) P.piv[c] = c;
   if (tid == 0) P.chol_ok = 1;
+}
+
+// Whether a sketch goes to the Householder kernels without an attempt.
+__device__ __forceinline__ bool not_tried(const Prob& P, int rows, int mode) {
+  return ((mode & QRM_FIRST) && !(P.chol & kGramFirst)) ||
+         ((mode & QRM_LARGE) && qr_class(rows, P.l1) < 2);
 }
 
 // The same by one wavefront, for l <= 16 columns of at most 64 rows (most
@@ -593,7 +603,7 @@ __device__ __forceinline__ bool gram_qr_small(Prob& P, int which, int mode, zt* 
   if (l == 0) return true;
   if (l > 16 || rows > kGqSmallRows) return false;
   const bool first = mode & QRM_FIRST, want_r = mode & QRM_WANT_R;
-  if (first && !(P.chol & kGramFirst)) {
+  if (not_tried(P, rows, mode)) {
     if (lane == 0) P.chol_ok = 0;
     return true;
   }
@@ -713,7 +723,7 @@ __global__ __launch_bounds__(kGqThreads) void k_gram_qr(Prob* probs, const int32
       if (p < 0) continue;
       Prob& P = probs[p];
       if (P.l == 0 || (P.chol & (which ? kGramTileN : kGramTileM))) continue;
-      if ((mode & QRM_FIRST) && !(P.chol & kGramFirst)) {
+      if (not_tried(P, which ? P.n : P.m, mode)) {
         if (threadIdx.x == 0) P.chol_ok = 0;
         continue;
       }

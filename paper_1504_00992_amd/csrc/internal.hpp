@@ -334,6 +334,11 @@ enum {
   QRM_FIRST = 1,   // the QR of Y0 = A Omega: the Householder kernels reveal the rank of what it refuses
   QRM_STRICT = 2,  // the columns must be orthonormal to rounding (a second pass where one is not enough)
   QRM_WANT_R = 4,  // also R (into Rb, column order)
+  // FP32 products: their rounding fills up the columns beyond a problem's rank,
+  // and A^H of those is almost parallel: the QR of B^H refuses such problems, and
+  // leaves them to the Householder kernels in the register classes 0 and 1
+  QRM_LEAVE = 16,
+  QRM_LARGE = 32,  // ... without an attempt there (sweeps, whose bonds are such while they grow)
   QRM_QUIET = 8    // a refusal is not reported (TEBD_DEV_QR_FALLBACK; else in size classes 2, 3)
 };
 hipError_t launch_gram_qr(Prob* probs, const Common& c, int which, int mode, hipStream_t s);

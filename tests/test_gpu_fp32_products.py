@@ -96,3 +96,57 @@ def test_refused_sketches_of_fp32_products(chi_max):
         u = u[:, s > 0]
         assert np.allclose(u.conj().T @ u, np.eye(u.shape[1]), atol=1e-12)
         assert np.allclose(vh @ vh.conj().T, np.eye(c), atol=1e-12)
+
+
+def _kernels(run):
+    import torch
+    from paper_1504_00992_amd import _lib
+    torch.cuda.synchronize()
+    _lib.tebd_profile_enable(True)
+    try:
+        run()
+        torch.cuda.synchronize()
+        return {k: v[1] for k, v in _lib.tebd_profile_read().items() if k.startswith("k_")}
+    finally:
+        _lib.tebd_profile_enable(False)
+
+
+@pytest.mark.parametrize("m,n,rank,chi_max,p", [(30, 28, 4, 10, 6), (60, 60, 6, 16, 10), (96, 80, 10, 24, 10),
+                                                (150, 140, 10, 38, 10), (400, 400, 10, 10, 10)])
+def test_rank_deficient_matrices_with_fp32_products(m, n, rank, chi_max, p):
+    # the FP32 rounding fills up the sketch, and the QR of B^H refuses the columns
+    # beyond the rank: register classes (up to 150 x 140) are left to their
+    # Householder kernel, which then runs the four QRs of the power iterations and this one
+    import torch
+    import test_gpu_rrsvd as rr
+    import workloads as wl
+    from paper_1504_00992_amd import _lib, api
+    gen = wl.rng(m)
+    a = wl.known_spectrum(m, n, np.linspace(1.0, 0.3, rank), gen)
+    out = []
+    launches = _kernels(lambda: out.extend(api.rrsvd_truncate([torch.from_numpy(a).cuda()], chi_max, p, 2, 1e-10,
+                                                              rr.SEED, 0, precision=1)))
+    cls = _lib.tebd_size_class(0, m, chi_max + p)
+    if cls < 2:
+        assert sum(v for k, v in launches.items() if k.startswith("k_qr_reg") and k.endswith("false>")) == 5
+    U, S, VH, chi, w, st = out
+    ou, os_, ovh, ochi, ow, ost = rr._oracle(a, 0, chi_max, p, 2, 1e-10)
+    c = int(chi[0])
+    assert c == ochi == rank and bool(int(st[0]) & _lib.DEV_QR_FALLBACK) == (cls >= 2)
+    u, s, vh = U[0].cpu().numpy()[:, :c], S[0].cpu().numpy()[:c], VH[0].cpu().numpy()[:c]
+    assert np.max(np.abs(s - os_)) <= 1e-5 * os_[0]
+    assert np.max(np.abs((u * s) @ vh - (ou * os_) @ ovh)) <= 1e-5 * os_[0]
+    assert np.allclose(u.conj().T @ u, np.eye(c), atol=1e-12)
+    assert np.allclose(vh @ vh.conj().T, np.eye(c), atol=1e-12)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+def test_sweeps_with_fp32_products_use_no_gram_in_the_register_classes(mode):
+    # their bonds are rank deficient while they grow
+    from paper_1504_00992_amd import api, models as pm
+    dims, hb = pm.spin_boson(12, 4)
+    dev = api.DeviceMPS.product_state(2, dims, [0] * 12, 16)
+    drv = api.TEBD(dev, hb, 0.1, 16, p=6, q=2, trunc_eps=1e-10, seed=5, adaptive=mode, precision=1)
+    launches = _kernels(lambda: [drv.step() for _ in range(3)])
+    assert not any(k.startswith("k_gram") for k in launches)
+    assert int(drv.ws.status.max()) & ~(16 | 64 | 128) == 0
