@@ -17,6 +17,7 @@
 #include <mutex>
 #include <vector>
 
+#include "householder.hpp"
 #include "internal.hpp"
 #include "kinds.hpp"
 
@@ -374,8 +375,11 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
     if (e != hipSuccess) return e; \
   } while (0)
 #define TIMED(kind, call) TRY(timed(kind, s, [&]() { return (call); }))
-  // (the sweep planner marks the problems of a sweep's first pass itself)
-  if (c.chol && (c.pass2 || !c.tebd)) TIMED(PK_SCHEDULE, launch_chol_mark(probs, c, s));
+  // (the routes of a truncation and of a sweep's first pass are in their
+  // descriptors; the second pass is wider, which matters where a large sketch may be)
+  if (c.chol && c.pass2 &&
+      (gram_f32_any(c, 0) || gram_f32_any(c, 1) || gram_on_queue(c, 0) || gram_on_queue(c, 1)))
+    TIMED(PK_SCHEDULE, launch_chol_mark(probs, c, s));
   TIMED(PK_SCHEDULE, launch_schedule(probs, c, s));
   if (c.bounds_dev) TRY(bounds_ready(s));
   if (c.tebd) {
@@ -695,6 +699,7 @@ __global__ void k_noalloc_desc(DescArgs a) {
   P.kcap = a.chi_max;
   P.k1 = a.chi_max;
   P.l1 = P.l2 = l;
+  P.chol = gram_bits(P.m, P.n, l, true, true, a.precision != 0);
   P.pid = b;
   P.mixed = a.precision;
   carve_slab(P, o.slab, o.m, o.n, l, 0, a.precision, kFrobSlices);
@@ -878,6 +883,7 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
     P.kcap = prm->chi_max;
     P.k1 = prm->chi_max;
     P.l1 = P.l2 = P.l;
+    P.chol = gram_bits(P.m, P.n, P.l, true, true, prm->precision != 0);
     P.pid = int32_t(b);
     P.mixed = prm->precision;
     carve_slab(P, slab, m[b], n[b], P.l, 0, prm->precision, kFrobSlices);

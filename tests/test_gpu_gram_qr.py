@@ -225,3 +225,20 @@ def test_a_kept_sketch_of_one_pass_is_not_orthonormal(n, chi_max, p, decay):
     res = rr._gpu([a], chi_max, p, 0, 0.0)
     assert not res[5][0] & _lib.DEV_QR_FALLBACK
     rr._compare([a], res, chi_max, p, 0, 0.0)
+
+
+@pytest.mark.parametrize("adaptive", [0, 1, 2])
+def test_no_launch_marks_the_routes_of_small_problems(adaptive):
+    # the routes of a truncation are in its descriptors, and the second pass of an
+    # FP32-product sweep needs them anew only where a sketch may be a large one
+    import torch
+    from test_gpu_fp32_products import _kernels
+    from paper_1504_00992_amd import api, models as pm
+    gen = wl.rng(5)
+    mats = [torch.from_numpy(wl.known_spectrum(m, n, np.exp(-np.arange(min(m, n)) / 9.0), gen)).cuda()
+            for m, n in ((1, 1), (40, 30), (400, 300))]
+    dims, hb = pm.transverse_ising(8)
+    dev = api.DeviceMPS.product_state(1, dims, [0] * 8, 16)
+    drv = api.TEBD(dev, hb, 0.1, 16, p=4, q=1, trunc_eps=1e-10, seed=5, adaptive=adaptive, precision=1)
+    launches = _kernels(lambda: (api.rrsvd_truncate(mats, 30, 10, 1, 1e-10), drv.step()))
+    assert "k_chol_mark" not in launches
