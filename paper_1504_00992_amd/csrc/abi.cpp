@@ -414,8 +414,8 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   // Every QR after the first is Gram-based: its columns are graded like the
   // singular values, and scaled to unit length they are well conditioned.
   // The first one's are not; in the standalone call it tries the Gram (which
-  // then keeps every column, as the pivoted QR would), and the pivoted
-  // Householder kernels take what that refuses.  In a sweep, whose bonds are
+  // then keeps every column, as the pivoted QR would) beyond kGramFirstMinL
+  // columns, and the pivoted Householder kernels take what that refuses.  In a sweep, whose bonds are
   // rank deficient while they grow, it does for the bonds at capacity and the
   // sketches of QR class 3 (plan_item): an attempt costs 27 us against 84 us of
   // Householder (64 x 42), 60 against 160 (LDS), 80 against 1900 (128 x 74,
@@ -429,7 +429,7 @@ hipError_t run_pipeline(Prob* probs, Common& c, hipStream_t s) {
   auto qr_step = [&](int which, bool first, bool last) -> hipError_t {
     const int mode = (last ? QRM_STRICT : 0) | (first ? QRM_FIRST : 0) | quiet;
     const bool gram = c.mixed ? gram_f32_any(c, which)
-                              : !first || c.chol || c.ktiles[TK_GQ_F] != 0;
+                              : !first || c.ktiles[TK_GQ_F] != 0;
     if (gram) {
       const hipError_t er = timed(PK_QR, s, [&]() {
         return c.mixed ? launch_gram_f32(probs, c, which, s) : launch_gram_qr(probs, c, which, mode, s);
@@ -840,6 +840,7 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
       known[TK_SKN_W] += tiles_of<TK_SKN_W>(n[b], l);
       known[TK_SKM_S] += tiles_of<TK_SKM_S>(m[b], l);
       known[TK_SKN_S] += tiles_of<TK_SKN_S>(n[b], l);
+      known[TK_GQ_F] += gram_bits(int(m[b]), int(n[b]), int(l), true, true, false) & kGramFirst ? 1 : 0;
     }
     {
       const int64_t tm = (m[b] + 63) / 64, tn = (n[b] + 63) / 64;
@@ -912,7 +913,7 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
   }
   c.offs = reinterpret_cast<int32_t*>(base + align256(size_t(batch) * sizeof(Prob)));
   c.grid = persistent_grid(tiles);
-  for (const int k : {TK_SKM, TK_SKN, TK_SKM_W, TK_SKN_W, TK_SKM_S, TK_SKN_S})
+  for (const int k : {TK_SKM, TK_SKN, TK_SKM_W, TK_SKN_W, TK_SKM_S, TK_SKN_S, TK_GQ_F})
     c.ktiles[k] = int32_t(std::min<int64_t>(known[k], kKnownGridMax));
   c.split[0] = TileKinds<Prob>::few(c.ktiles[TK_SKM], 0, c.nprob, 0);
   c.split[1] = TileKinds<Prob>::few(c.ktiles[TK_SKN], 0, c.nprob, 0);

@@ -594,8 +594,8 @@ __device__ __forceinline__ bool not_tried(const Prob& P, int rows, int mode) {
 
 // The same by one wavefront, for l <= 16 columns of at most 64 rows (most
 // bonds of a sweep): one Gram tile, one factorisation, no barrier.  False
-// when the workgroup has to do it (refused, or a second pass is wanted);
-// nothing is written then that it does not write again.
+// when the workgroup has to do it (a later QR that is refused, or a second pass
+// is wanted); nothing is written then that it does not write again.
 __device__ __forceinline__ bool gram_qr_small(Prob& P, int which, int mode, zt* xs) {
   constexpr int NS = kGqSmallRows / 16;
   const int lane = threadIdx.x & 63, ti = lane & 15, tk = lane >> 4;
@@ -655,6 +655,10 @@ __device__ __forceinline__ bool gram_qr_small(Prob& P, int which, int mode, zt* 
   chol_tile(g, xs, l);
   const double gmax = first ? largest_of(gd, l) : 0.0;
   const int flags = chol_tile_end(g, 0, l, gd, first, gmax, want_r ? P.Rb : nullptr, l);
+  if (first && (flags & 1)) {  // the pivoted Householder QR is next (class 0: no report)
+    if (lane == 0) P.chol_ok = 0;
+    return true;
+  }
   if ((flags & 1) || ((mode & QRM_STRICT) && (flags & 2))) return false;
   asm volatile("" ::: "memory");  // the diagonal is read
   tile_store(xs, 17, g);

@@ -56,7 +56,7 @@ __host__ __device__ __forceinline__ int qr_class(int rows, int l) {
 // then only serve the QR of B^H.
 __host__ __device__ __forceinline__ int gram_bits(int m, int n, int l, bool queue, bool first,
                                                   bool mixed) {
-  int b = first ? kGramFirst : 0;
+  int b = first && (l > kGramFirstMinL || qr_class(m, l) >= 2) ? kGramFirst : 0;
   if (queue && gram_queue_size(m, l)) b |= kGramTileM;
   if (queue && gram_queue_size(n, l)) b |= kGramTileN;
   if (mixed && qr_class(m, l) >= 2) b |= kGramF32M;

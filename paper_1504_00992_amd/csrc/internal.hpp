@@ -282,6 +282,12 @@ __host__ __device__ inline bool gram_queue_size(int64_t rows, int64_t l) {
 inline int gram_queue_rows(int l) {
   return l >= kGramQueueMinL ? int(kGramQueueWork / (int64_t(l) * l)) + 1 : INT32_MAX;
 }
+// A first QR of so few columns, in a register class, does not try the Gram: an
+// attempt that is kept saves 1 to 4 % of such a truncation (12 x 12, l = 8: 111.6
+// of 115.3 us), one that is refused costs 5 % (30 x 28 of rank 3, l = 8: 119.9 us
+// instead of 113.7).  Beyond, kept and refused, with an attempt / without: 30 x
+// 28, l = 16, 151 / 169 and 121 / 114; in size class 2 (2000 x 40, l = 4) 401 / 536.
+constexpr int kGramFirstMinL = 8;
 // Problems whose Gram-based QRs one wavefront does (both sketches).
 constexpr int kGqSmallRows = 64;
 __host__ __device__ inline bool gram_small(int m, int n, int l) {

@@ -242,3 +242,21 @@ def test_no_launch_marks_the_routes_of_small_problems(adaptive):
     drv = api.TEBD(dev, hb, 0.1, 16, p=4, q=1, trunc_eps=1e-10, seed=5, adaptive=adaptive, precision=1)
     launches = _kernels(lambda: (api.rrsvd_truncate(mats, 30, 10, 1, 1e-10), drv.step()))
     assert "k_chol_mark" not in launches
+
+
+@pytest.mark.parametrize("rank", [3, 0])
+@pytest.mark.parametrize("m,n,chi_max,p,tries", [(1, 1, 1, 0, False), (30, 28, 6, 2, False), (30, 28, 6, 3, True),
+                                                 (30, 28, 10, 6, True), (2000, 40, 3, 1, True)])
+def test_first_sketches_that_try_the_gram(m, n, chi_max, p, tries, rank):
+    # more than eight columns, or size class 2: an attempt before the pivoted QR,
+    # which takes what it refuses (rank 3); the four QRs of the power iterations and
+    # that of B^H follow
+    from test_gpu_fp32_products import _kernels
+    gen = wl.rng(m + p)
+    r = min(m, n, rank or n)
+    a = wl.known_spectrum(m, n, np.exp(-np.arange(r) / 4.0), gen)
+    out = []
+    launches = _kernels(lambda: out.append(rr._gpu([a], chi_max, p, 2, 1e-10)))
+    U, S, VH, chi, w, st = out[0]
+    assert launches["k_gram_qr"] == 5 + tries
+    rr._compare([a], (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, p, 2, 1e-10)
