@@ -111,7 +111,9 @@ def qr_bytes(rows, l, with_r=False):
 
 # The QRs without pivoting run as k_gram_qr, or as k_gram, k_chol and k_qapply for
 # large sketches, counted together under that name with a Householder QR's work.
-# A run that has no such kernel (FP32 products apart) took the Householder ones.
+# A run that has no such kernel took the Householder ones, as sweeps with FP32
+# products do in the size classes 0 and 1; their larger sketches have a Gram-based
+# QR of their own but for B^H.
 GRAM_QR = "k_gram_qr"
 GRAM_PARTS = ("k_gram<", "k_chol<", "k_qapply<")
 QR_KERNELS = ("k_qr_reg<512, 8, {}>", "k_qr_reg<1024, 12, {}>", "k_qr_lds<1024>", "k_qr_glb<1024>")
@@ -137,14 +139,17 @@ class Work:
             self._cls[key] = self.lib.tebd_size_class(0, rows, l)
         return self._cls[key]
 
-    def qr(self, rows, l_class, l, pivot, with_r=False):
-        name = QR_KERNELS[self.qr_class(rows, l_class)].format("true" if pivot else "false")
+    def qr(self, rows, l_class, l, pivot, with_r=False, mixed=False):
+        cls = self.qr_class(rows, l_class)
+        name = QR_KERNELS[cls].format("true" if pivot else "false")
         self.add(name, qr_flops(rows, l), qr_bytes(rows, l, with_r))
-        if not pivot:
+        if pivot or (mixed and cls < 2):
+            return
+        if with_r or not mixed:
             self.add(GRAM_QR, qr_flops(rows, l), qr_bytes(rows, l, with_r))
-            e = self.unpivoted.setdefault(name, [0.0, 0.0])
-            e[0] += qr_flops(rows, l)
-            e[1] += qr_bytes(rows, l, with_r)
+        e = self.unpivoted.setdefault(name, [0.0, 0.0])
+        e[0] += qr_flops(rows, l)
+        e[1] += qr_bytes(rows, l, with_r)
 
     def rrsvd_pass(self, m, n, l, q, mixed, chi_new, form=True):
         """Kernels of Alg. 1 and steps i-iii for one problem at width l
@@ -157,11 +162,11 @@ class Work:
         self.qr(m, lc, l, True)
         for _ in range(q):
             self.add(sk.format(1), f, mn + 16.0 * (m * l + n * l))
-            self.qr(n, lc, l, False)
+            self.qr(n, lc, l, False, mixed=mixed)
             self.add(sk.format(2), f, mn + 16.0 * (n * l + m * l))
-            self.qr(m, lc, l, False)
+            self.qr(m, lc, l, False, mixed=mixed)
         self.add("k_sketch<1>", f, mn + 16.0 * (m * l + n * l))   # B^H = A^H Q (FP64)
-        self.qr(n, lc, l, False, with_r=True)   # B^H = Q_B R_B, column order
+        self.qr(n, lc, l, False, with_r=True, mixed=mixed)   # B^H = Q_B R_B, column order
         c = chi_new
         if not form:
             return
