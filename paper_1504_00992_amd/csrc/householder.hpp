@@ -49,33 +49,6 @@ __host__ __device__ __forceinline__ int qr_class(int rows, int l) {
   return 3;
 }
 
-// rows l^2 beyond which a sketch's Gram-based QR is spread over the chip
-// (three or four launches) instead of run by one workgroup (one launch).
-// Measured, the six QRs of a truncation, one workgroup / tile queue: 512 x 20
-// (204800) 310 / 240 us, 256 x 40 (409600) 348 / 306, 512 x 58 915 / 417, 2048 x
-// 20 958 / 327.
-constexpr int64_t kGramQueueWork = 200000;
-// Not, up to this many rows, the sketches of the register classes: whole
-// truncations, one workgroup / tile queue, 190 x 180, l = 34, 541 / 571 us, l = 48
-// 652 / 679, 260 x 250, l = 30, 442 / 485, 300 x 290, l = 30, 465 / 467, and of
-// rank 6, where the launches are the time, 210 / 294, 207 / 291, 231 / 315, 242 /
-// 303; but 384 x 380, l = 32, 507 / 478.
-constexpr int kGramQueueRegRows = 320;
-// The padded 16 x 16 blocks of the factor need four l x l buffers (k_chol),
-// which hold one block from l = 8 on.
-constexpr int kGramQueueMinL = 8;
-// The fewest rows of a sketch of l columns that takes the tile queue.
-__host__ __device__ inline int gram_queue_rows(int l) {
-  if (l < kGramQueueMinL || l > kMaxL) return INT32_MAX;
-  const int by_work = int(kGramQueueWork / (int64_t(l) * l)) + 1;
-  int reg = 12 * reg_group(1024, l);  // rows of the register classes
-  if (reg > kGramQueueRegRows) reg = kGramQueueRegRows;
-  return by_work > reg ? by_work : reg + 1;
-}
-__host__ __device__ inline bool gram_queue_size(int rows, int l) {
-  return rows >= gram_queue_rows(l);
-}
-
 // Route bits (kGram*) of a problem with sketches m x l and n x l.  queue: the
 // tile queue is open to it; first: the first QR tries the Gram.  With FP32
 // products (mixed) the range finder's QRs of classes 2 and 3 take

@@ -266,6 +266,22 @@ enum {
   kGramF32M = 8,   // FP32 products: the m x l sketch takes launch_gram_f32
   kGramF32N = 16   // FP32 products: the n x l sketch takes launch_gram_f32
 };
+// rows l^2 beyond which a sketch's Gram-based QR is spread over the chip
+// (three or four launches) instead of run by one workgroup (one launch).
+// Measured, the six QRs of a truncation, one workgroup / tile queue: 256 x 30
+// (230400) 217 / 250 us, 512 x 20 (204800) 310 / 240, 256 x 40 (409600)
+// 348 / 306, 512 x 58 915 / 417, 2048 x 20 958 / 327.
+constexpr int64_t kGramQueueWork = 200000;
+// The padded 16 x 16 blocks of the factor need four l x l buffers (k_chol),
+// which hold one block from l = 8 on.
+constexpr int64_t kGramQueueMinL = 8;
+__host__ __device__ inline bool gram_queue_size(int64_t rows, int64_t l) {
+  return l >= kGramQueueMinL && rows * l * l > kGramQueueWork;
+}
+// The fewest rows of such a sketch of l columns.
+inline int gram_queue_rows(int l) {
+  return l >= kGramQueueMinL ? int(kGramQueueWork / (int64_t(l) * l)) + 1 : INT32_MAX;
+}
 // A first QR of so few columns, in a register class, does not try the Gram: an
 // attempt that is kept saves 1 to 4 % of such a truncation (12 x 12, l = 8: 111.6
 // of 115.3 us), one that is refused costs 5 % (30 x 28 of rank 3, l = 8: 119.9 us

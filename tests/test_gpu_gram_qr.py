@@ -260,22 +260,3 @@ def test_first_sketches_that_try_the_gram(m, n, chi_max, p, tries, rank):
     U, S, VH, chi, w, st = out[0]
     assert launches["k_gram_qr"] == 5 + tries
     rr._compare([a], (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, p, 2, 1e-10)
-
-
-@pytest.mark.parametrize("m,n,chi_max,p,queued", [
-    (192, 150, 48, 10, 0), (193, 150, 48, 10, 1), (150, 193, 48, 10, 1), (320, 300, 20, 10, 0),
-    (321, 300, 20, 10, 1), (96, 90, 70, 10, 0), (97, 90, 70, 10, 1), (250, 240, 18, 10, 0), (600, 550, 12, 10, 2)])
-@pytest.mark.parametrize("rank", [6, 0])
-def test_sketches_at_the_edge_of_the_tile_queue(m, n, chi_max, p, queued, rank):
-    # the register classes stay with a workgroup up to 320 rows (l = 58: 192 rows, l
-    # = 30: 320, l = 80: 96); queued: how many of the two sketches take the queue.
-    # Of full rank, and of rank 6, whose first sketch is refused.
-    from test_gpu_fp32_products import _kernels
-    gen = wl.rng(m + n)
-    r = rank or min(m, n)
-    a = wl.known_spectrum(m, n, np.exp(-np.arange(r) / (chi_max / 6.0)), gen)
-    out = []
-    launches = _kernels(lambda: out.append(rr._gpu([a], chi_max, p, 2, 1e-10)))
-    U, S, VH, chi, w, st = out[0]
-    assert sum(any(k.startswith(f"k_chol<{i}>") for k in launches) for i in (0, 1)) == queued
-    rr._compare([a], (U, S, VH, chi, w, st & ~_lib.DEV_QR_FALLBACK), chi_max, p, 2, 1e-10)
