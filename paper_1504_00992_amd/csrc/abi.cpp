@@ -699,7 +699,7 @@ __global__ void k_noalloc_desc(DescArgs a) {
   P.kcap = a.chi_max;
   P.k1 = a.chi_max;
   P.l1 = P.l2 = l;
-  P.chol = gram_bits(P.m, P.n, l, true, true, a.precision != 0);
+  P.chol = gram_bits(P.m, P.n, l, true, true, a.precision != 0, false);
   P.pid = b;
   P.mixed = a.precision;
   carve_slab(P, o.slab, o.m, o.n, l, 0, a.precision, kFrobSlices);
@@ -840,7 +840,7 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
       known[TK_SKN_W] += tiles_of<TK_SKN_W>(n[b], l);
       known[TK_SKM_S] += tiles_of<TK_SKM_S>(m[b], l);
       known[TK_SKN_S] += tiles_of<TK_SKN_S>(n[b], l);
-      known[TK_GQ_F] += gram_bits(int(m[b]), int(n[b]), int(l), true, true, false) & kGramFirst ? 1 : 0;
+      known[TK_GQ_F] += gram_bits(int(m[b]), int(n[b]), int(l), true, true, false, false) & kGramFirst ? 1 : 0;
     }
     {
       const int64_t tm = (m[b] + 63) / 64, tn = (n[b] + 63) / 64;
@@ -884,7 +884,7 @@ tebd_status rrsvd_enqueue(int64_t batch, const int64_t* m, const int64_t* n,
     P.kcap = prm->chi_max;
     P.k1 = prm->chi_max;
     P.l1 = P.l2 = P.l;
-    P.chol = gram_bits(P.m, P.n, P.l, true, true, prm->precision != 0);
+    P.chol = gram_bits(P.m, P.n, P.l, true, true, prm->precision != 0, false);
     P.pid = int32_t(b);
     P.mixed = prm->precision;
     carve_slab(P, slab, m[b], n[b], P.l, 0, prm->precision, kFrobSlices);

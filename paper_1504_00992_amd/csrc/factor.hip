@@ -127,7 +127,7 @@ __device__ __forceinline__ void plan_item(int t, Prob* probs, int nprob, const t
   P.l = bad ? 0 : l;
   P.k1 = k1;
   P.l1 = l;
-  P.chol = bad ? 0 : gram_bits(P.m, P.n, l, chol != 0, chol != 0 || cm >= kcap || qr_class(P.m, l) >= 3, mixed != 0);
+  P.chol = bad ? 0 : gram_bits(P.m, P.n, l, chol != 0, chol != 0 || cm >= kcap || qr_class(P.m, l) >= 3, mixed != 0, true);
   P.l2 = l2;
   P.retry = 0;
   P.kcap = kcap;

@@ -870,7 +870,7 @@ __global__ void k_chol_mark(Prob* probs, int nprob) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= nprob) return;
   Prob& P = probs[p];
-  P.chol = P.l > 0 ? gram_bits(P.m, P.n, P.l1, true, true, P.mixed != 0) : 0;
+  P.chol = P.l > 0 ? gram_bits(P.m, P.n, P.l1, true, true, P.mixed != 0, true) : 0;
   P.chol_ok = 0;
   P.chol_again = 0;
 }

@@ -50,15 +50,15 @@ __host__ __device__ __forceinline__ int qr_class(int rows, int l) {
 }
 
 // Route bits (kGram*) of a problem with sketches m x l and n x l.  queue: the
-// tile queue is open to it; first: the first QR tries the Gram.  With FP32
+// tile queue is open to it (in a sweep from size class 2 on); first: the first QR tries the Gram.  With FP32
 // products (mixed) the range finder's QRs of classes 2 and 3 take
 // launch_gram_f32 and the others the Householder kernels; the other bits
 // then only serve the QR of B^H.
 __host__ __device__ __forceinline__ int gram_bits(int m, int n, int l, bool queue, bool first,
-                                                  bool mixed) {
+                                                  bool mixed, bool sweep) {
   int b = first && (l > kGramFirstMinL || qr_class(m, l) >= 2) ? kGramFirst : 0;
-  if (queue && gram_queue_size(m, l)) b |= kGramTileM;
-  if (queue && gram_queue_size(n, l)) b |= kGramTileN;
+  if (queue && gram_queue_size(m, l) && (!sweep || qr_class(m, l) >= 2)) b |= kGramTileM;
+  if (queue && gram_queue_size(n, l) && (!sweep || qr_class(n, l) >= 2)) b |= kGramTileN;
   if (mixed && qr_class(m, l) >= 2) b |= kGramF32M;
   if (mixed && qr_class(n, l) >= 2) b |= kGramF32N;
   return b;

@@ -92,3 +92,33 @@ def test_tile_variants_give_the_same_bits():
     for o in outs[1:]:
         for x, y in zip(outs[0], o):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("chi", [24, 60])
+def test_rank_modes_agree_bitwise_where_a_sketch_may_be_large(chi, precision):
+    # d = 8: bonds of 192 rows and l = 40 (register class 1, of the queue's size) and of
+    # 480 rows and l = 85 (class 3); mode 1 knows the capacities, mode 2 the bonds.
+    # Gates near the identity: sketches of full rank whose first stage is accepted.
+    import test_gpu_tebd as tb
+    import torch
+    from paper_1504_00992_amd import _lib, api
+    dims, chis, n = [8] * 6, [1, 8, chi, chi, chi, 8, 1], 6
+    gam, lam = tb._random_chain(dims, chis, 41)
+    g = []
+    for b in range(n - 1):
+        h = wl.ginibre(64, 64, wl.rng(b))
+        ev, vec = np.linalg.eigh(h + h.conj().T)
+        g.append((vec * np.exp(-0.01j * ev)) @ vec.conj().T)
+    gates = torch.from_numpy(np.stack(g)).cuda()
+    state = []
+    for mode in (1, 2):
+        dev = api.DeviceMPS.from_host([(gam, lam)], dims, 64)
+        prm = _lib.params(64, 10, 1, 0.1, 1e-14, 1504, 3, precision, mode)
+        ws = api.BondWorkspace(dev, prm)
+        api.tebd_sweep(dev, gates, 0, prm, ws)
+        torch.cuda.synchronize()
+        assert not int(ws.status[0, 2]) & _lib.DEV_RANK_RETRY
+        state.append((dev.gamma.clone(), dev.lam.clone(), dev.chi.clone(), ws.disc.clone(), ws.status.clone()))
+    for x, y in zip(*state):
+        assert torch.equal(x, y)
