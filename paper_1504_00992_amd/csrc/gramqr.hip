@@ -326,25 +326,25 @@ __device__ __forceinline__ void apply_strip(int rows, int l, int nb, int r0, con
 }
 
 // One wavefront: tile (bi, bj) of G = Y^H Y over the rows [ra, re), Y
-// column-major with leading dimension ldy.  Lane t takes four consecutive
-// rows of columns 16 bi + t % 16 and 16 bj + t % 16 per 16 rows; the k-steps
-// go through them in that order, which permutes the sum only.  Columns beyond
-// l repeat the last one (the caller masks their products).
+// column-major with leading dimension ldy.  Lane t takes rows t / 16, 4 + t / 16,
+// ... of columns 16 bi + t % 16 and 16 bj + t % 16 per 16 rows: the order of
+// zgemm_tile, so that a sketch has the same Gram matrix on the tile queue.
+// Columns beyond l repeat the last one (the caller masks their products).
 // From LDS: the rows up to the next multiple of 16 hold zeros, no tests.
 __device__ __forceinline__ ZTile gram_tile_lds(const zt* ys, int ldy, int l, int bi, int bj, int ra,
                                                int re) {
   const int lane = threadIdx.x & 63, ti = lane & 15, tk = lane >> 4;
   const int ca = bi * 16 + ti, cb = bj * 16 + ti;
-  const zt* pa = ys + (ca < l ? ca : l - 1) * ldy + 4 * tk;
-  const zt* pb = ys + (cb < l ? cb : l - 1) * ldy + 4 * tk;
+  const zt* pa = ys + (ca < l ? ca : l - 1) * ldy + tk;
+  const zt* pb = ys + (cb < l ? cb : l - 1) * ldy + tk;
   ZTile c = tile_zero();
 #pragma unroll 2
   for (int r = ra; r < re; r += 16) {
     zt a[4], b[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      a[u] = pa[r + u];
-      b[u] = pb[r + u];
+      a[u] = pa[r + 4 * u];
+      b[u] = pb[r + 4 * u];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) tile_mma(c, zconj(a[u]), b[u]);
@@ -362,7 +362,7 @@ __device__ __forceinline__ ZTile gram_tile_glb(const zt* Y, int rows, int l, int
   auto load = [&](int r, zt (&a)[4], zt (&b)[4]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int k = r + 4 * tk + u;
+      const int k = r + 4 * u + tk;
       a[u] = zload_if(k < re, pa + k);
       b[u] = pb[k < re ? k : re - 1];
     }
@@ -463,8 +463,12 @@ __device__ __forceinline__ void gram_qr_problem(Prob& P, int which, int mode, in
   zt* ys = smem + ys_at;
   const bool first = mode & QRM_FIRST, want_r = mode & QRM_WANT_R;
   const int ntile = nb * (nb + 1) / 2;
-  // depth slices: 4 for one tile, 2 for three, else 1
-  const int lsl = rows < 64 || nb > 2 ? 0 : nb == 1 ? 2 : 1, slices = 1 << lsl;
+  // depth slices: 4 for one tile, 2 for three, else 1; of a sketch that is the
+  // tile queue's elsewhere, its chunks (one or two, see kGramQueueRegRows)
+  int lsl = rows < 64 || nb > 2 ? 0 : nb == 1 ? 2 : 1;
+  if (P.chol & (which ? kGramTileN : kGramTileM))
+    lsl = nb <= 2 && gram_chunks(rows, P.l1, gram_room(P)) > 1 ? 1 : 0;
+  const int slices = 1 << lsl;
   const int chunk = (((rows + slices - 1) >> lsl) + 15) & ~15;
   bool failed = false;
   for (int pass = 0; pass < 2; ++pass) {
@@ -726,7 +730,7 @@ __global__ __launch_bounds__(kGqThreads) void k_gram_qr(Prob* probs, const int32
       const int p = sh.todo[w];
       if (p < 0) continue;
       Prob& P = probs[p];
-      if (P.l == 0 || (P.chol & (which ? kGramTileN : kGramTileM))) continue;
+      if (P.l == 0 || (!(mode & QRM_ALL) && (P.chol & (which ? kGramTileN : kGramTileM)))) continue;
       if (not_tried(P, which ? P.n : P.m, mode)) {
         if (threadIdx.x == 0) P.chol_ok = 0;
         continue;
@@ -882,7 +886,9 @@ hipError_t launch_chol_mark(Prob* probs, const Common& c, hipStream_t s) {
 }
 
 bool gram_on_queue(const Common& c, int which) {
-  return c.chol && gram_queue_size(which ? c.nmax : c.mmax, c.lmax);
+  const int rows = which ? c.nmax : c.mmax;
+  return c.chol && gram_queue_size(rows, c.lmax) &&
+         (qr_class(rows, c.lmax) >= 2 || (!c.tebd && rows > kGramQueueRegRows));
 }
 
 hipError_t launch_gram_qr(Prob* probs, const Common& c, int which, int mode, hipStream_t s) {
@@ -904,6 +910,7 @@ hipError_t launch_gram_qr(Prob* probs, const Common& c, int which, int mode, hip
   const size_t lds = size_t(base) * sizeof(zt);
   hipError_t e = hipSuccess;
   const bool queue = gram_on_queue(c, which);
+  if (!queue) mode |= QRM_ALL;
   if (queue) {
     const int passes = mode & QRM_STRICT ? 2 : 1;
     for (int pass = 0; pass < passes && e == hipSuccess; ++pass) {

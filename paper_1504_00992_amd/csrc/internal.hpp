@@ -272,6 +272,14 @@ enum {
 // (230400) 217 / 250 us, 512 x 20 (204800) 310 / 240, 256 x 40 (409600)
 // 348 / 306, 512 x 58 915 / 417, 2048 x 20 958 / 327.
 constexpr int64_t kGramQueueWork = 200000;
+// A launch with none beyond the register classes and this many rows leaves the
+// queue out (the workgroup adds the same sums, kGramTile* bits tell it the
+// chunks): whole truncations, workgroups / queue, 190 x 180, l = 34, 541 / 570
+// us, l = 48 651 / 677, 260 x 250, l = 30, 458 / 483, and of rank 6, where the
+// launches are the time, 230 / 297, 228 / 294, 254 / 316; but 384 x 380, l = 32,
+// 507 / 478.  Beside larger sketches, whose queue runs anyway, its small ones go
+// there too: 16 ragged matrices up to 640 x 500, l = 58, 1.78 / 1.31 ms.
+constexpr int kGramQueueRegRows = 320;
 // The padded 16 x 16 blocks of the factor need four l x l buffers (k_chol),
 // which hold one block from l = 8 on.
 constexpr int64_t kGramQueueMinL = 8;
@@ -340,6 +348,7 @@ enum {
   QRM_FIRST = 1,   // the QR of Y0 = A Omega: the Householder kernels reveal the rank of what it refuses
   QRM_STRICT = 2,  // the columns must be orthonormal to rounding (a second pass where one is not enough)
   QRM_WANT_R = 4,  // also R (into Rb, column order)
+  QRM_ALL = 64,    // (launch_gram_qr's own) no tile queue: a workgroup takes its sketches too
   // FP32 products: their rounding fills up the columns beyond a problem's rank,
   // and A^H of those is almost parallel: the QR of B^H refuses such problems, and
   // leaves them to the Householder kernels in the register classes 0 and 1

@@ -95,6 +95,33 @@ def test_tile_variants_give_the_same_bits():
 
 
 @pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("m,n,chi_max,rank", [
+    (190, 180, 24, 0), (190, 170, 38, 0), (192, 190, 54, 0), (260, 250, 20, 0), (300, 257, 20, 0),
+    (320, 300, 20, 0), (321, 300, 20, 0), (384, 380, 22, 0), (96, 90, 80, 0), (190, 180, 24, 6), (300, 257, 20, 6)])
+def test_a_register_class_sketch_on_and_off_the_tile_queue(m, n, chi_max, rank, precision):
+    # alone and beside its like a workgroup takes it, beside a larger one the queue:
+    # the same Gram matrix (one chunk of rows below 256, two from there on), factor,
+    # second pass and Q
+    import torch
+    from test_gpu_fp32_products import _kernels
+    gen = wl.rng(m + n)
+
+    def mat(rows, cols, r):
+        s = np.exp(-np.arange(r or min(rows, cols)) / 12.0)
+        return torch.from_numpy(wl.known_spectrum(rows, cols, s, gen)).cuda()
+    a, large = mat(m, n, rank), mat(700, 500, 0)
+    out = []
+    kernels = [_kernels(lambda: out.append(_first(x, chi_max, 10, precision)))
+               for x in ([a], [a] * 5, [a, large], [a] + [large] * 7 + [a] * 3)]
+    if precision == 0:
+        on_queue = [any(k.startswith("k_chol<") for k in x) for x in kernels]
+        assert on_queue == [m > 320, m > 320, True, True]
+    for o in out[1:]:
+        for x, y in zip(out[0], o):
+            assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("chi", [24, 60])
 def test_rank_modes_agree_bitwise_where_a_sketch_may_be_large(chi, precision):
     # d = 8: bonds of 192 rows and l = 40 (register class 1, of the queue's size) and of
